@@ -219,7 +219,7 @@ int run_dev(int B, int d, int m, int N, const void* H0, const void* Hc, const vo
   L.total_slices = B * N;
   L.total_chunks = B * Lo.P;
   L.max_m = m;
-  L.flags = flags;
+  L.flags = flags | (opt.generators ? qoc::RUN_GENERAL : 0);
   L.stream = st;
   L.scratch = Lo.scratch_bytes ? base + Lo.scratch : nullptr;
   L.dyn = nullptr;

@@ -195,6 +195,18 @@ __device__ __forceinline__ void panel_axpby(Panel<T, D>& Y, T a, const Panel<T, 
   }
 }
 
+// Y += a * X, one rounding per element
+template <typename T, int D>
+__device__ __forceinline__ void panel_fma(Panel<T, D>& Y, T a, const Panel<T, D>& X) {
+#pragma unroll
+  for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      Y.re[rb][r] = fma(a, X.re[rb][r], Y.re[rb][r]);
+      Y.im[rb][r] = fma(a, X.im[rb][r], Y.im[rb][r]);
+    }
+}
+
 template <typename T, int D>
 __device__ __forceinline__ void panel_scale(Panel<T, D>& Y, T a) {
 #pragma unroll

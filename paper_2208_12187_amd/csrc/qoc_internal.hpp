@@ -53,6 +53,7 @@ struct ProbDesc {
   void* grp;          // 4 x PG PF matrices: forward and backward group totals, then the
                       // forward and backward carries into each group
   double* g;          // complex128 Tr(V^dag X_N)
+  double* vscale;     // power of two by which k_prep divided the stored target
   double* diag;       // [0] ||X_N^dag X_N - I||_F; [1] largest chunk residual (FP64
                       // bits, atomic max); [2] re-unitarisation steps (uint64 count)
   double reun_tol;    // re-unitarisation threshold for chunk totals, < 0: off
@@ -289,6 +290,7 @@ inline void fill_desc(ProbDesc& P, const Layout& Lo, char* pb, int d, int m, int
   P.g = small;                    // 2 doubles
   P.F = F ? F : small + 2;        // 1 double
   P.diag = diag ? diag : small + 4;  // 4 doubles
+  P.vscale = small + 8;              // 1 double
   P.reun_tol = reun_tol;
 }
 

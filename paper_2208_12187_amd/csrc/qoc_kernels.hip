@@ -25,6 +25,7 @@
 #include "qoc_internal.hpp"
 #include "qoc_plan.hpp"
 #include "qoc_bf16.hpp"
+#include "qoc_f16.hpp"
 
 namespace qoc {
 
@@ -138,27 +139,23 @@ __device__ __forceinline__ void control_rows(const ProbDesc& P, int j, const dou
     gp(P.mok)[j] = (!any && !(P.flags & CTRL_DENSE)) ? (1 | (bij && P.minv ? 2 : 0) | (all_same ? 4 : 0)) : 0;
 }
 
-// True when every control of the problem has a usable row table (at most
-// one nonzero per row, dense kernels not forced).  Uniform across the
-// workgroup.
-__device__ __forceinline__ bool controls_monomial(const ProbDesc& P) {
-  for (int j = 0; j < P.m; ++j)
-    if (!gp(P.mok)[j]) return false;
-  return true;
-}
-
-// True when every control's row table is also a bijection from rows to
-// columns (minv holds its inverse).  (All the flags are loaded together.)
-__device__ __forceinline__ bool controls_permutation(const ProbDesc& P) {
-  int all = 2;
+// The flags that every control of the problem has: bit 0, a usable row table
+// (at most one nonzero per row, dense kernels not forced); bit 1, the table is
+// also a bijection from rows to columns (minv holds its inverse).  (All the
+// flags are loaded together.)
+__device__ __forceinline__ int controls_flags(const ProbDesc& P) {
+  int all = 3;
   for (int j = 0; j < P.m; ++j) all &= gp(P.mok)[j];
-  return all != 0;
+  return all;
 }
 
 // Bit 24 of a slice's packed plan: the FP32 adjoint may sample its last step
 // there (s = 0 and permutation controls), so that the adjoint's two instances
 // split the slices with the one load of the plan.
 constexpr int kPlanSampled = 1 << 24;
+// Bit 25: every control has a usable row table (controls_flags), so that a
+// slice's workgroup does not walk the m flags, one dependent load each.
+constexpr int kPlanMono = 1 << 25;
 
 // Convert the caller's complex128 matrices to the compute precision: H0 and
 // Hc[j] to planar D x D (zero padded), V to PF; also the FP64 one-norms
@@ -217,13 +214,26 @@ __device__ __forceinline__ void prep_one(const ProbDesc& P, int mat, double* col
     if (mat > 0) control_rows<T, D>(P, mat - 1, src);
     __syncthreads();
   } else if (P.Vz != nullptr && P.Vint != nullptr) {
+    // V / 2^e with 2^e <= |V|_F < 2^(e+1): no entry of the costates exceeds 2,
+    // whatever the target, as the FP16 split of their products assumes.  The
+    // gradient is linear in V and takes the exact factor back (grad_put).
+    double f2 = 0;
+    for (int e = threadIdx.x; e < 2 * d * d; e += 256) f2 = fma(P.Vz[e], P.Vz[e], f2);
+    f2 = wave_sum(f2);
+    if ((threadIdx.x & 63) == 0) colmax[threadIdx.x >> 6] = f2;
+    __syncthreads();
+    const double nf = sqrt((colmax[0] + colmax[1]) + (colmax[2] + colmax[3]));
+    int ex = 1;
+    if (nf > 0 && nf < 1e300) (void)frexp(nf, &ex);
+    const double dn = ldexp(1.0, 1 - ex);
+    if (threadIdx.x == 0) *P.vscale = ldexp(1.0, ex - 1);
     T* dst = reinterpret_cast<T*>(P.Vint);
     for (int e = threadIdx.x; e < D * D; e += 256) {
       int row = e / D, col = e % D;
       double re = 0, im = 0;
       if (row < d && col < d) {
-        re = P.Vz[2 * (row * d + col)];
-        im = P.Vz[2 * (row * d + col) + 1];
+        re = dn * P.Vz[2 * (row * d + col)];
+        im = dn * P.Vz[2 * (row * d + col) + 1];
       }
       int w = col >> 4, c16 = col & 15, rb = row >> 4, rr = row & 15;
       int r, g;
@@ -266,7 +276,8 @@ __global__ __launch_bounds__(256) void k_plan(Work W, double ur, int flags) {
     for (int j = 0; j < P.m; ++j) th = fma(fabs(gp(P.u)[(size_t)j * P.N + k]), gp(P.norms)[j + 1], th);
     th *= P.dt;
     const SlicePlan pl = choose_plan(th, ur, (flags & 1) != 0, (flags & 2) != 0);
-    P.sq[k] = pack_plan(pl) | (pl.s == 0 && controls_permutation(P) ? kPlanSampled : 0);
+    const int cf = controls_flags(P);
+    P.sq[k] = pack_plan(pl) | (pl.s == 0 && (cf & 2) ? kPlanSampled : 0) | ((cf & 1) ? kPlanMono : 0);
   }
 }
 
@@ -591,13 +602,14 @@ constexpr int kEpiDense = 8;
 
 // Stores the gradient entry (j, k) from T_j = a + i b.
 __device__ __forceinline__ void grad_put(const ProbDesc& P, int j, int k, double a, double b) {
+  const double dt = P.dt * gp(P.vscale)[0];  // Z_k is that of the normalised target
   if (P.flags & RUN_RAWDG) {
     // dg/du[j][k] = -i dt Tr(Z_k^dag Hc[j]), complex interleaved
     const size_t o = 2 * ((size_t)j * P.N + k);
-    gp(P.grad)[o] = P.dt * b;
-    gp(P.grad)[o + 1] = -P.dt * a;
+    gp(P.grad)[o] = dt * b;
+    gp(P.grad)[o + 1] = -dt * a;
   } else {
-    const double pref = 2.0 * P.dt / ((double)P.d * P.d);
+    const double pref = 2.0 * dt / ((double)P.d * P.d);
     gp(P.grad)[(size_t)j * P.N + k] = pref * (gp(P.g)[0] * b - gp(P.g)[1] * a);
   }
 }
@@ -745,7 +757,6 @@ __device__ __forceinline__ void gradient_epilogue(const ProbDesc& P, int k, cons
 // Delta_k = U_k - I for every slice: one workgroup per slice, D/16 wavefronts.
 // Horner in delta form: R_q = I + X/q, R_i = I + X R_{i+1} / i, Delta = X R_2
 // (X = A_k / 2^s), then s squarings Delta <- 2 Delta + Delta^2.
-// FP32 gradient runs at D >= 32 keep X^2 for the adjoint (keep_square).
 // (Paterson-Stockmeyer in X^2, which would form X^2 as a product, needs the
 // same two products at q = 3 but held 40 more VGPRs at d = 64, a workgroup
 // per CU less, and was 0.4 ms slower on the d = 64 batch of 32.)
@@ -765,27 +776,6 @@ constexpr bool kKeepH = D >= 32;
 // the extra fragment registers would add to its spills.
 template <typename T>
 constexpr int kExpmPairs = sizeof(T) == 4 ? 2 : 1;
-// FP32 keeps X2 = (A_k / 2^s)^2 for the adjoint at D >= 32 (where the
-// workspace has room for it: not for the split-BF16 adjoint, P.x2 null); in
-// FP64 the read-back would make the d = 64 adjoint spill, and it forms X2
-// itself.
-template <typename T>
-constexpr bool kKeepX2 = sizeof(T) == 4;
-
-// The first Horner product is P1 = X (I + X/q) = X + X^2/q, so
-// X^2 = q (P1 - X) comes without a product of its own (X re-read from LDS).
-// Its error, about q u |X| against |X^2|, enters the adjoint's Z only through
-// terms of size |X^2| |E|, so Z keeps an error of order q u |X| |E|.  For
-// Hermitian H_k the adjoint's X = A_k^dag / 2^s = -A_k / 2^s has the same
-// square.
-template <typename T, int D, typename Ops>
-__device__ __forceinline__ void keep_square(T* out, const Panel<T, D>& P1, const void* lds, int q, const Lane& L) {
-  Panel<T, D> X;
-  Ops::load(X, lds, L);
-  panel_axpby(X, (T)q, P1, (T)-q);
-  panel_store(out, X, L);
-}
-
 // The FP32 d = 64 expm (one slice per workgroup) takes a floor of four waves
 // per SIMD: it needs 130 VGPRs otherwise, and at 128 (two spilled) four
 // workgroups share a CU instead of three (expm 1.88 -> 1.80 ms on the d = 64
@@ -804,19 +794,18 @@ void k_expm(Work W) {
   split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
   const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
   int s, q, qb;
-  unpack_sq(gp(P.sq)[k], s, q, qb);
+  const int sqk = gp(P.sq)[k];
+  unpack_sq(sqk, s, q, qb);
   T* hk = (kKeepH<D> && (P.flags & RUN_GRAD)) ? pf_mat<T, D>(P.hk, k - W.rg.kbase) : nullptr;
-  assemble<T, D, Ops>(lds, P, k, ldexp(P.dt, -s), 1.0, hk, controls_monomial(P));
+  assemble<T, D, Ops>(lds, P, k, ldexp(P.dt, -s), 1.0, hk, (sqk & kPlanMono) != 0);
   __syncthreads();
   Panel<T, D> R, acc;
   Ops::load(R, lds, L);
-  T* x2 = (kKeepX2<T> && hk && P.x2) ? pf_mat<T, D>(P.x2, k - W.rg.kbase) : nullptr;
   if (q >= 2) {
     panel_scale(R, (T)(1.0 / q));
     panel_add_identity(R, L, (T)1);
     for (int i = q - 1; i >= 1; --i) {
       Ops::template gemm3<kExpmPairs<T>>(acc, lds, R, L, true);
-      if (x2 && i == q - 1) keep_square<T, D, Ops>(x2, acc, lds, q, L);
       R = acc;
       if (i >= 2) {
         panel_scale(R, (T)(1.0 / i));
@@ -933,9 +922,11 @@ constexpr int kScanBufs = (sizeof(T) == 4 && D == 64) ? 1 : 2;
 
 template <typename T, int D, typename Ops, bool PERSIST>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kMinWaves<D>)))
-void k_scan_local(Work W, int dir) {
+void k_scan_local(Work W, int dir, T dscale) {
   __shared__ __align__(16) unsigned char lds[kScanBufs<T, D>][Ops::BYTES];
-  const int bwd = dir < 0 ? (int)blockIdx.y : dir;  // dir < 0: both passes, one per blockIdx.y
+  const int bwd = dir < 0 ? (int)blockIdx.y : dir & 1;  // dir < 0: both passes, one per blockIdx.y
+  const bool keep = dir != 2;  // dir = 2: forward, the chunk totals only
+  // dscale: 1 over the power of two by which the stored Delta is scaled
   Lane L;
   const Items I(W);
   for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
@@ -956,11 +947,11 @@ void k_scan_local(Work W, int dir) {
     const int kn = bwd ? k - 1 : k + 1;
     // the store of S before the prefetch of the next Delta, so that the wait
     // for the prefetch at the next step covers nothing issued after it
-    panel_store(pf_mat<T, D>(bwd ? P.bloc : P.xprev, k - W.rg.kbase), S, L);
+    if (keep) panel_store(pf_mat<T, D>(bwd ? P.bloc : P.xprev, k - W.rg.kbase), S, L);
     if (i + 1 < n) panel_load(nxt, pf_mat<T, D>(P.delta, kn - W.rg.kbase), L);
     __syncthreads();
     Ops::gemm3(acc, buf, S, L, true);
-    panel_axpby(S, (T)1, acc, (T)1);
+    panel_axpby(S, dscale, acc, (T)1);
     k = kn;
   }
   if (!bwd && !W.rg.recompute) panel_store(pf_mat<T, D>(P.tf, c), S, L);  // (k_reun follows in FP32)
@@ -1011,20 +1002,20 @@ __global__ __launch_bounds__(4 * D) void k_reun(Work W) {
 // n steps of S <- A_i S, storing S before each step to out[i] (i < nstore).
 // A_i is the PF matrix src[i] (stride step) or, with ct, its conjugate
 // transpose.  Double-buffered LDS; the next factor is loaded during a step.
-template <typename T, int D>
+template <typename T, int D, typename Ops>
 __device__ __forceinline__ void carry_chain(Panel<T, D>& S, const T* src, int step, int n, bool ct, T* out,
-                                            int ostep, int nstore, T (*lds)[Mat<T, D>::LDS_ELEMS], const Lane& L) {
+                                            int ostep, int nstore, unsigned char (*lds)[Ops::BYTES], const Lane& L) {
   constexpr int EL = Mat<T, D>::ELEMS;
   Panel<T, D> nxt, acc;
   if (n > 0) panel_load(nxt, src, L);
   for (int i = 0; i < nstore || i < n; ++i) {
     if (i < nstore) panel_store(out + (ptrdiff_t)i * ostep * EL, S, L);
     if (i >= n) break;
-    T* buf = lds[i & 1];
-    if (ct) panel_to_lds_ct(buf, nxt, L); else panel_to_lds(buf, nxt, L);
+    void* buf = lds[i & 1];
+    if (ct) Ops::store_ct(buf, nxt, L); else Ops::store(buf, nxt, L);
     if (i + 1 < n) panel_load(nxt, src + (ptrdiff_t)(i + 1) * step * EL, L);
     __syncthreads();
-    if constexpr (D >= 32) cgemm3m(acc, buf, S, L, true); else cgemm(acc, buf, S, L, true);
+    Ops::gemm3(acc, buf, S, L, true);
     S = acc;
   }
 }
@@ -1036,9 +1027,9 @@ __device__ __forceinline__ T* grp_mat(const ProbDesc& P, int kind, int g) {
   return pf_mat<T, D>(P.grp, kind * P.PG + g);
 }
 
-template <typename T, int D>
+template <typename T, int D, typename Ops>
 __global__ __launch_bounds__(4 * D) void k_carry_grp(Work W) {
-  __shared__ T lds[2][Mat<T, D>::LDS_ELEMS];
+  __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
   Lane L;
   const int bwd = blockIdx.y;
   const Items I(W);
@@ -1051,21 +1042,21 @@ __global__ __launch_bounds__(4 * D) void k_carry_grp(Work W) {
   Panel<T, D> S;
   panel_identity(S, L);
   if (!bwd) {
-    carry_chain<T, D>(S, pf_mat<T, D>(P.tf, c0), 1, n, false, pf_mat<T, D>(P.cf, c0), 1, n, lds, L);
+    carry_chain<T, D, Ops>(S, pf_mat<T, D>(P.tf, c0), 1, n, false, pf_mat<T, D>(P.cf, c0), 1, n, lds, L);
     panel_store(grp_mat<T, D>(P, 0, g), S, L);
   } else {
     const int c1 = c0 + n - 1;  // the chain runs from the group's last chunk down
-    carry_chain<T, D>(S, pf_mat<T, D>(P.tf, c1), -1, n, true, pf_mat<T, D>(P.cb, c1), -1, n, lds, L);
+    carry_chain<T, D, Ops>(S, pf_mat<T, D>(P.tf, c1), -1, n, true, pf_mat<T, D>(P.cb, c1), -1, n, lds, L);
     panel_store(grp_mat<T, D>(P, 1, g), S, L);
   }
   __syncthreads();
   }
 }
 
-template <typename T, int D>
+template <typename T, int D, typename Ops>
 __global__ __launch_bounds__(4 * D) void k_carry_top(Work W) {
   constexpr int NW = Mat<T, D>::NW;
-  __shared__ T lds[2][Mat<T, D>::LDS_ELEMS];
+  __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
   __shared__ double red[2 * NW];
   Lane L;
   const int bwd = blockIdx.y;
@@ -1076,17 +1067,17 @@ __global__ __launch_bounds__(4 * D) void k_carry_top(Work W) {
   const int ng = P.PG;
   if (!bwd) {
     panel_identity(S, L);
-    carry_chain<T, D>(S, grp_mat<T, D>(P, 0, 0), 1, ng, false, grp_mat<T, D>(P, 2, 0), 1, ng, lds, L);
+    carry_chain<T, D, Ops>(S, grp_mat<T, D>(P, 0, 0), 1, ng, false, grp_mat<T, D>(P, 2, 0), 1, ng, lds, L);
     fidelity_epilogue<T, D>(P, S, L, red);
     // Unitarity residual of X_N: S^dag S from the conjugate transpose in LDS.
     __syncthreads();
-    panel_to_lds_ct(lds[0], S, L);
+    Ops::store_ct(lds[0], S, L);
     __syncthreads();
-    cgemm(acc, lds[0], S, L, true);
+    Ops::gemm(acc, lds[0], S, L, true);
     residual_epilogue<T, D>(P, acc, L, red);
   } else {
     panel_load(S, reinterpret_cast<const T*>(P.Vint), L);
-    carry_chain<T, D>(S, grp_mat<T, D>(P, 1, ng - 1), -1, ng - 1, false, grp_mat<T, D>(P, 3, ng - 1), -1, ng,
+    carry_chain<T, D, Ops>(S, grp_mat<T, D>(P, 1, ng - 1), -1, ng - 1, false, grp_mat<T, D>(P, 3, ng - 1), -1, ng,
                       lds, L);
   }
   __syncthreads();
@@ -1096,9 +1087,9 @@ __global__ __launch_bounds__(4 * D) void k_carry_top(Work W) {
 // mc[c] = cb[c] cf[c]^dag for every chunk, the start of its backward scan, so
 // that W_k = (local backward product) mc[c] xprev[k]^dag; cf[c] and cb[c] are
 // formed here from the in-group carries and the group carries.
-template <typename T, int D>
+template <typename T, int D, typename Ops>
 __global__ __launch_bounds__(4 * D) void k_mc(Work W) {
-  __shared__ T lds[2][Mat<T, D>::LDS_ELEMS];
+  __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
   Lane L;
   const Items I(W);
   for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
@@ -1112,23 +1103,18 @@ __global__ __launch_bounds__(4 * D) void k_mc(Work W) {
   panel_load(b, pf_mat<T, D>(P.cb, c), L);
   panel_load(x, grp_mat<T, D>(P, 2, g), L);
   panel_load(y, grp_mat<T, D>(P, 3, g), L);
-  panel_to_lds(lds[0], a, L);
-  panel_to_lds(lds[1], b, L);
+  Ops::store(lds[0], a, L);
+  Ops::store(lds[1], b, L);
   __syncthreads();
-  if constexpr (D >= 32) {
-    cgemm3m(a, lds[0], x, L, true);
-    cgemm3m(b, lds[1], y, L, true);
-  } else {
-    cgemm(a, lds[0], x, L, true);
-    cgemm(b, lds[1], y, L, true);
-  }
+  Ops::gemm3(a, lds[0], x, L, true);
+  Ops::gemm3(b, lds[1], y, L, true);
   // mc[c] = cb[c] cf[c]^dag
   __syncthreads();
-  panel_to_lds(lds[0], b, L);
-  panel_to_lds(lds[1], a, L);
+  Ops::store(lds[0], b, L);
+  Ops::store(lds[1], a, L);
   __syncthreads();
-  panel_from_lds_ct(x, lds[1], L);
-  cgemm(a, lds[0], x, L, true);
+  Ops::load_ct(x, lds[1], L);
+  Ops::gemm(a, lds[0], x, L, true);
   panel_store(pf_mat<T, D>(P.mc, c), a, L);
   __syncthreads();
   }
@@ -1390,7 +1376,7 @@ void k_adjoint(Work W) {
       else return;
     }
   }
-  const bool mono = controls_monomial(P);
+  const bool mono = (sqk & kPlanMono) != 0;
   Panel<T, D> R1, R2, A1, A2;
 
   // 1. W = bloc[k] xprev[k]^dag (bloc carries mc[c]).  The slice's global
@@ -1433,12 +1419,7 @@ void k_adjoint(Work W) {
   int ga[kSampleGather / 4];
   if constexpr (GATHER) sample_rows<D>(P, ga);
   Ops::load(R1, X, L);  // R1 = X, R2 = E
-  // A1 = X2: kept by the expm pass where it keeps H_k and forms its own
-  // square (q >= 2; for Hermitian H_k its X X equals this X X); general
-  // generators form it here.
-  if (kKeepH<D> && kKeepX2<T> && q >= 2 && P.x2 && !(P.flags & RUN_GENERAL))
-    panel_load(A1, pf_mat<T, D>(P.x2, k - W.rg.kbase), L);
-  else Ops::gemm3(A1, X, R1, L, true);
+  Ops::gemm3(A1, X, R1, L, true);  // A1 = X2
   gemm3p<AP, Ops>(A2, X, R2, L, true);
   gemm3p<AP, Ops>(A2, E, R1, L, false);  // A2 = S
   if constexpr (GATHER) sample_gather<D>(P, ga, E, eg);
@@ -1510,6 +1491,371 @@ void k_adjoint(Work W) {
   }
   if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
   __syncthreads();
+  }
+}
+
+// ================================================================ FP32 on the FP16 matrix cores
+//
+// The FP32 expm, costate scan and adjoint at 32 <= D <= 64 for Hermitian
+// Hamiltonians, with their products on F16Ops.  Panels and the stored Delta_k
+// and W_k carry its factor c = kF16Scale.
+
+// X = -i c H_k as this wavefront's panel (FP32), H_k = H0 + sum_j u[j][k] Hc[j]
+// with the sums of assemble(); lds holds one planar FP32 matrix and is free
+// again after the caller's next barrier.
+template <int D>
+__device__ __forceinline__ void assemble_panel(Panel<float, D>& X, void* lds, const ProbDesc& P, int k, double c,
+                                               bool mono, const Lane& L) {
+  constexpr int NV = D / 16;
+  constexpr int NT = 4 * D;
+  const float* H = reinterpret_cast<const float*>(P.Hint);
+  float* pl = static_cast<float*>(lds);
+  float* pi = pl + D * Mat<float, D>::SD;
+  const int e0 = 4 * threadIdx.x;
+  f4 hr[NV], hi[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    hr[v] = Prec<float>::gld4(H + e0 + 4 * NT * v);
+    hi[v] = Prec<float>::gld4(H + D * D + e0 + 4 * NT * v);
+  }
+  if (!mono) {
+    constexpr int G = 2;  // controls loaded together
+    for (int j0 = 0; j0 < P.m; j0 += G) {
+      f4 ar[G][NV], ai[G][NV];
+      float uw[G];
+#pragma unroll
+      for (int jj = 0; jj < G; ++jj) {
+        const int j = min(j0 + jj, P.m - 1);
+        uw[jj] = j0 + jj < P.m ? (float)gp(P.u)[(size_t)j * P.N + k] : 0.0f;
+        const float* Hj = H + (size_t)(j + 1) * 2 * D * D + e0;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          ar[jj][v] = Prec<float>::gld4(Hj + 4 * NT * v);
+          ai[jj][v] = Prec<float>::gld4(Hj + D * D + 4 * NT * v);
+        }
+      }
+#pragma unroll
+      for (int jj = 0; jj < G; ++jj)
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            hr[v][i] = fmaf(uw[jj], ar[jj][v][i], hr[v][i]);
+            hi[v][i] = fmaf(uw[jj], ai[jj][v][i], hi[v][i]);
+          }
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int e = e0 + 4 * NT * v;
+    const int off = lds_off<float, D>(e / D, e % D);
+    Prec<float>::st4(pl + off, hr[v]);
+    Prec<float>::st4(pi + off, hi[v]);
+  }
+  __syncthreads();
+  if (mono) {
+    // The thread of row a adds the row's entry of each control in turn; runs of
+    // controls at the same column (X_i and Y_i) stay in registers, and the
+    // tables of G controls are loaded together.
+    if ((int)threadIdx.x < D) {
+      constexpr int G = 4;
+      const int a = threadIdx.x;
+      const float* mv = reinterpret_cast<const float*>(P.mval);
+      int off = -1;
+      float sr = 0.0f, si = 0.0f;
+      for (int j0 = 0; j0 < P.m; j0 += G) {
+        int col[G];
+        float vr[G], vi[G], uj[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+          const int j = min(j0 + i, P.m - 1);
+          const size_t idx = (size_t)j * D + a;
+          col[i] = gp(P.mcol)[idx];
+          vr[i] = gp(mv)[2 * idx];
+          vi[i] = gp(mv)[2 * idx + 1];
+          uj[i] = (float)gp(P.u)[(size_t)j * P.N + k];
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+          if (j0 + i < P.m) {
+            const int o = lds_off<float, D>(a, col[i]);
+            if (o != off) {
+              if (off >= 0) {
+                pl[off] = sr;
+                pi[off] = si;
+              }
+              off = o;
+              sr = pl[o];
+              si = pi[o];
+            }
+            sr = fmaf(uj[i], vr[i], sr);
+            si = fmaf(uj[i], vi[i], si);
+          }
+        }
+      }
+      pl[off] = sr;
+      pi[off] = si;
+    }
+    __syncthreads();
+  }
+  // c in two FP32 numbers: its rounding alone would be the same relative error
+  // in every slice, and add up over the chain
+  const float f = (float)c, fl = (float)(c - (double)f);
+  panel_from_lds(X, static_cast<const float*>(lds), L);
+#pragma unroll
+  for (int rb = 0; rb < NV; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float xr = X.re[rb][r], xi = X.im[rb][r];
+      X.re[rb][r] = fmaf(f, xi, fl * xi);  // -i c (xr + i xi)
+      X.im[rb][r] = -fmaf(f, xr, fl * xr);
+    }
+}
+
+// c (U_k - I) of the plan (s, q) from X = c A_k / 2^s (panel), A_k being
+// anti-Hermitian: Horner in delta form, D <- (X + X D) / i for i = q - 1 ... 1
+// from D = X / q, then s squarings.  lds: one F16Ops matrix, in use until the
+// caller's next barrier; starts with a barrier (the LDS may still be read).
+template <int D>
+__device__ __forceinline__ void taylor_delta(Panel<float, D>& R, const Panel<float, D>& X, void* lds, int s, int q,
+                                             const Lane& L) {
+  using Ops = F16Ops<D>;
+  __syncthreads();
+  Ops::store_nct(lds, X, L);  // X = -X^dag
+  __syncthreads();
+  R = X;
+  if (q >= 2) {
+    panel_scale(R, (float)(1.0 / q));
+    Panel<float, D> acc;
+    for (int i = q - 1; i >= 1; --i) {
+      Ops::gemm(acc, lds, R, L, true);
+      const float ri = (float)(1.0 / i), rs = ri * kF16Inv;
+#pragma unroll
+      for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          R.re[rb][r] = fmaf(rs, acc.re[rb][r], ri * X.re[rb][r]);
+          R.im[rb][r] = fmaf(rs, acc.im[rb][r], ri * X.im[rb][r]);
+        }
+    }
+  }
+  for (int j = 0; j < s; ++j) {
+    Panel<float, D> acc;
+    __syncthreads();
+    Ops::store(lds, R, L);
+    __syncthreads();
+    Ops::gemm(acc, lds, R, L, true);
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        R.re[rb][r] = fmaf(kF16Inv, acc.re[rb][r], 2.0f * R.re[rb][r]);
+        R.im[rb][r] = fmaf(kF16Inv, acc.im[rb][r], 2.0f * R.im[rb][r]);
+      }
+  }
+}
+
+// Delta_k = c (U_k - I); gradient runs with dense controls also keep X (in
+// hk), which the adjoint then need not assemble again from m + 1 matrices.
+template <int D, bool PERSIST>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void k_expm_f16(Work W) {
+  using Ops = F16Ops<D>;
+  static_assert(Mat<float, D>::LDS_ELEMS * 4 <= Ops::BYTES, "one planar FP32 matrix");
+  __shared__ __align__(16) unsigned char lds[Ops::BYTES];
+  Lane L;
+  const Items I(W);
+  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+    int p, k;
+    split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
+    const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
+    const int sqk = gp(P.sq)[k];
+    int s, q, qb;
+    unpack_sq(sqk, s, q, qb);
+    const bool mono = (sqk & kPlanMono) != 0;
+    Panel<float, D> X, R;
+    assemble_panel<D>(X, lds, P, k, ldexp(P.dt * kF16Scale, -s), mono, L);
+    if (!mono && (P.flags & RUN_GRAD)) panel_store(pf_mat<float, D>(P.hk, k - W.rg.kbase), X, L);
+    taylor_delta<D>(R, X, lds, s, q, L);
+    panel_store(pf_mat<float, D>(P.delta, k - W.rg.kbase), R, L);
+    if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
+    __syncthreads();
+  }
+}
+
+// The costates W_k = Q_k P_{k-1}^dag of a chunk, one workgroup per chunk,
+// without stored products: with N_{k+1} = W_k U_k^dag = Q_k P_k^dag and the
+// slices unitary (U_k U_k^dag = I to the unit roundoff of the plan),
+//   N_{k1} = mc[c] tf[c]^dag,   W_k = N_{k+1} U_k,   N_k = U_k^dag W_k,
+// two products per slice from the chunk's last slice down, each adding
+// N Delta_k or Delta_k^dag W to the running panel.  Per slice it reads Delta_k
+// and writes W_k (into bloc): the forward scan stores nothing per slice and
+// the adjoint reads one matrix instead of two or three (five HBM transfers of
+// a matrix per slice in the whole path, against eleven with stored prefix and
+// suffix products and the kept H_k and X^2).  Two barriers per slice: N in
+// buffer 0, Delta_k^dag in buffer 1, from which the right factor Delta_k of
+// the first product is read as it is.
+template <int D, bool PERSIST>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void k_wscan_f16(Work W) {
+  using Ops = F16Ops<D>;
+  __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
+  Lane L;
+  const Items I(W);
+  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+    int p, c;
+    split_item(item, W.rg.c_lo, W.rg.c_n, I.start, I.nprob, p, c);
+    const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
+    const int k0 = c * P.L;
+    const int k1 = min(P.N, k0 + P.L);
+    Panel<float, D> S, nxt, acc;
+    typename Ops::Frag B;
+    panel_load(acc, pf_mat<float, D>(P.tf, c), L);
+    panel_load(nxt, pf_mat<float, D>(P.mc, c), L);
+    panel_scale(acc, kF16Scale);
+    panel_scale(nxt, kF16Scale);
+    Ops::store(lds[0], nxt, L);
+    Ops::store(lds[1], acc, L);
+    panel_load(nxt, pf_mat<float, D>(P.delta, k1 - 1 - W.rg.kbase), L);
+    __syncthreads();
+    Ops::frag_ct(B, lds[1], L);
+    Ops::gemm(S, lds[0], B, L, true);
+    panel_scale(S, kF16Inv);  // N_{k1}
+    __syncthreads();
+    for (int k = k1 - 1; k >= k0; --k) {
+      Ops::store(lds[0], S, L);
+      Ops::store_ct(lds[1], nxt, L);
+      if (k > k0) panel_load(nxt, pf_mat<float, D>(P.delta, k - 1 - W.rg.kbase), L);
+      __syncthreads();
+      Ops::frag_ct(B, lds[1], L);
+      Ops::gemm(acc, lds[0], B, L, true);
+      panel_fma(S, kF16Inv, acc);  // W_k = N + N Delta
+      panel_store(pf_mat<float, D>(P.bloc, k - W.rg.kbase), S, L);
+      if (k == k0) break;
+      Ops::gemm(acc, lds[1], S, L, true);
+      panel_fma(S, kF16Inv, acc);  // N = W + Delta^dag W
+      __syncthreads();
+    }
+    if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
+    __syncthreads();
+  }
+}
+
+// c Z_k, Z_k = L(A_k^dag, W_k), from R1 = c A_k^dag / 2^s (anti-Hermitian) and
+// R2 = c W_k (panels), by the steps 2 to 4 of k_adjoint; X^2 is formed here
+// (reading it back from the expm would cost two HBM transfers of a matrix,
+// more than the product), and the block is halved at each squaring instead of
+// W being divided by 2^s, so that every factor stays in FP16's range whatever
+// s.  lds0 and lds1 hold one F16Ops matrix each and are free on entry; on
+// return they may still be read by other wavefronts.
+template <int D>
+__device__ __forceinline__ void frechet_panel(Panel<float, D>& R2, Panel<float, D>& R1, void* lds0, void* lds1,
+                                              int s, int qb, const Lane& L) {
+  using Ops = F16Ops<D>;
+  Panel<float, D> A1, A2, R3;
+  Ops::store_nct(lds0, R1, L);  // X = -X^dag
+  Ops::store(lds1, R2, L);
+  __syncthreads();
+  {
+    Ops::gemm(A2, lds0, R2, L, true);
+    typename Ops::Frag BX;
+    Ops::frag_nct(BX, lds0, L);
+    Ops::gemm(A1, lds0, BX, L, true);
+    Ops::gemm(A2, lds1, BX, L, false);
+  }
+  panel_scale(A1, kF16Inv);  // X2
+  panel_scale(A2, kF16Inv);  // S = X E + E X
+  __syncthreads();           // X and E are read: M^2 takes their place
+  Ops::store_ct(lds0, A1, L);  // X2 = X2^dag
+  Ops::store(lds1, A2, L);
+  const int top = (qb - 2) / 2;
+  int t;
+  if (qb & 1) {  // C = I / (qb-1)! + M / qb!
+    t = top - 1;
+    A1 = R1;
+    panel_scale(A1, (float)inv_factorial(qb));
+    panel_add_identity(A1, L, (float)(kF16Scale * inv_factorial(qb - 1)));
+    A2 = R2;
+    panel_scale(A2, (float)inv_factorial(qb));
+  } else if (top > 0) {  // C = D_{top-1} + M^2 / qb!
+    t = top - 2;
+    panel_axpby(A1, (float)inv_factorial(qb - 1), R1, (float)inv_factorial(qb));
+    panel_add_identity(A1, L, (float)(kF16Scale * inv_factorial(qb - 2)));
+    panel_axpby(A2, (float)inv_factorial(qb - 1), R2, (float)inv_factorial(qb));
+  } else {  // qb = 2: C = I / 2
+    t = -1;
+    panel_zero(A1);
+    panel_add_identity(A1, L, 0.5f * kF16Scale);
+    panel_zero(A2);
+  }
+  __syncthreads();
+  for (; t >= 0; --t) {
+    const double a = inv_factorial(2 * t + 2), b = inv_factorial(2 * t + 3);
+    R3 = R2;
+    panel_scale(R3, (float)(b * kF16Scale));
+    Ops::gemm(R3, lds0, A2, L, false);
+    Ops::gemm(R3, lds1, A1, L, false);
+    panel_scale(R3, kF16Inv);  // b E + X2 C2 + S C1
+    A2 = R1;
+    panel_scale(A2, (float)(b * kF16Scale));
+    panel_add_identity(A2, L, (float)(a * kF16Scale * kF16Scale));
+    Ops::gemm(A2, lds0, A1, L, false);
+    panel_scale(A2, kF16Inv);  // a I + b X + X2 C1
+    A1 = A2;
+    A2 = R3;
+  }
+  Ops::gemm(R3, lds0, A2, L, true);
+  Ops::gemm(R3, lds1, A1, L, false);
+  panel_fma(R2, kF16Inv, R3);  // Q = E + X2 C2 + S C1
+  if (s == 0) return;
+  // squarings, halved: Q <- Q + (D1 Q + Q D1) / 2, D1 <- 2 D1 + D1^2
+  Ops::gemm(R3, lds0, A1, L, true);
+  panel_fma(R1, kF16Inv, R3);  // D1 = X + X2 C1
+  for (int j = 0; j < s; ++j) {
+    __syncthreads();
+    Ops::store(lds0, R1, L);
+    Ops::store(lds1, R2, L);
+    __syncthreads();
+    Ops::gemm(R3, lds0, R2, L, true);   // D1 Q
+    Ops::gemm(R3, lds1, R1, L, false);  // + Q D1
+    if (j + 1 < s) {
+      Ops::gemm(A1, lds0, R1, L, true);
+      panel_scale(R1, 2.0f);
+      panel_fma(R1, kF16Inv, A1);
+    }
+    panel_fma(R2, 0.5f * kF16Inv, R3);
+  }
+}
+
+template <int D, bool PERSIST>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void k_adjoint_f16(Work W) {
+  using Ops = F16Ops<D>;
+  constexpr int NW = D / 16;
+  __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
+  __shared__ double red[2 * kEpiDense * 2 * NW];
+  Lane L;
+  const Items I(W);
+  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+    int p, k;
+    split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
+    const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
+    const int sqk = gp(P.sq)[k];
+    int s, q, qb;
+    unpack_sq(sqk, s, q, qb);
+    const bool mono = (sqk & kPlanMono) != 0;
+    Panel<float, D> R1, R2;
+    panel_load(R2, pf_mat<float, D>(P.bloc, k - W.rg.kbase), L);  // c W_k
+    // c A_k^dag / 2^s
+    if (mono) {
+      assemble_panel<D>(R1, lds[0], P, k, -ldexp(P.dt * kF16Scale, -s), true, L);
+      __syncthreads();
+    } else {
+      panel_load(R1, pf_mat<float, D>(P.hk, k - W.rg.kbase), L);
+      panel_scale(R1, -1.0f);
+    }
+    frechet_panel<D>(R2, R1, lds[0], lds[1], s, qb, L);
+    panel_scale(R2, kF16Inv);
+    gradient_epilogue<float, D>(P, k, R2, L, lds[0], red, mono);
+    if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
+    __syncthreads();
   }
 }
 
@@ -1960,6 +2306,13 @@ __device__ __forceinline__ void gradient_epilogue128(const ProbDesc& P, int k, c
   }
 }
 
+// FP32 keeps X2 = (A_k / 2^s)^2 for the adjoint (where the workspace has room
+// for it); in FP64 the expm runs Horner and the adjoint forms X2 itself.  For
+// Hermitian H_k the adjoint's X = A_k^dag / 2^s = -A_k / 2^s has the same
+// square.
+template <typename T>
+constexpr bool kKeepX2 = sizeof(T) == 4;
+
 // The three-product form in the FP32 expm and adjoint products at D = 128
 // (their registers allow it; the FP64 kernels already spill).
 template <typename T>
@@ -1982,9 +2335,10 @@ __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
     split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
     const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
     int s, q, qb;
-    unpack_sq(gp(P.sq)[k], s, q, qb);
+    const int sqk = gp(P.sq)[k];
+    unpack_sq(sqk, s, q, qb);
     Panel<T, 128> acc;
-    assemble128<T>(acc, SX, lds, P, k, ldexp(P.dt, -s), 1.0, L, controls_monomial(P));  // SX: the left factor
+    assemble128<T>(acc, SX, lds, P, k, ldexp(P.dt, -s), 1.0, L, (sqk & kPlanMono) != 0);  // SX: the left factor
     // For the adjoint: X = A_k / 2^s in PF layout (its X, A_k^dag / 2^s, is
     // the exact negation), one coalesced store of this wavefront's panel.
     if (P.flags & RUN_GRAD) panel_store(pf_mat<T, 128>(P.hk, k - W.rg.kbase), acc, L);
@@ -2511,7 +2865,7 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
       }
     }
     panel_store(S0, acc, L);  // Z (own panel)
-    gradient_epilogue128<T>(P, k, S0, L, lds, red, sizeof(T) == 4 && controls_monomial(P));
+    gradient_epilogue128<T>(P, k, S0, L, lds, red, sizeof(T) == 4 && (sqk & kPlanMono));
     __syncthreads();
   }
 }
@@ -2533,9 +2887,19 @@ static inline int grid_of(const Launch& L, int items, int cap) {
   return items < 1 ? 1 : (cap > 0 && items > cap ? cap : items);
 }
 
+// The FP16-split policy of the Hermitian FP32 path.
+template <typename Ops>
+constexpr bool kF16Path = false;
+template <int D>
+constexpr bool kF16Path<F16Ops<D>> = true;
+
 template <typename T, int D, typename Ops>
 static void stage_small(int stage, const Launch& L, const Range& rg, double ur) {
   constexpr int NT = Mat<T, D>::NT;
+  constexpr bool F16 = kF16Path<Ops>;
+  // The forward scans, carries and chunk products: a chain of N slices and full-size
+  // factors, whose errors reach Tr(V^dag X_N) (two FP16 numbers keep 22-23 bits)
+  using COps = StdOps<T, D>;
   hipStream_t st = L.stream;
   const int dirs = (L.flags & RUN_BWD) ? 2 : 1;
   const int grad = (L.flags & RUN_GRAD) ? 1 : 0;
@@ -2555,7 +2919,11 @@ static void stage_small(int stage, const Launch& L, const Range& rg, double ur) 
     }
     case ST_EXPM: {
       // the split-BF16 policy serves the adjoint only (launch_stage)
-      if constexpr (kStdLds<T, D, Ops>) {
+      if constexpr (F16) {
+        Work w = L.dyn ? dyn : slice_work(L, rg);
+        if (L.dyn) hipLaunchKernelGGL((k_expm_f16<D, true>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
+        else hipLaunchKernelGGL((k_expm_f16<D, false>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
+      } else if constexpr (kStdLds<T, D, Ops>) {
       Work w = L.dyn ? dyn : slice_work(L, rg);
       if (L.dyn) hipLaunchKernelGGL((k_expm<T, D, Ops, true>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
       else hipLaunchKernelGGL((k_expm<T, D, Ops, false>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
@@ -2564,15 +2932,27 @@ static void stage_small(int stage, const Launch& L, const Range& rg, double ur) 
     }
     case ST_SCAN:
     case ST_BSCAN: {
-      if constexpr (kStdLds<T, D, Ops>) {
+      if constexpr (F16 || kStdLds<T, D, Ops>) {
       Work w = L.dyn ? dyn : chunk_work(L, rg);
       // a recompute sweep runs the forward and backward passes of a segment
       // together (they are independent once mc is known)
-      const bool both = stage == ST_SCAN && rg.recompute && !L.dyn;
+      const bool both = !F16 && stage == ST_SCAN && rg.recompute && !L.dyn;
       const int dir = stage == ST_BSCAN ? 1 : (both ? -1 : 0);
       const dim3 grid(grid_of(L, w.total, 0), both ? 2 : 1);
-      if (L.dyn) hipLaunchKernelGGL((k_scan_local<T, D, Ops, true>), grid, dim3(NT), 0, st, w, dir);
-      else hipLaunchKernelGGL((k_scan_local<T, D, Ops, false>), grid, dim3(NT), 0, st, w, dir);
+      if constexpr (F16) {
+        // the forward pass leaves the chunk totals only; with them k_wscan_f16
+        // needs no stored products, so a recompute sweep has no forward pass
+        if (stage == ST_SCAN && !rg.recompute) {
+          if (L.dyn) hipLaunchKernelGGL((k_scan_local<T, D, COps, true>), grid, dim3(NT), 0, st, w, 2, (T)kF16Inv);
+          else hipLaunchKernelGGL((k_scan_local<T, D, COps, false>), grid, dim3(NT), 0, st, w, 2, (T)kF16Inv);
+        } else {
+          if (L.dyn) hipLaunchKernelGGL((k_wscan_f16<D, true>), grid, dim3(NT), 0, st, w);
+          else hipLaunchKernelGGL((k_wscan_f16<D, false>), grid, dim3(NT), 0, st, w);
+        }
+      } else {
+        if (L.dyn) hipLaunchKernelGGL((k_scan_local<T, D, Ops, true>), grid, dim3(NT), 0, st, w, dir, (T)1);
+        else hipLaunchKernelGGL((k_scan_local<T, D, Ops, false>), grid, dim3(NT), 0, st, w, dir, (T)1);
+      }
       if constexpr (sizeof(T) == 4) {
         if (stage == ST_SCAN && !rg.recompute) {
           if (L.dyn) hipLaunchKernelGGL((k_reun<D, true>), dim3(grid.x), dim3(NT), 0, st, w);
@@ -2586,20 +2966,23 @@ static void stage_small(int stage, const Launch& L, const Range& rg, double ur) 
       int CG, PG;
       carry_groups(L.uniformP, CG, PG);
       Work wg = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * PG, nullptr, Range{0, 0, 0, PG, 0}, nullptr};
-      hipLaunchKernelGGL((k_carry_grp<T, D>), dim3(grid_of(L, wg.total, 0), dirs), dim3(NT), 0, st, wg);
+      hipLaunchKernelGGL((k_carry_grp<T, D, COps>), dim3(grid_of(L, wg.total, 0), dirs), dim3(NT), 0, st, wg);
       Work w = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob, nullptr, all, nullptr};
-      hipLaunchKernelGGL((k_carry_top<T, D>), dim3(grid_of(L, L.nprob, 0), dirs), dim3(NT), 0, st, w);
+      hipLaunchKernelGGL((k_carry_top<T, D, COps>), dim3(grid_of(L, L.nprob, 0), dirs), dim3(NT), 0, st, w);
       break;
     }
     case ST_MC: {
       Work w = L.dyn ? dyn : chunk_work(L, all);
-      hipLaunchKernelGGL((k_mc<T, D>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
+      hipLaunchKernelGGL((k_mc<T, D, COps>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
       break;
     }
     case ST_ADJ: {
       Work w = L.dyn ? dyn : slice_work(L, rg);
       const dim3 grid(grid_of(L, w.total, 0));
-      if constexpr (kSampleLast<T, D, Ops>) {
+      if constexpr (F16) {
+        if (L.dyn) hipLaunchKernelGGL((k_adjoint_f16<D, true>), grid, dim3(NT), 0, st, w);
+        else hipLaunchKernelGGL((k_adjoint_f16<D, false>), grid, dim3(NT), 0, st, w);
+      } else if constexpr (kSampleLast<T, D, Ops>) {
         if (L.dyn) {
           hipLaunchKernelGGL((k_adjoint<T, D, Ops, true, 2>), grid, dim3(NT), 0, st, w);
           hipLaunchKernelGGL((k_adjoint<T, D, Ops, true, 1>), grid, dim3(NT), 0, st, w);
@@ -2689,8 +3072,14 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
   } else if (precision == 1) {
     switch (D) {
       case 16: stage_small<float, 16, StdOps<float, 16>>(stage, L, rg, ur32); break;
-      case 32: stage_small<float, 32, StdOps<float, 32>>(stage, L, rg, ur32); break;
-      case 64: stage_small<float, 64, StdOps<float, 64>>(stage, L, rg, ur32); break;
+      case 32:
+        if (L.flags & RUN_GENERAL) stage_small<float, 32, StdOps<float, 32>>(stage, L, rg, ur32);
+        else stage_small<float, 32, F16Ops<32>>(stage, L, rg, ur32);
+        break;
+      case 64:
+        if (L.flags & RUN_GENERAL) stage_small<float, 64, StdOps<float, 64>>(stage, L, rg, ur32);
+        else stage_small<float, 64, F16Ops<64>>(stage, L, rg, ur32);
+        break;
       case 128: stage_128<float>(stage, L, rg, ur32); break;
       default: ok = false;
     }
