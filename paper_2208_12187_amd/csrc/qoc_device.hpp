@@ -610,6 +610,7 @@ template <typename T, int D>
 struct StdOps {
   using Tp = T;
   static constexpr int BYTES = Mat<T, D>::LDS_ELEMS * (int)sizeof(T);
+  static constexpr T C = (T)1;  // factor carried by panels and left factors
   __device__ static __forceinline__ void put(void* lds, int row, int col, T re, T im) {
     T* p = static_cast<T*>(lds);
     const int off = lds_off<T, D>(row, col);
@@ -635,6 +636,17 @@ struct StdOps {
   __device__ static __forceinline__ void store_ct(void* lds, const Panel<T, D>& P, const Lane& L) {
     panel_to_lds_ct(static_cast<T*>(lds), P, L);
   }
+  // the negative conjugate transpose
+  __device__ static __forceinline__ void store_nct(void* lds, const Panel<T, D>& P, const Lane& L) {
+    T* re = static_cast<T*>(lds);
+    T* im = re + D * Mat<T, D>::SD;
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb) {
+      const int off = (16 * L.w + L.c16) * Mat<T, D>::SD + 16 * rb + 4 * L.g;
+      Prec<T>::st4(re + off, -P.re[rb]);
+      Prec<T>::st4(im + off, P.im[rb]);
+    }
+  }
   __device__ static __forceinline__ void load(Panel<T, D>& P, const void* lds, const Lane& L) {
     panel_from_lds(P, static_cast<const T*>(lds), L);
   }
@@ -650,8 +662,25 @@ struct StdOps {
   template <int PAIRS = 1>
   __device__ static __forceinline__ void gemm3(Panel<T, D>& acc, const void* lds, const Panel<T, D>& P,
                                                const Lane& L, bool zero_acc) {
-    if constexpr (D >= 32) cgemm3m<T, D, PAIRS>(acc, static_cast<const T*>(lds), P, L, zero_acc);
+    if constexpr (D >= 32 || sizeof(T) == 8) cgemm3m<T, D, D >= 32 ? PAIRS : 1>(acc, static_cast<const T*>(lds), P, L, zero_acc);
     else cgemm(acc, static_cast<const T*>(lds), P, L, zero_acc);
+  }
+  __device__ static __forceinline__ void mul(Panel<T, D>& acc, const void* lds, const Panel<T, D>& P, const Lane& L) {
+    gemm3(acc, lds, P, L, true);
+  }
+  // with work on the row blocks that depends on nothing here
+  template <typename Side>
+  __device__ static __forceinline__ void mul(Panel<T, D>& acc, const void* lds, const Panel<T, D>& P, const Lane& L,
+                                             Side side) {
+    gemm3(acc, lds, P, L, true);
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb) side(rb);
+  }
+  // acc = A B^dag, both in LDS
+  __device__ static __forceinline__ void mul_ct(Panel<T, D>& acc, const void* a, const void* b, const Lane& L) {
+    Panel<T, D> P;
+    load_ct(P, b, L);
+    gemm3(acc, a, P, L, true);
   }
 };
 

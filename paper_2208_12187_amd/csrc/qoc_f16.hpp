@@ -39,9 +39,6 @@ typedef _Float16 h2v __attribute__((ext_vector_type(2)));
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 
-constexpr float kF16Scale = 4096.0f;  // c
-constexpr float kF16Inv = 1.0f / kF16Scale;
-
 // Two scaled values at once; element 0 sits in the low 16 bits of the packed
 // results.  (The opaque factor 1 keeps x - hi one v_fma_mix_f32, which reads
 // hi as FP16, instead of a conversion and a subtraction.)
@@ -58,6 +55,7 @@ __device__ __forceinline__ void f16_split2(float x0, float x1, unsigned& hi, uns
 template <int D>
 struct F16Ops {
   using Tp = float;
+  static constexpr float C = 4096.0f;  // c
   static constexpr int SB = D + 8;     // row stride in FP16 elements
   static constexpr int PLANE = D * SB;  // elements per plane
   static constexpr int BYTES = 4 * PLANE * 2;
@@ -124,56 +122,54 @@ struct F16Ops {
     store_t<true>(lds, P, L);
   }
 
+  // Panel of the conjugate transpose of the stored matrix (its 22-bit values).
+  __device__ static __forceinline__ void load_ct(Panel<float, D>& P, const void* lds, const Lane& L) {
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb) {
+      const int off = (16 * L.w + L.c16) * SB + phys(16 * rb + 4 * L.g);
+      const h4v rh = *reinterpret_cast<const h4v*>(plane(lds, 0) + off);
+      const h4v rl = *reinterpret_cast<const h4v*>(plane(lds, 1) + off);
+      const h4v ih = *reinterpret_cast<const h4v*>(plane(lds, 2) + off);
+      const h4v il = *reinterpret_cast<const h4v*>(plane(lds, 3) + off);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        P.re[rb][r] = (float)rh[r] + (float)rl[r];
+        P.im[rb][r] = -((float)ih[r] + (float)il[r]);
+      }
+    }
+  }
+
   // The right factor of one wavefront, split: K step t's values of its 16 columns.
   struct Frag {
     h8v rh[D / 32], rl[D / 32], ih[D / 32], il[D / 32];
   };
 
-  __device__ static __forceinline__ void frag(Frag& F, const Panel<float, D>& P) {
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t) {
-      u4v rh, rl, ih, il;
-#pragma unroll
-      for (int jp = 0; jp < 4; ++jp) {
-        const int rb = 2 * t + (jp >> 1), r = 2 * (jp & 1);
-        unsigned h, l;
-        f16_split2(P.re[rb][r], P.re[rb][r + 1], h, l);
-        rh[jp] = h;
-        rl[jp] = l;
-        f16_split2(P.im[rb][r], P.im[rb][r + 1], h, l);
-        ih[jp] = h;
-        il[jp] = l;
-      }
-      F.rh[t] = __builtin_bit_cast(h8v, rh);
-      F.rl[t] = __builtin_bit_cast(h8v, rl);
-      F.ih[t] = __builtin_bit_cast(h8v, ih);
-      F.il[t] = __builtin_bit_cast(h8v, il);
-    }
+  // Pair jp (of 4) of K step t of a panel: rows 32 t + 16 (jp / 2) + 4 g + 2 (jp % 2) + {0, 1}.
+  __device__ static __forceinline__ void frag_pair(u4v& rh, u4v& rl, u4v& ih, u4v& il, const Panel<float, D>& P,
+                                                   int t, int jp) {
+    const int rb = 2 * t + (jp >> 1), r = 2 * (jp & 1);
+    unsigned h, l;
+    f16_split2(P.re[rb][r], P.re[rb][r + 1], h, l);
+    rh[jp] = h;
+    rl[jp] = l;
+    f16_split2(P.im[rb][r], P.im[rb][r + 1], h, l);
+    ih[jp] = h;
+    il[jp] = l;
   }
 
-  // The conjugate transpose of the stored matrix, or its negative, as a right
-  // factor: column 16 w + c16 is a row of the matrix, whose K values phys()
-  // has put together, so the split values are read as they are.
-  template <bool NEG>
-  __device__ static __forceinline__ void frag_t(Frag& F, const void* lds, const Lane& L) {
+  // The conjugate transpose of the stored matrix as a right factor: column
+  // 16 w + c16 is a row of the matrix, whose K values phys() has put together,
+  // so the split values are read as they are.
+  __device__ static __forceinline__ void frag_ct(Frag& F, const void* lds, const Lane& L) {
     const int off = (16 * L.w + L.c16) * SB + 8 * L.g;
 #pragma unroll
     for (int t = 0; t < D / 32; ++t) {
       F.rh[t] = *reinterpret_cast<const h8v*>(plane(lds, 0) + off + 32 * t);
       F.rl[t] = *reinterpret_cast<const h8v*>(plane(lds, 1) + off + 32 * t);
-      F.ih[t] = *reinterpret_cast<const h8v*>(plane(lds, 2) + off + 32 * t);
-      F.il[t] = *reinterpret_cast<const h8v*>(plane(lds, 3) + off + 32 * t);
-      if (NEG) {
-        F.rh[t] = neg(F.rh[t]);
-        F.rl[t] = neg(F.rl[t]);
-      } else {
-        F.ih[t] = neg(F.ih[t]);
-        F.il[t] = neg(F.il[t]);
-      }
+      F.ih[t] = neg(*reinterpret_cast<const h8v*>(plane(lds, 2) + off + 32 * t));
+      F.il[t] = neg(*reinterpret_cast<const h8v*>(plane(lds, 3) + off + 32 * t));
     }
   }
-  __device__ static __forceinline__ void frag_ct(Frag& F, const void* lds, const Lane& L) { frag_t<false>(F, lds, L); }
-  __device__ static __forceinline__ void frag_nct(Frag& F, const void* lds, const Lane& L) { frag_t<true>(F, lds, L); }
 
   __device__ static __forceinline__ h8v neg(h8v x) {
     u4v u = __builtin_bit_cast(u4v, x);
@@ -186,56 +182,213 @@ struct F16Ops {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
 
-  // acc (+)= A B with A the LDS matrix.  Per K step and row block 4 x 16-byte reads and 12 MFMAs, the
-  // smallest terms first.
-  __device__ static __forceinline__ void gemm(Panel<float, D>& acc, const void* lds, const Frag& B,
-                                                   const Lane& L, bool zero_acc) {
+  // The 12 MFMAs of one (K step, row block), the smallest terms first.  FIRST:
+  // the accumulators start from zero.
+  template <bool FIRST>
+  __device__ static __forceinline__ void step(f4& re, f4& im, const h8v (&a)[4], h8v brh, h8v brl, h8v bih, h8v bil,
+                                              h8v nih, h8v nil) {
+    const f4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+    re = mfma(a[0], brl, FIRST ? z : re);
+    im = mfma(a[0], bil, FIRST ? z : im);
+    re = mfma(a[1], brh, re);
+    im = mfma(a[1], bih, im);
+    re = mfma(a[2], nil, re);
+    im = mfma(a[2], brl, im);
+    re = mfma(a[3], nih, re);
+    im = mfma(a[3], brh, im);
+    re = mfma(a[0], brh, re);
+    im = mfma(a[0], bih, im);
+    re = mfma(a[2], nih, re);
+    im = mfma(a[2], brh, im);
+  }
+
+  __device__ static __forceinline__ void load_a(h8v (&a)[4], const void* lds, int off) {
+#pragma unroll
+    for (int pl = 0; pl < 4; ++pl) a[pl] = *reinterpret_cast<const h8v*>(plane(lds, pl) + off);
+  }
+
+  // acc = A B with A the LDS matrix: per K step and row block 4 x 16-byte
+  // reads and 12 MFMAs.
+  __device__ static __forceinline__ void gemm(Panel<float, D>& acc, const void* lds, const Frag& B, const Lane& L) {
     constexpr int RB = D / 16;
     constexpr int KT = D / 32;
     __builtin_amdgcn_sched_barrier(0);
-    if (zero_acc) panel_zero(acc);
     const int base = L.c16 * SB + 8 * L.g;
     h8v a[2][4];
-#pragma unroll
-    for (int pl = 0; pl < 4; ++pl) a[0][pl] = *reinterpret_cast<const h8v*>(plane(lds, pl) + base);
+    load_a(a[0], lds, base);
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
-      const h8v brh = B.rh[t], brl = B.rl[t], bih = B.ih[t], bil = B.il[t];
-      const h8v nih = neg(bih), nil = neg(bil);
+      const h8v nih = neg(B.ih[t]), nil = neg(B.il[t]);
 #pragma unroll
       for (int mb = 0; mb < RB; ++mb) {
         const int st = t * RB + mb, cur = st & 1;
-        if (st + 1 < KT * RB) {
-          const int off = base + 16 * ((st + 1) % RB) * SB + 32 * ((st + 1) / RB);
-#pragma unroll
-          for (int pl = 0; pl < 4; ++pl) a[cur ^ 1][pl] = *reinterpret_cast<const h8v*>(plane(lds, pl) + off);
-        }
-        const h8v arh = a[cur][0], arl = a[cur][1], aih = a[cur][2], ail = a[cur][3];
-        f4 re = acc.re[mb], im = acc.im[mb];
-        re = mfma(arh, brl, re);
-        im = mfma(arh, bil, im);
-        re = mfma(arl, brh, re);
-        im = mfma(arl, bih, im);
-        re = mfma(aih, nil, re);
-        im = mfma(aih, brl, im);
-        re = mfma(ail, nih, re);
-        im = mfma(ail, brh, im);
-        re = mfma(arh, brh, re);
-        im = mfma(arh, bih, im);
-        re = mfma(aih, nih, re);
-        im = mfma(aih, brh, im);
-        acc.re[mb] = re;
-        acc.im[mb] = im;
+        if (st + 1 < KT * RB) load_a(a[cur ^ 1], lds, base + 16 * ((st + 1) % RB) * SB + 32 * ((st + 1) / RB));
+        if (t == 0) step<true>(acc.re[mb], acc.im[mb], a[cur], B.rh[t], B.rl[t], B.ih[t], B.il[t], nih, nil);
+        else step<false>(acc.re[mb], acc.im[mb], a[cur], B.rh[t], B.rl[t], B.ih[t], B.il[t], nih, nil);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
 
-  __device__ static __forceinline__ void gemm(Panel<float, D>& acc, const void* lds, const Panel<float, D>& P,
-                                                     const Lane& L, bool zero_acc) {
+  // acc = A P with A the LDS matrix.  A K step's values of P are split while
+  // the previous step's MFMAs run, and side(rb), work on row block rb that
+  // depends on nothing here, is issued among the last K step's.
+  template <typename Side>
+  __device__ static __forceinline__ void mul(Panel<float, D>& acc, const void* lds, const Panel<float, D>& P,
+                                             const Lane& L, Side side) {
+    constexpr int RB = D / 16;
+    constexpr int KT = D / 32;
+    __builtin_amdgcn_sched_barrier(0);
+    const int base = L.c16 * SB + 8 * L.g;
+    h8v a[2][4];
+    load_a(a[0], lds, base);
+    u4v rh[2], rl[2], ih[2], il[2];
+#pragma unroll
+    for (int jp = 0; jp < 4; ++jp) frag_pair(rh[0], rl[0], ih[0], il[0], P, 0, jp);
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      const int c = t & 1;
+      const h8v brh = __builtin_bit_cast(h8v, rh[c]), brl = __builtin_bit_cast(h8v, rl[c]);
+      const h8v bih = __builtin_bit_cast(h8v, ih[c]), bil = __builtin_bit_cast(h8v, il[c]);
+      const h8v nih = neg(bih), nil = neg(bil);
+#pragma unroll
+      for (int mb = 0; mb < RB; ++mb) {
+        const int st = t * RB + mb, cur = st & 1;
+        if (st + 1 < KT * RB) load_a(a[cur ^ 1], lds, base + 16 * ((st + 1) % RB) * SB + 32 * ((st + 1) / RB));
+        if (t == 0) step<true>(acc.re[mb], acc.im[mb], a[cur], brh, brl, bih, bil, nih, nil);
+        else step<false>(acc.re[mb], acc.im[mb], a[cur], brh, brl, bih, bil, nih, nil);
+        if (t + 1 < KT) frag_pair(rh[c ^ 1], rl[c ^ 1], ih[c ^ 1], il[c ^ 1], P, t + 1, mb);
+        if (t + 1 == KT) side(mb);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  __device__ static __forceinline__ void mul(Panel<float, D>& acc, const void* lds, const Panel<float, D>& P,
+                                             const Lane& L) {
+    mul(acc, lds, P, L, [](int) {});
+  }
+  // acc = A B^dag, both in LDS
+  __device__ static __forceinline__ void mul_ct(Panel<float, D>& acc, const void* a, const void* b, const Lane& L) {
     Frag B;
-    frag(B, P);
-    gemm(acc, lds, B, L, zero_acc);
+    frag_ct(B, b, L);
+    gemm(acc, a, B, L);
+  }
+};
+
+// D = 16: the K = 32 of one MFMA takes the real and imaginary parts of the 16
+// terms at once, Re = [Ar, -Ai] [Br; Bi] and Im = [Ai, Ar] [Br; Bi], so that a
+// complex product is 6 MFMAs (FP32: 16 of twice the cycles).  K index 8g + j
+// stands for the real (j < 4) or imaginary (j >= 4) part of row 4g + j % 4,
+// which is what lane (g, c16) holds of a panel; the left factor is staged as
+// four planes (the Re rows hi, lo, the Im rows hi, lo), row stride 40.
+template <>
+struct F16Ops<16> {
+  using Tp = float;
+  static constexpr int D = 16;
+  static constexpr float C = 4096.0f;
+  static constexpr int SB = 40;
+  static constexpr int PLANE = D * SB;
+  static constexpr int BYTES = 4 * PLANE * 2;
+
+  __device__ static __forceinline__ unsigned short* plane(void* lds, int i) {
+    return static_cast<unsigned short*>(lds) + i * PLANE;
+  }
+  __device__ static __forceinline__ const unsigned short* plane(const void* lds, int i) {
+    return static_cast<const unsigned short*>(lds) + i * PLANE;
+  }
+  __device__ static __forceinline__ void split_panel(u2v& rh, u2v& rl, u2v& ih, u2v& il, const Panel<float, D>& P) {
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+      unsigned h, l;
+      f16_split2(P.re[0][r], P.re[0][r + 1], h, l);
+      rh[r / 2] = h;
+      rl[r / 2] = l;
+      f16_split2(P.im[0][r], P.im[0][r + 1], h, l);
+      ih[r / 2] = h;
+      il[r / 2] = l;
+    }
+  }
+  __device__ static __forceinline__ u2v flip(u2v x) { return (u2v){x[0] ^ 0x80008000u, x[1] ^ 0x80008000u}; }
+
+  __device__ static __forceinline__ void store(void* lds, const Panel<float, D>& P, const Lane& L) {
+    u2v v[4];  // re hi, re lo, im hi, im lo of rows 4g .. 4g + 3
+    split_panel(v[0], v[1], v[2], v[3], P);
+    const int col = 8 * (L.c16 >> 2) + (L.c16 & 3);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int off = (4 * L.g + r) * SB + col, sh = 16 * (r & 1);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const unsigned short re = (unsigned short)(v[p][r / 2] >> sh), im = (unsigned short)(v[2 + p][r / 2] >> sh);
+        plane(lds, p)[off] = re;
+        plane(lds, p)[off + 4] = im ^ 0x8000u;
+        plane(lds, 2 + p)[off] = im;
+        plane(lds, 2 + p)[off + 4] = re;
+      }
+    }
+  }
+  // The conjugate transpose (or, NEG, its negative): one 16-byte write per plane.
+  template <bool NEG>
+  __device__ static __forceinline__ void store_t(void* lds, const Panel<float, D>& P, const Lane& L) {
+    u2v rh, rl, ih, il;
+    split_panel(rh, rl, ih, il, P);
+    const int off = L.c16 * SB + 8 * L.g;
+    auto put = [&](int pl, u2v a, u2v b) {
+      *reinterpret_cast<u4v*>(plane(lds, pl) + off) = (u4v){a[0], a[1], b[0], b[1]};
+    };
+    // M^dag: Ar = re, Ai = -im, so [Ar, -Ai] = [re, im] and [Ai, Ar] = [-im, re]
+    put(0, NEG ? flip(rh) : rh, NEG ? flip(ih) : ih);
+    put(1, NEG ? flip(rl) : rl, NEG ? flip(il) : il);
+    put(2, NEG ? ih : flip(ih), NEG ? flip(rh) : rh);
+    put(3, NEG ? il : flip(il), NEG ? flip(rl) : rl);
+  }
+  __device__ static __forceinline__ void store_ct(void* lds, const Panel<float, D>& P, const Lane& L) {
+    store_t<false>(lds, P, L);
+  }
+  __device__ static __forceinline__ void store_nct(void* lds, const Panel<float, D>& P, const Lane& L) {
+    store_t<true>(lds, P, L);
+  }
+  // Panel of the conjugate transpose of the stored matrix (its 22-bit values):
+  // the Re rows [Ar, -Ai] are its real and imaginary parts.
+  __device__ static __forceinline__ void load_ct(Panel<float, D>& P, const void* lds, const Lane& L) {
+    const int off = L.c16 * SB + 8 * L.g;
+    const h8v h = *reinterpret_cast<const h8v*>(plane(lds, 0) + off);
+    const h8v l = *reinterpret_cast<const h8v*>(plane(lds, 1) + off);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      P.re[0][r] = (float)h[r] + (float)l[r];
+      P.im[0][r] = (float)h[4 + r] + (float)l[4 + r];
+    }
+  }
+  __device__ static __forceinline__ void gemm(Panel<float, D>& acc, const void* lds, h8v bh, h8v bl, const Lane& L) {
+    const int off = L.c16 * SB + 8 * L.g;
+    h8v a[4];
+#pragma unroll
+    for (int pl = 0; pl < 4; ++pl) a[pl] = *reinterpret_cast<const h8v*>(plane(lds, pl) + off);
+    const f4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+    f4 re = F16Ops<32>::mfma(a[0], bl, z), im = F16Ops<32>::mfma(a[2], bl, z);
+    re = F16Ops<32>::mfma(a[1], bh, re);
+    im = F16Ops<32>::mfma(a[3], bh, im);
+    acc.re[0] = F16Ops<32>::mfma(a[0], bh, re);
+    acc.im[0] = F16Ops<32>::mfma(a[2], bh, im);
+  }
+  template <typename Side>
+  __device__ static __forceinline__ void mul(Panel<float, D>& acc, const void* lds, const Panel<float, D>& P,
+                                             const Lane& L, Side side) {
+    u2v rh, rl, ih, il;
+    split_panel(rh, rl, ih, il, P);
+    const u4v h = {rh[0], rh[1], ih[0], ih[1]}, l = {rl[0], rl[1], il[0], il[1]};
+    gemm(acc, lds, __builtin_bit_cast(h8v, h), __builtin_bit_cast(h8v, l), L);
+    side(0);
+  }
+  __device__ static __forceinline__ void mul(Panel<float, D>& acc, const void* lds, const Panel<float, D>& P,
+                                             const Lane& L) {
+    mul(acc, lds, P, L, [](int) {});
+  }
+  // acc = A B^dag, both in LDS
+  __device__ static __forceinline__ void mul_ct(Panel<float, D>& acc, const void* a, const void* b, const Lane& L) {
+    const int off = L.c16 * SB + 8 * L.g;
+    gemm(acc, a, *reinterpret_cast<const h8v*>(plane(b, 0) + off), *reinterpret_cast<const h8v*>(plane(b, 1) + off), L);
   }
 };
 

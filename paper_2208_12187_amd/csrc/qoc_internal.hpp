@@ -53,6 +53,7 @@ struct ProbDesc {
   void* grp;          // 4 x PG PF matrices: forward and backward group totals, then the
                       // forward and backward carries into each group
   double* g;          // complex128 Tr(V^dag X_N)
+  int* squared;       // nonzero: some slice's plan has s > 0
   double* vscale;     // power of two by which k_prep divided the stored target
   double* diag;       // [0] ||X_N^dag X_N - I||_F; [1] largest chunk residual (FP64
                       // bits, atomic max); [2] re-unitarisation steps (uint64 count)
@@ -70,6 +71,7 @@ enum : int {
   RUN_FID = 4,   // fidelity against V
   CTRL_DENSE = 8,  // always the dense control kernels (qoc_options.dense_controls)
   RUN_RAWDG = 16,  // write dg/du[j][k] = d Tr(V^dag X_N) / du[j][k] (complex) instead of dF/du
+  RUN_STATE = 64,  // state-to-state path (launches only): its own plan rule
   RUN_GENERAL = 32,  // H0, Hc are general generators G (stored as i G; see prep_one)
 };
 
@@ -81,6 +83,7 @@ struct Launch {
   const ProbDesc* descs;  // device array of nprob descriptors
   int nprob;
   int uniformN, uniformP;
+  int chunk;  // slices per chunk of a uniform launch
   const int* slice_start;  // device, nprob + 1 entries (or null)
   const int* chunk_start;  // device, nprob + 1 entries (or null)
   int total_slices, total_chunks;
@@ -167,6 +170,13 @@ inline int default_chunk(int D, int N) {
 // d = 128, N = 1000: 5.45 -> 4.42 ms), at a cost of about 2% in throughput
 // at batch 32.
 inline int engine_chunk(int N) { return std::max(1, (int)ceil(sqrt(N / 8.0))); }
+
+// Segments of a chunk of L slices (Hermitian path at D <= 64), and slices per
+// segment: at most kSegMax, as even as they come.
+constexpr int kSegMax = 8;
+__host__ __device__ inline int seg_max(int D) { return D == 16 ? 2 : kSegMax; }
+__host__ __device__ inline int seg_count(int D, int L) { return (L + seg_max(D) - 1) / seg_max(D); }
+__host__ __device__ inline int seg_len(int D, int L) { return (L + seg_count(D, L) - 1) / seg_count(D, L); }
 
 // The carry over the P chunk totals runs in groups of CG =
 // ceil(sqrt(P)) chunks: a serial chain inside every group, one over the PG
@@ -291,6 +301,7 @@ inline void fill_desc(ProbDesc& P, const Layout& Lo, char* pb, int d, int m, int
   P.F = F ? F : small + 2;        // 1 double
   P.diag = diag ? diag : small + 4;  // 4 doubles
   P.vscale = small + 8;              // 1 double
+  P.squared = reinterpret_cast<int*>(small + 9);
   P.reun_tol = reun_tol;
 }
 

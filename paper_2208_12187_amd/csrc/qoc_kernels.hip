@@ -81,70 +81,13 @@ __device__ __forceinline__ T* pf_mat(void* base, int i) {
 
 // ---------------------------------------------------------------- prep
 
-// Row table of control j: for each row a, the column and value (in
-// precision T, as the dense copy holds it) of its nonzero, and whether every
-// row has at most one.  Such controls (Pauli strings, for instance) are then
-// assembled and paired with Z_k entry by entry.  The table is written even
-// when the control does not qualify; mok[j] says whether it may be used.
-template <typename T, int D>
-__device__ __forceinline__ void control_rows(const ProbDesc& P, int j, const double* src) {
-  const int d = P.d;
-  const int a = threadIdx.x;
-  const bool gen = (P.flags & RUN_GENERAL) != 0;  // stored as i G (see prep_one)
-  __shared__ int hits[D];  // rows whose entry lies in each column
-  if (a < D) hits[a] = 0;
-  __syncthreads();
-  int multi = 0, col = a;
-  {
-    if (a < D) {
-      int cnt = 0;
-      T vr = 0, vi = 0;
-      if (a < d)
-        for (int c = 0; c < d; ++c) {
-          const double sr = src[2 * (a * d + c)], si = src[2 * (a * d + c) + 1];
-          const T r = (T)(gen ? -si : sr), i = (T)(gen ? sr : si);
-          if (r != (T)0 || i != (T)0) {
-            ++cnt;
-            col = c;
-            vr = r;
-            vi = i;
-          }
-        }
-      multi = cnt > 1;
-      const size_t idx = (size_t)j * D + a;
-      gp(P.mcol)[idx] = col;
-      gp(reinterpret_cast<T*>(P.mval))[2 * idx] = vr;
-      gp(reinterpret_cast<T*>(P.mval))[2 * idx + 1] = vi;
-      atomicAdd(&hits[col], 1);
-    }
-  }
-  // Whether control j - 1 puts its entries at the same columns (X_i and Y_i
-  // do), from its source rows: then the entries of Z that both read are the
-  // same (flag 4).
-  int same = 1;
-  if (j > 0 && a < d) {
-    const double* prev = src - 2 * (size_t)d * d;
-    int pc = a;
-    for (int c = 0; c < d; ++c)
-      if (prev[2 * (a * d + c)] != 0.0 || prev[2 * (a * d + c) + 1] != 0.0) pc = c;
-    same = pc == col;
-  }
-  const int any = __syncthreads_or(multi);
-  // A bijection when every column is hit once (empty rows count at their own
-  // column, with a zero entry); then minv[j][col_j(a)] = a.
-  const int bij = __syncthreads_and(a >= D || hits[a] == 1);
-  const int all_same = __syncthreads_and(same) && j > 0;
-  if (P.minv && a < D) gp(P.minv)[(size_t)j * D + col] = a;
-  if (threadIdx.x == 0)
-    gp(P.mok)[j] = (!any && !(P.flags & CTRL_DENSE)) ? (1 | (bij && P.minv ? 2 : 0) | (all_same ? 4 : 0)) : 0;
-}
-
 // The flags that every control of the problem has: bit 0, a usable row table
 // (at most one nonzero per row, dense kernels not forced); bit 1, the table is
 // also a bijection from rows to columns (minv holds its inverse).  (All the
 // flags are loaded together.)
 __device__ __forceinline__ int controls_flags(const ProbDesc& P) {
   int all = 3;
+#pragma unroll 4
   for (int j = 0; j < P.m; ++j) all &= gp(P.mok)[j];
   return all;
 }
@@ -164,54 +107,141 @@ constexpr int kPlanMono = 1 << 25;
 // A = -i dt H is dt G, and the norm is the larger of the one- and
 // infinity-norms: the adjoint works with A^dag, whose one-norm is A's
 // infinity-norm.
+// The same pass over a control builds its row table: for each row a, the
+// column and value (in precision T, as the dense copy holds it) of its nonzero,
+// and whether every row has at most one.  Such controls (Pauli strings, for
+// instance) are then assembled and paired with Z_k entry by entry.  The table
+// is written even when the control does not qualify; mok[j] says whether it may
+// be used (bit 0), whether its columns are a bijection (bit 1; then
+// minv[j][col_j(a)] = a; empty rows count at their own column, with a zero
+// entry) and whether control j - 1 puts its entries at the same columns, as X_i
+// and Y_i do (bit 2).
+//
+// A wavefront reads whole rows (64 / D of them at once, or half a row at a time
+// at D = 128), so that a matrix takes D^2 / 256 coalesced loads per thread with
+// no dependence between rows: latency-bound, one round trip deep (one thread
+// per row or column walked D dependent steps: 46 us at d = 64 and 128 us at
+// d = 128, now 6 and 11).
 template <typename T, int D>
 __device__ __forceinline__ void prep_one(const ProbDesc& P, int mat, double* colmax) {
   const int d = P.d, m = P.m;
   if (mat == 0 && threadIdx.x == 0) {
     P.diag[1] = 0.0;
     P.diag[2] = 0.0;
+    *P.squared = 0;
   }
   if (mat <= m) {
+    constexpr int LPR = D < 64 ? D : 64;  // lanes per row
+    constexpr int CPL = D / LPR;          // columns per lane
+    constexpr int RPW = 64 / LPR;         // rows per wavefront and step
+    constexpr int STEPS = D / (4 * RPW);
+    __shared__ int hits[D];               // rows whose entry lies in each column
+    __shared__ double csum[4][D];         // column sums by wavefront
+    const bool gen = (P.flags & RUN_GENERAL) != 0;
+    const bool ctl = mat > 0;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lr = lane / LPR, lc = lane % LPR;
     const double* src = mat == 0 ? P.H0z : P.Hcz + (size_t)(mat - 1) * 2 * d * d;
+    const double* prev = mat > 1 ? src - 2 * (size_t)d * d : nullptr;
     T* dst = reinterpret_cast<T*>(P.Hint) + (size_t)mat * 2 * D * D;
-    for (int e = threadIdx.x; e < D * D; e += 256) {
-      int row = e / D, col = e % D;
-      double re = 0, im = 0;
-      if (row < d && col < d) {
-        re = src[2 * (row * d + col)];
-        im = src[2 * (row * d + col) + 1];
-      }
-      if (P.flags & RUN_GENERAL) {  // i (re + i im)
-        const double t = re;
-        re = -im;
-        im = t;
-      }
-      dst[e] = (T)re;
-      dst[D * D + e] = (T)im;
-    }
-    double s = 0;
-    if ((int)threadIdx.x < d) {
-      for (int row = 0; row < d; ++row) {
-        double re = src[2 * (row * d + threadIdx.x)], im = src[2 * (row * d + threadIdx.x) + 1];
-        s += sqrt(fma(re, re, im * im));
-      }
-      if (P.flags & RUN_GENERAL) {
-        double r = 0;
-        for (int col = 0; col < d; ++col) {
-          double re = src[2 * (threadIdx.x * d + col)], im = src[2 * (threadIdx.x * d + col) + 1];
-          r += sqrt(fma(re, re, im * im));
-        }
-        s = fmax(s, r);
-      }
-    }
-    colmax[threadIdx.x] = s;
+    if ((int)threadIdx.x < D) hits[threadIdx.x] = 0;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if ((int)threadIdx.x < o) colmax[threadIdx.x] = fmax(colmax[threadIdx.x], colmax[threadIdx.x + o]);
-      __syncthreads();
+    double cs[CPL];
+    double rmax = 0;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) cs[q] = 0;
+    int multi = 0, same = 1;
+    const unsigned long long rowmask = (LPR == 64 ? ~0ull : ((1ull << LPR) - 1) << (lr * LPR));
+#pragma unroll 4
+    for (int st = 0; st < STEPS; ++st) {
+      const int row = (st * 4 + w) * RPW + lr;
+      unsigned long long nz[CPL], pz[CPL];
+      T tr[CPL], ti[CPL];
+      double rs = 0;
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) {
+        const int col = lc + q * LPR;
+        double re = 0, im = 0, pr = 0, pi = 0;
+        if (row < d && col < d) {
+          const d2 v = *(const QOC_GLOBAL d2*)(src + 2 * ((size_t)row * d + col));
+          re = v.x;
+          im = v.y;
+          if (prev) {
+            const d2 u = *(const QOC_GLOBAL d2*)(prev + 2 * ((size_t)row * d + col));
+            pr = u.x;
+            pi = u.y;
+          }
+        }
+        const double a = sqrt(fma(re, re, im * im));
+        cs[q] += a;
+        rs += a;
+        if (gen) {  // i (re + i im)
+          const double t = re;
+          re = -im;
+          im = t;
+        }
+        tr[q] = (T)re;
+        ti[q] = (T)im;
+        gp(dst)[row * D + col] = tr[q];
+        gp(dst)[D * D + row * D + col] = ti[q];
+        nz[q] = __ballot(tr[q] != (T)0 || ti[q] != (T)0) & rowmask;
+        pz[q] = __ballot(pr != 0.0 || pi != 0.0) & rowmask;
+      }
+      if (gen) {  // row sums, for the infinity norm
+#pragma unroll
+        for (int o = 1; o < LPR; o <<= 1) rs += __shfl_xor(rs, o, 64);
+        rmax = fmax(rmax, rs);
+      }
+      if (ctl) {
+        int cnt = 0, col = row, pc = row, own = -1;
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+          cnt += __popcll(nz[q]);
+          if (nz[q]) col = 63 - __clzll(nz[q]) - lr * LPR + q * LPR;  // the last one
+          if (pz[q]) pc = 63 - __clzll(pz[q]) - lr * LPR + q * LPR;
+        }
+        multi |= cnt > 1;
+        if (row < d) same &= pc == col;
+#pragma unroll
+        for (int q = 0; q < CPL; ++q)
+          if (lc + q * LPR == col) own = q;
+        if (own >= 0) {  // the lane of the row's entry (its own column in an empty row)
+          const size_t idx = (size_t)(mat - 1) * D + row;
+          T vr = tr[0], vi = ti[0];
+          if (CPL > 1 && own > 0) {
+            vr = tr[CPL - 1];
+            vi = ti[CPL - 1];
+          }
+          gp(P.mcol)[idx] = col;
+          gp(reinterpret_cast<T*>(P.mval))[2 * idx] = vr;
+          gp(reinterpret_cast<T*>(P.mval))[2 * idx + 1] = vi;
+          atomicAdd(&hits[col], 1);
+          if (P.minv) gp(P.minv)[(size_t)(mat - 1) * D + col] = row;
+        }
+      }
     }
-    if (threadIdx.x == 0) P.norms[mat] = colmax[0];
-    if (mat > 0) control_rows<T, D>(P, mat - 1, src);
+    // column sums: lanes of one column within the wavefront, then the wavefronts
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+#pragma unroll
+      for (int o = LPR; o < 64; o <<= 1) cs[q] += __shfl_xor(cs[q], o, 64);
+      if (lr == 0) csum[w][lc + q * LPR] = cs[q];
+    }
+    const int any = __syncthreads_or(multi);
+    const int a = threadIdx.x;
+    double mx = gen ? rmax : 0.0;
+    if (a < D) mx = fmax(mx, (csum[0][a] + csum[1][a]) + (csum[2][a] + csum[3][a]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) colmax[w] = mx;
+    const int bij = __syncthreads_and(a >= D || hits[a] == 1);
+    const int all_same = __syncthreads_and(same) && mat > 1;
+    if (threadIdx.x == 0) {
+      P.norms[mat] = fmax(fmax(colmax[0], colmax[1]), fmax(colmax[2], colmax[3]));
+      if (ctl)
+        gp(P.mok)[mat - 1] =
+            (!any && !(P.flags & CTRL_DENSE)) ? (1 | (bij && P.minv ? 2 : 0) | (all_same ? 4 : 0)) : 0;
+    }
     __syncthreads();
   } else if (P.Vz != nullptr && P.Vint != nullptr) {
     // V / 2^e with 2^e <= |V|_F < 2^(e+1): no entry of the costates exceeds 2,
@@ -265,18 +295,20 @@ __global__ __launch_bounds__(256) void k_prep(Work W) {
 // Per slice: theta = dt (|H0|_1 + sum_j |u[j][k]| |Hc[j]|_1) in FP64, then the
 // scaling exponent and Taylor degrees of choose_plan().
 // flags: bit 0 gradient, bit 1 the expm evaluates by Paterson-Stockmeyer
-// (FP32 at D = 128).
+// (FP32 at D = 128), bit 2 the gradient takes the commutator series.
 __global__ __launch_bounds__(256) void k_plan(Work W, double ur, int flags) {
   const Items I(W);
   for (int item = blockIdx.x * 256 + threadIdx.x; item < I.total; item += gridDim.x * 256) {
     int p, k;
     split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
     const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
-    double th = P.norms[0];
+    double th = gp(P.norms)[0];
+#pragma unroll 4
     for (int j = 0; j < P.m; ++j) th = fma(fabs(gp(P.u)[(size_t)j * P.N + k]), gp(P.norms)[j + 1], th);
     th *= P.dt;
-    const SlicePlan pl = choose_plan(th, ur, (flags & 1) != 0, (flags & 2) != 0);
+    const SlicePlan pl = choose_plan(th, ur, (flags & 1) != 0, (flags & 2) != 0, (flags & 4) != 0);
     const int cf = controls_flags(P);
+    if (pl.s > 0) atomicOr(P.squared, 1);
     P.sq[k] = pack_plan(pl) | (pl.s == 0 && (cf & 2) ? kPlanSampled : 0) | ((cf & 1) ? kPlanMono : 0);
   }
 }
@@ -922,11 +954,9 @@ constexpr int kScanBufs = (sizeof(T) == 4 && D == 64) ? 1 : 2;
 
 template <typename T, int D, typename Ops, bool PERSIST>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kMinWaves<D>)))
-void k_scan_local(Work W, int dir, T dscale) {
+void k_scan_local(Work W, int dir) {
   __shared__ __align__(16) unsigned char lds[kScanBufs<T, D>][Ops::BYTES];
-  const int bwd = dir < 0 ? (int)blockIdx.y : dir & 1;  // dir < 0: both passes, one per blockIdx.y
-  const bool keep = dir != 2;  // dir = 2: forward, the chunk totals only
-  // dscale: 1 over the power of two by which the stored Delta is scaled
+  const int bwd = dir < 0 ? (int)blockIdx.y : dir;  // dir < 0: both passes, one per blockIdx.y
   Lane L;
   const Items I(W);
   for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
@@ -947,11 +977,11 @@ void k_scan_local(Work W, int dir, T dscale) {
     const int kn = bwd ? k - 1 : k + 1;
     // the store of S before the prefetch of the next Delta, so that the wait
     // for the prefetch at the next step covers nothing issued after it
-    if (keep) panel_store(pf_mat<T, D>(bwd ? P.bloc : P.xprev, k - W.rg.kbase), S, L);
+    panel_store(pf_mat<T, D>(bwd ? P.bloc : P.xprev, k - W.rg.kbase), S, L);
     if (i + 1 < n) panel_load(nxt, pf_mat<T, D>(P.delta, kn - W.rg.kbase), L);
     __syncthreads();
     Ops::gemm3(acc, buf, S, L, true);
-    panel_axpby(S, dscale, acc, (T)1);
+    panel_axpby(S, (T)1, acc, (T)1);
     k = kn;
   }
   if (!bwd && !W.rg.recompute) panel_store(pf_mat<T, D>(P.tf, c), S, L);  // (k_reun follows in FP32)
@@ -1494,44 +1524,124 @@ void k_adjoint(Work W) {
   }
 }
 
-// ================================================================ FP32 on the FP16 matrix cores
+// ================================================================ segments: the Hermitian path at D <= 64
 //
-// The FP32 expm, costate scan and adjoint at 32 <= D <= 64 for Hermitian
-// Hamiltonians, with their products on F16Ops.  Panels and the stored Delta_k
-// and W_k carry its factor c = kF16Scale.
+// For Hermitian H_k the costates need no stored products and no Frechet
+// block.  With N_k = Q_{k-1} P_{k-1}^dag (Q, P of the header), W_k = U_k N_k and
+// N_{k+1} = U_k N_k U_k^dag, and
+//   Z_k = L(A_k^dag, W_k) = int_0^1 e^{sA_k} N_k e^{-sA_k} ds = sum_n C_n / (n + 1)!,
+//   N_{k+1} = sum_n C_n / n!,   C_0 = N_k,  C_{n+1} = [A_k, C_n]
+// (A_k anti-Hermitian).  Every step keeps Hermitian matrices Hermitian, and
+// dF/du[j][k] = -(2 dt / d^2) |g| Tr(Hc[j] Z(Y_k)) reads only the Hermitian
+// Y = (g N - (g N)^dag) / (2i |g|), whose commutator is one product:
+// [A, C] = A C + (A C)^dag.  A slice costs m products with the one left factor
+// A_k (m the degree at which the series' remainder at 2 |A_k| meets the unit
+// roundoff) where the block form took a chain product, W, and six to twelve
+// for the block, and reads nothing per slice but its amplitudes.
+//
+// Slices with s > 0 take the series on A_k / 2^s and double it s times,
+// Z <- (Z + U Z U^dag) / 2 with U the propagator of the part covered so far.
+//
+// The chunks are cut into segments of at most kSegMax slices, so that few
+// problems still fill the chip: k_seg_fwd forms the segment totals, k_seg_join
+// the chunk totals and the prefixes at the segment starts, k_seg_y each
+// chunk's Y (after the carry), k_seg_grad the gradient of a segment from
+// Y at its start, P_s Y P_s^dag (from P_s - I: the rounding of the products
+// then scales with it and not with Y).  Panels and left factors carry Ops::C.
+// Two workgroups per CU (two waves per SIMD) where registers and LDS allow it.
+template <typename T, int D>
+constexpr int kSegWaves = (sizeof(T) == 8 && D == 64) ? 1 : 2;
 
-// X = -i c H_k as this wavefront's panel (FP32), H_k = H0 + sum_j u[j][k] Hc[j]
-// with the sums of assemble(); lds holds one planar FP32 matrix and is free
-// again after the caller's next barrier.
-template <int D>
-__device__ __forceinline__ void assemble_panel(Panel<float, D>& X, void* lds, const ProbDesc& P, int k, double c,
-                                               bool mono, const Lane& L) {
+// Item -> (problem, chunk, segment), and the segment's slices [ka, kb).
+struct SegItem {
+  int p, c, s, ka, kb;
+};
+__device__ __forceinline__ SegItem seg_split(int item, const Range& rg, const Items& I, const ProbDesc* descs) {
+  SegItem r;
+  if (rg.c_n > 0) {
+    const int sc = seg_count(descs[0].D, descs[0].L);  // uniform launches share L
+    const int per = rg.c_n * sc;
+    r.p = item / per;
+    const int x = item - r.p * per;
+    r.c = rg.c_lo + x / sc;
+    r.s = x % sc;
+  } else {
+    r.p = locate(I.start, I.nprob, item);
+    const int x = item - gp(I.start)[r.p];
+    const int sc = seg_count(descs[I.desc(r.p)].D, descs[I.desc(r.p)].L);
+    r.c = x / sc;
+    r.s = x % sc;
+  }
+  const ProbDesc& P = descs[I.desc(r.p)];
+  const int h = seg_len(P.D, P.L);
+  const int k1 = min(P.N, (r.c + 1) * P.L);
+  r.ka = r.c * P.L + r.s * h;
+  r.kb = min(k1, r.ka + h);
+  return r;
+}
+
+// The row tables and amplitudes of one segment in LDS (row-table controls,
+// where they fit): entries (j, a) in ENT, amplitudes u[j][ka + i] in SL * MAX.
+template <typename T, int D>
+struct SegTab {
+  // two workgroups of the d = 64 FP32 gradient kernel share a CU's 160 KB
+  static constexpr int ENT = (sizeof(T) == 4 && D == 64) ? 12 * D : 16 * D;
+  static constexpr int MAXM = ENT / D;
+  T vr[ENT], vi[ENT];
+  unsigned char col[ENT];
+  T u[MAXM * kSegMax];
+};
+
+template <typename T, int D>
+__device__ __forceinline__ bool seg_tab_load(SegTab<T, D>& S, const ProbDesc& P, int ka, int kb, bool mono) {
+  if (!mono || P.m > SegTab<T, D>::MAXM) return false;
+  const T* mv = reinterpret_cast<const T*>(P.mval);
+  for (int e = threadIdx.x; e < P.m * D; e += 4 * D) {
+    S.col[e] = (unsigned char)gp(P.mcol)[e];
+    S.vr[e] = gp(mv)[2 * e];
+    S.vi[e] = gp(mv)[2 * e + 1];
+  }
+  const int n = kb - ka;
+  for (int e = threadIdx.x; e < P.m * n; e += 4 * D) {
+    const int j = e / n, i = e - j * n;
+    S.u[j * kSegMax + i] = (T)gp(P.u)[(size_t)j * P.N + ka + i];
+  }
+  return true;
+}
+
+// X = -i c H_k as this wavefront's panel, H_k = H0 + sum_j u[j][k] Hc[j] with
+// the sums of assemble(); lds (one planar matrix) and the tables are written
+// and read inside: starts and ends with a barrier.
+template <typename T, int D>
+__device__ __forceinline__ void assemble_panel(Panel<T, D>& X, void* lds, const ProbDesc& P, int k, double c,
+                                               bool mono, const SegTab<T, D>* tab, int ki, const Lane& L) {
+  using v4 = typename Prec<T>::v4;
   constexpr int NV = D / 16;
   constexpr int NT = 4 * D;
-  const float* H = reinterpret_cast<const float*>(P.Hint);
-  float* pl = static_cast<float*>(lds);
-  float* pi = pl + D * Mat<float, D>::SD;
+  const T* H = reinterpret_cast<const T*>(P.Hint);
+  T* pl = static_cast<T*>(lds);
+  T* pi = pl + D * Mat<T, D>::SD;
   const int e0 = 4 * threadIdx.x;
-  f4 hr[NV], hi[NV];
+  v4 hr[NV], hi[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    hr[v] = Prec<float>::gld4(H + e0 + 4 * NT * v);
-    hi[v] = Prec<float>::gld4(H + D * D + e0 + 4 * NT * v);
+    hr[v] = Prec<T>::gld4(H + e0 + 4 * NT * v);
+    hi[v] = Prec<T>::gld4(H + D * D + e0 + 4 * NT * v);
   }
   if (!mono) {
-    constexpr int G = 2;  // controls loaded together
+    constexpr int G = sizeof(T) == 4 ? 2 : 1;  // controls loaded together
     for (int j0 = 0; j0 < P.m; j0 += G) {
-      f4 ar[G][NV], ai[G][NV];
-      float uw[G];
+      v4 ar[G][NV], ai[G][NV];
+      T uw[G];
 #pragma unroll
       for (int jj = 0; jj < G; ++jj) {
         const int j = min(j0 + jj, P.m - 1);
-        uw[jj] = j0 + jj < P.m ? (float)gp(P.u)[(size_t)j * P.N + k] : 0.0f;
-        const float* Hj = H + (size_t)(j + 1) * 2 * D * D + e0;
+        uw[jj] = j0 + jj < P.m ? (T)gp(P.u)[(size_t)j * P.N + k] : (T)0;
+        const T* Hj = H + (size_t)(j + 1) * 2 * D * D + e0;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          ar[jj][v] = Prec<float>::gld4(Hj + 4 * NT * v);
-          ai[jj][v] = Prec<float>::gld4(Hj + D * D + 4 * NT * v);
+          ar[jj][v] = Prec<T>::gld4(Hj + 4 * NT * v);
+          ai[jj][v] = Prec<T>::gld4(Hj + D * D + 4 * NT * v);
         }
       }
 #pragma unroll
@@ -1540,57 +1650,58 @@ __device__ __forceinline__ void assemble_panel(Panel<float, D>& X, void* lds, co
         for (int v = 0; v < NV; ++v)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            hr[v][i] = fmaf(uw[jj], ar[jj][v][i], hr[v][i]);
-            hi[v][i] = fmaf(uw[jj], ai[jj][v][i], hi[v][i]);
+            hr[v][i] = fma(uw[jj], ar[jj][v][i], hr[v][i]);
+            hi[v][i] = fma(uw[jj], ai[jj][v][i], hi[v][i]);
           }
     }
   }
+  __syncthreads();  // the buffer's last readers are done
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const int e = e0 + 4 * NT * v;
-    const int off = lds_off<float, D>(e / D, e % D);
-    Prec<float>::st4(pl + off, hr[v]);
-    Prec<float>::st4(pi + off, hi[v]);
+    if constexpr (sizeof(T) == 4) {
+      const int off = lds_off<T, D>(e / D, e % D);
+      Prec<T>::st4(pl + off, hr[v]);
+      Prec<T>::st4(pi + off, hi[v]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int off = lds_off<T, D>(e / D, e % D + i);
+        pl[off] = hr[v][i];
+        pi[off] = hi[v][i];
+      }
+    }
   }
   __syncthreads();
   if (mono) {
     // The thread of row a adds the row's entry of each control in turn; runs of
-    // controls at the same column (X_i and Y_i) stay in registers, and the
-    // tables of G controls are loaded together.
+    // controls at the same column (X_i and Y_i) stay in registers.
     if ((int)threadIdx.x < D) {
-      constexpr int G = 4;
       const int a = threadIdx.x;
-      const float* mv = reinterpret_cast<const float*>(P.mval);
       int off = -1;
-      float sr = 0.0f, si = 0.0f;
-      for (int j0 = 0; j0 < P.m; j0 += G) {
-        int col[G];
-        float vr[G], vi[G], uj[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-          const int j = min(j0 + i, P.m - 1);
-          const size_t idx = (size_t)j * D + a;
-          col[i] = gp(P.mcol)[idx];
-          vr[i] = gp(mv)[2 * idx];
-          vi[i] = gp(mv)[2 * idx + 1];
-          uj[i] = (float)gp(P.u)[(size_t)j * P.N + k];
-        }
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-          if (j0 + i < P.m) {
-            const int o = lds_off<float, D>(a, col[i]);
-            if (o != off) {
-              if (off >= 0) {
-                pl[off] = sr;
-                pi[off] = si;
-              }
-              off = o;
-              sr = pl[o];
-              si = pi[o];
-            }
-            sr = fmaf(uj[i], vr[i], sr);
-            si = fmaf(uj[i], vi[i], si);
+      T sr = 0, si = 0;
+      auto add = [&](int col, T uj, T vr, T vi) {
+        const int o = lds_off<T, D>(a, col);
+        if (o != off) {
+          if (off >= 0) {
+            pl[off] = sr;
+            pi[off] = si;
           }
+          off = o;
+          sr = pl[o];
+          si = pi[o];
+        }
+        sr = fma(uj, vr, sr);
+        si = fma(uj, vi, si);
+      };
+      if (tab) {
+        for (int j = 0; j < P.m; ++j)
+          add(tab->col[j * D + a], tab->u[j * kSegMax + ki], tab->vr[j * D + a], tab->vi[j * D + a]);
+      } else {
+        const T* mv = reinterpret_cast<const T*>(P.mval);
+        for (int j = 0; j < P.m; ++j) {
+          const size_t idx = (size_t)j * D + a;
+          add(gp(P.mcol)[idx], (T)gp(P.u)[(size_t)j * P.N + k], gp(mv)[2 * idx], gp(mv)[2 * idx + 1]);
         }
       }
       pl[off] = sr;
@@ -1598,105 +1709,177 @@ __device__ __forceinline__ void assemble_panel(Panel<float, D>& X, void* lds, co
     }
     __syncthreads();
   }
-  // c in two FP32 numbers: its rounding alone would be the same relative error
-  // in every slice, and add up over the chain
-  const float f = (float)c, fl = (float)(c - (double)f);
-  panel_from_lds(X, static_cast<const float*>(lds), L);
+  panel_from_lds(X, static_cast<const T*>(lds), L);
+  __syncthreads();
+  // c in two numbers of type T: in FP32 its rounding alone would be the same
+  // relative error in every slice, and add up over the chain
+  const T f = (T)c, fl = (T)(c - (double)f);
 #pragma unroll
   for (int rb = 0; rb < NV; ++rb)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float xr = X.re[rb][r], xi = X.im[rb][r];
-      X.re[rb][r] = fmaf(f, xi, fl * xi);  // -i c (xr + i xi)
-      X.im[rb][r] = -fmaf(f, xr, fl * xr);
+      const T xr = X.re[rb][r], xi = X.im[rb][r];
+      X.re[rb][r] = fma(f, xi, fl * xi);  // -i c (xr + i xi)
+      X.im[rb][r] = -fma(f, xr, fl * xr);
     }
 }
 
-// c (U_k - I) of the plan (s, q) from X = c A_k / 2^s (panel), A_k being
-// anti-Hermitian: Horner in delta form, D <- (X + X D) / i for i = q - 1 ... 1
-// from D = X / q, then s squarings.  lds: one F16Ops matrix, in use until the
-// caller's next barrier; starts with a barrier (the LDS may still be read).
-template <int D>
-__device__ __forceinline__ void taylor_delta(Panel<float, D>& R, const Panel<float, D>& X, void* lds, int s, int q,
+// Coefficients of the degree-8 Taylor polynomial in three products (Bader,
+// Blanes and Casas, Mathematics 7 (2019) 1174, eq. 8):
+//   A4 = A2 (x1 A + x2 A2),  T8 = I + A + y2 A2 + (x3 A2 + A4)(x4 I + x5 A + x6 A2 + x7 A4).
+struct T8 {
+  static constexpr double r177 = 13.304134695650071;  // sqrt(177)
+  static constexpr double x3 = 2.0 / 3.0, x1 = x3 * (1 + r177) / 88, x2 = x3 * (1 + r177) / 352,
+                          x4 = (-271 + 29 * r177) / (315 * x3), x5 = 11 * (-1 + r177) / (1260 * x3),
+                          x6 = 11 * (-9 + r177) / (5040 * x3), x7 = (89 - r177) / (5040 * x3 * x3),
+                          y2 = (857 - 58 * r177) / 630;
+};
+
+// R = C (exp(A) - I) from the panel X = C A / 2^s (A anti-Hermitian), whose left
+// factor is in lds already (and is replaced there): the Taylor polynomial of a
+// degree of at least q in taylor_products(q) products, then s squarings.
+//  * q <= 3: Horner in delta form with the one left factor, R <- (X + X R) / i;
+//  * q = 4: X + A2 (I / 2 + X / 6 + A2 / 24);  q <= 8: T8;
+//  * above: Paterson-Stockmeyer with A3 as the step.
+template <typename T, int D, typename Ops>
+__device__ __forceinline__ void taylor_delta(Panel<T, D>& R, const Panel<T, D>& X, void* lds, int s, int q,
                                              const Lane& L) {
-  using Ops = F16Ops<D>;
-  __syncthreads();
-  Ops::store_nct(lds, X, L);  // X = -X^dag
-  __syncthreads();
-  R = X;
-  if (q >= 2) {
-    panel_scale(R, (float)(1.0 / q));
-    Panel<float, D> acc;
+  constexpr T C = Ops::C, CI = (T)1 / Ops::C;
+  Panel<T, D> acc;
+  if (q <= 3) {
+    R = X;
+    panel_scale(R, (T)(1.0 / q));
     for (int i = q - 1; i >= 1; --i) {
-      Ops::gemm(acc, lds, R, L, true);
-      const float ri = (float)(1.0 / i), rs = ri * kF16Inv;
+      Ops::mul(acc, lds, R, L);
+      const T ri = (T)(1.0 / i), rs = ri * CI;
 #pragma unroll
       for (int rb = 0; rb < D / 16; ++rb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          R.re[rb][r] = fmaf(rs, acc.re[rb][r], ri * X.re[rb][r]);
-          R.im[rb][r] = fmaf(rs, acc.im[rb][r], ri * X.im[rb][r]);
+          R.re[rb][r] = fma(rs, acc.re[rb][r], ri * X.re[rb][r]);
+          R.im[rb][r] = fma(rs, acc.im[rb][r], ri * X.im[rb][r]);
         }
+    }
+  } else {
+    Panel<T, D> A2;
+    Ops::mul(A2, lds, X, L);
+    panel_scale(A2, CI);
+    if (q <= 8) {
+      __syncthreads();
+      Ops::store_ct(lds, A2, L);  // A2 = A2^dag
+      __syncthreads();
+      // B = a I + b X + c A2 as the right factor of the next product
+      const T a = q == 4 ? (T)0.5 : (T)0, b = (T)(q == 4 ? 1.0 / 6 : T8::x1), c = (T)(q == 4 ? 1.0 / 24 : T8::x2);
+#pragma unroll
+      for (int rb = 0; rb < D / 16; ++rb) {
+        R.re[rb] = b * X.re[rb] + c * A2.re[rb];
+        R.im[rb] = b * X.im[rb] + c * A2.im[rb];
+      }
+      panel_add_identity(R, L, a * C);
+      Ops::mul(acc, lds, R, L);
+      panel_scale(acc, CI);  // A4 (q = 4: A2 B)
+      R = X;
+      if (q == 4) {
+        panel_fma(R, (T)1, acc);
+      } else {
+        panel_fma(R, (T)T8::y2, A2);
+#pragma unroll
+        for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const T ar = A2.re[rb][r], ai = A2.im[rb][r], pr = acc.re[rb][r], pi = acc.im[rb][r];
+            acc.re[rb][r] = fma((T)T8::x3, ar, pr);  // the left factor x3 A2 + A4
+            acc.im[rb][r] = fma((T)T8::x3, ai, pi);
+            A2.re[rb][r] = fma((T)T8::x5, X.re[rb][r], fma((T)T8::x6, ar, (T)T8::x7 * pr));
+            A2.im[rb][r] = fma((T)T8::x5, X.im[rb][r], fma((T)T8::x6, ai, (T)T8::x7 * pi));
+          }
+        __syncthreads();
+        Ops::store(lds, acc, L);
+        panel_add_identity(A2, L, (T)(T8::x4 * C));
+        __syncthreads();
+        Ops::mul(acc, lds, A2, L);
+        panel_fma(R, CI, acc);
+      }
+    } else {
+      Ops::mul(R, lds, A2, L);
+      panel_scale(R, CI);  // A3
+      __syncthreads();
+      Ops::store_nct(lds, R, L);  // A3 = -A3^dag
+      __syncthreads();
+      const int top = (q - 1) / 3;
+      panel_scale(R, q >= 3 * top + 3 ? (T)inv_factorial(3 * top + 3) : (T)0);
+      for (int t = top;; --t) {  // R <- D_t + A3 R, D_t = X^0, X, X^2 over (3t)!, (3t+1)!, (3t+2)!
+        const T b = 3 * t + 1 <= q ? (T)inv_factorial(3 * t + 1) : (T)0;
+        const T c = 3 * t + 2 <= q ? (T)inv_factorial(3 * t + 2) : (T)0;
+        panel_fma(R, b, X);
+        panel_fma(R, c, A2);
+        if (t == 0) break;
+        panel_add_identity(R, L, (T)inv_factorial(3 * t) * C);
+        Ops::mul(acc, lds, R, L);
+        R = acc;
+        panel_scale(R, CI);
+      }
     }
   }
   for (int j = 0; j < s; ++j) {
-    Panel<float, D> acc;
     __syncthreads();
     Ops::store(lds, R, L);
     __syncthreads();
-    Ops::gemm(acc, lds, R, L, true);
-#pragma unroll
-    for (int rb = 0; rb < D / 16; ++rb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        R.re[rb][r] = fmaf(kF16Inv, acc.re[rb][r], 2.0f * R.re[rb][r]);
-        R.im[rb][r] = fmaf(kF16Inv, acc.im[rb][r], 2.0f * R.im[rb][r]);
-      }
+    Ops::mul(acc, lds, R, L);
+    panel_scale(R, (T)2);
+    panel_fma(R, CI, acc);
   }
 }
 
-// Delta_k = c (U_k - I); gradient runs with dense controls also keep X (in
-// hk), which the adjoint then need not assemble again from m + 1 matrices.
-template <int D, bool PERSIST>
-__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void k_expm_f16(Work W) {
-  using Ops = F16Ops<D>;
-  static_assert(Mat<float, D>::LDS_ELEMS * 4 <= Ops::BYTES, "one planar FP32 matrix");
-  __shared__ __align__(16) unsigned char lds[Ops::BYTES];
+// The totals U_{kb-1} ... U_{ka} of the segments (into xprev at the segment's
+// first slice).  The exponentials' products run on Ops; the chain's, whose
+// errors add up over the N slices, always in precision T.
+template <typename T, int D, typename Ops, bool PERSIST>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_seg_fwd(Work W) {
+  using Std = StdOps<T, D>;
+  constexpr T CI = (T)1 / Ops::C;
+  __shared__ __align__(16) unsigned char la[Ops::BYTES];
+  __shared__ __align__(16) unsigned char lb[Std::BYTES];
+  __shared__ SegTab<T, D> tab;
   Lane L;
   const Items I(W);
   for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
-    int p, k;
-    split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
-    const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
-    const int sqk = gp(P.sq)[k];
-    int s, q, qb;
-    unpack_sq(sqk, s, q, qb);
-    const bool mono = (sqk & kPlanMono) != 0;
-    Panel<float, D> X, R;
-    assemble_panel<D>(X, lds, P, k, ldexp(P.dt * kF16Scale, -s), mono, L);
-    if (!mono && (P.flags & RUN_GRAD)) panel_store(pf_mat<float, D>(P.hk, k - W.rg.kbase), X, L);
-    taylor_delta<D>(R, X, lds, s, q, L);
-    panel_store(pf_mat<float, D>(P.delta, k - W.rg.kbase), R, L);
+    const SegItem g = seg_split(item, W.rg, I, W.descs);
+    if (g.ka < g.kb) {
+      const ProbDesc P = W.descs[I.desc(g.p)];  // a copy: stores cannot alias it
+      const bool mono = (gp(P.sq)[g.ka] & kPlanMono) != 0;
+      const SegTab<T, D>* tb = seg_tab_load<T, D>(tab, P, g.ka, g.kb, mono) ? &tab : nullptr;
+      Panel<T, D> S, X, R;
+      for (int k = g.ka; k < g.kb; ++k) {
+        int s, q, qb;
+        unpack_sq(gp(P.sq)[k], s, q, qb);
+        assemble_panel<T, D>(X, lb, P, k, ldexp(P.dt * (double)Ops::C, -s), mono, tb, k - g.ka, L);
+        Ops::store_nct(la, X, L);  // X = -X^dag
+        __syncthreads();
+        taylor_delta<T, D, Ops>(R, X, la, s, q, L);
+        panel_scale(R, CI);
+        if (k == g.ka) {
+          S = R;
+          panel_add_identity(S, L, (T)1);
+        } else {
+          Std::store(lb, R, L);  // (every wavefront has left assemble_panel)
+          __syncthreads();
+          Std::gemm3(X, lb, S, L, true);
+          panel_fma(S, (T)1, X);  // S <- S + Delta S
+        }
+      }
+      panel_store(pf_mat<T, D>(P.xprev, g.ka - W.rg.kbase), S, L);
+    }
     if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
     __syncthreads();
   }
 }
 
-// The costates W_k = Q_k P_{k-1}^dag of a chunk, one workgroup per chunk,
-// without stored products: with N_{k+1} = W_k U_k^dag = Q_k P_k^dag and the
-// slices unitary (U_k U_k^dag = I to the unit roundoff of the plan),
-//   N_{k1} = mc[c] tf[c]^dag,   W_k = N_{k+1} U_k,   N_k = U_k^dag W_k,
-// two products per slice from the chunk's last slice down, each adding
-// N Delta_k or Delta_k^dag W to the running panel.  Per slice it reads Delta_k
-// and writes W_k (into bloc): the forward scan stores nothing per slice and
-// the adjoint reads one matrix instead of two or three (five HBM transfers of
-// a matrix per slice in the whole path, against eleven with stored prefix and
-// suffix products and the kept H_k and X^2).  Two barriers per slice: N in
-// buffer 0, Delta_k^dag in buffer 1, from which the right factor Delta_k of
-// the first product is read as it is.
-template <int D, bool PERSIST>
-__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void k_wscan_f16(Work W) {
-  using Ops = F16Ops<D>;
+// Per chunk: the prefixes P_s at its segment starts, as P_s - I (into bloc at
+// the segment's first slice), and the chunk total.
+template <typename T, int D, bool PERSIST>
+__global__ __launch_bounds__(4 * D) void k_seg_join(Work W) {
+  using Ops = StdOps<T, D>;
   __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
   Lane L;
   const Items I(W);
@@ -1704,158 +1887,343 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void
     int p, c;
     split_item(item, W.rg.c_lo, W.rg.c_n, I.start, I.nprob, p, c);
     const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
-    const int k0 = c * P.L;
-    const int k1 = min(P.N, k0 + P.L);
-    Panel<float, D> S, nxt, acc;
-    typename Ops::Frag B;
-    panel_load(acc, pf_mat<float, D>(P.tf, c), L);
-    panel_load(nxt, pf_mat<float, D>(P.mc, c), L);
-    panel_scale(acc, kF16Scale);
-    panel_scale(nxt, kF16Scale);
-    Ops::store(lds[0], nxt, L);
-    Ops::store(lds[1], acc, L);
-    panel_load(nxt, pf_mat<float, D>(P.delta, k1 - 1 - W.rg.kbase), L);
-    __syncthreads();
-    Ops::frag_ct(B, lds[1], L);
-    Ops::gemm(S, lds[0], B, L, true);
-    panel_scale(S, kF16Inv);  // N_{k1}
-    __syncthreads();
-    for (int k = k1 - 1; k >= k0; --k) {
-      Ops::store(lds[0], S, L);
-      Ops::store_ct(lds[1], nxt, L);
-      if (k > k0) panel_load(nxt, pf_mat<float, D>(P.delta, k - 1 - W.rg.kbase), L);
+    const int k1 = min(P.N, (c + 1) * P.L), h = seg_len(P.D, P.L);
+    Panel<T, D> S, nxt, acc;
+    int k = c * P.L;
+    panel_load(S, pf_mat<T, D>(P.xprev, k - W.rg.kbase), L);
+    k += h;
+    if (k < k1) panel_load(nxt, pf_mat<T, D>(P.xprev, k - W.rg.kbase), L);
+    for (int i = 0; k < k1; ++i) {
+      acc = S;
+      panel_add_identity(acc, L, (T)-1);
+      panel_store(pf_mat<T, D>(P.bloc, k - W.rg.kbase), acc, L);
+      Ops::store(lds[i & 1], nxt, L);
+      k += h;
+      if (k < k1) panel_load(nxt, pf_mat<T, D>(P.xprev, k - W.rg.kbase), L);
       __syncthreads();
-      Ops::frag_ct(B, lds[1], L);
-      Ops::gemm(acc, lds[0], B, L, true);
-      panel_fma(S, kF16Inv, acc);  // W_k = N + N Delta
-      panel_store(pf_mat<float, D>(P.bloc, k - W.rg.kbase), S, L);
-      if (k == k0) break;
-      Ops::gemm(acc, lds[1], S, L, true);
-      panel_fma(S, kF16Inv, acc);  // N = W + Delta^dag W
-      __syncthreads();
+      // four real products: the three-product form's larger error in these
+      // full-size factors doubled the gradient's
+      Ops::gemm(acc, lds[i & 1], S, L, true);
+      S = acc;
     }
+    if (!W.rg.recompute) panel_store(pf_mat<T, D>(P.tf, c), S, L);  // (k_reun follows in FP32)
     if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
     __syncthreads();
   }
 }
 
-// c Z_k, Z_k = L(A_k^dag, W_k), from R1 = c A_k^dag / 2^s (anti-Hermitian) and
-// R2 = c W_k (panels), by the steps 2 to 4 of k_adjoint; X^2 is formed here
-// (reading it back from the expm would cost two HBM transfers of a matrix,
-// more than the product), and the block is halved at each squaring instead of
-// W being divided by 2^s, so that every factor stays in FP16's range whatever
-// s.  lds0 and lds1 hold one F16Ops matrix each and are free on entry; on
-// return they may still be read by other wavefronts.
-template <int D>
-__device__ __forceinline__ void frechet_panel(Panel<float, D>& R2, Panel<float, D>& R1, void* lds0, void* lds1,
-                                              int s, int qb, const Lane& L) {
-  using Ops = F16Ops<D>;
-  Panel<float, D> A1, A2, R3;
-  Ops::store_nct(lds0, R1, L);  // X = -X^dag
-  Ops::store(lds1, R2, L);
-  __syncthreads();
-  {
-    Ops::gemm(A2, lds0, R2, L, true);
-    typename Ops::Frag BX;
-    Ops::frag_nct(BX, lds0, L);
-    Ops::gemm(A1, lds0, BX, L, true);
-    Ops::gemm(A2, lds1, BX, L, false);
-  }
-  panel_scale(A1, kF16Inv);  // X2
-  panel_scale(A2, kF16Inv);  // S = X E + E X
-  __syncthreads();           // X and E are read: M^2 takes their place
-  Ops::store_ct(lds0, A1, L);  // X2 = X2^dag
-  Ops::store(lds1, A2, L);
-  const int top = (qb - 2) / 2;
-  int t;
-  if (qb & 1) {  // C = I / (qb-1)! + M / qb!
-    t = top - 1;
-    A1 = R1;
-    panel_scale(A1, (float)inv_factorial(qb));
-    panel_add_identity(A1, L, (float)(kF16Scale * inv_factorial(qb - 1)));
-    A2 = R2;
-    panel_scale(A2, (float)inv_factorial(qb));
-  } else if (top > 0) {  // C = D_{top-1} + M^2 / qb!
-    t = top - 2;
-    panel_axpby(A1, (float)inv_factorial(qb - 1), R1, (float)inv_factorial(qb));
-    panel_add_identity(A1, L, (float)(kF16Scale * inv_factorial(qb - 2)));
-    panel_axpby(A2, (float)inv_factorial(qb - 1), R2, (float)inv_factorial(qb));
-  } else {  // qb = 2: C = I / 2
-    t = -1;
-    panel_zero(A1);
-    panel_add_identity(A1, L, 0.5f * kF16Scale);
-    panel_zero(A2);
-  }
-  __syncthreads();
-  for (; t >= 0; --t) {
-    const double a = inv_factorial(2 * t + 2), b = inv_factorial(2 * t + 3);
-    R3 = R2;
-    panel_scale(R3, (float)(b * kF16Scale));
-    Ops::gemm(R3, lds0, A2, L, false);
-    Ops::gemm(R3, lds1, A1, L, false);
-    panel_scale(R3, kF16Inv);  // b E + X2 C2 + S C1
-    A2 = R1;
-    panel_scale(A2, (float)(b * kF16Scale));
-    panel_add_identity(A2, L, (float)(a * kF16Scale * kF16Scale));
-    Ops::gemm(A2, lds0, A1, L, false);
-    panel_scale(A2, kF16Inv);  // a I + b X + X2 C1
-    A1 = A2;
-    A2 = R3;
-  }
-  Ops::gemm(R3, lds0, A2, L, true);
-  Ops::gemm(R3, lds1, A1, L, false);
-  panel_fma(R2, kF16Inv, R3);  // Q = E + X2 C2 + S C1
-  if (s == 0) return;
-  // squarings, halved: Q <- Q + (D1 Q + Q D1) / 2, D1 <- 2 D1 + D1^2
-  Ops::gemm(R3, lds0, A1, L, true);
-  panel_fma(R1, kF16Inv, R3);  // D1 = X + X2 C1
-  for (int j = 0; j < s; ++j) {
-    __syncthreads();
-    Ops::store(lds0, R1, L);
-    Ops::store(lds1, R2, L);
-    __syncthreads();
-    Ops::gemm(R3, lds0, R2, L, true);   // D1 Q
-    Ops::gemm(R3, lds1, R1, L, false);  // + Q D1
-    if (j + 1 < s) {
-      Ops::gemm(A1, lds0, R1, L, true);
-      panel_scale(R1, 2.0f);
-      panel_fma(R1, kF16Inv, A1);
-    }
-    panel_fma(R2, 0.5f * kF16Inv, R3);
-  }
-}
-
-template <int D, bool PERSIST>
-__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(2))) void k_adjoint_f16(Work W) {
-  using Ops = F16Ops<D>;
-  constexpr int NW = D / 16;
+// Per chunk, after the carry: N = Q_{k0-1} P_{k0-1}^dag at its start,
+// N = tf[c]^dag cb[c] cf[c]^dag with cf[c] = cf_loc[c] gcf[g] and
+// cb[c] = cb_loc[c] gcb[g], and from it Y = (w N - (w N)^dag) / (2i), w = g / |g|,
+// into mc; for the complex dg/du the parts of N itself, N = Y' + i Y:
+// Y into mc and Y' = (N + N^dag) / 2 into cb.
+template <typename T, int D>
+__global__ __launch_bounds__(4 * D) void k_seg_y(Work W) {
+  using Ops = StdOps<T, D>;
   __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
-  __shared__ double red[2 * kEpiDense * 2 * NW];
   Lane L;
   const Items I(W);
   for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
-    int p, k;
-    split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
+    int p, c;
+    split_item(item, W.rg.c_lo, W.rg.c_n, I.start, I.nprob, p, c);
     const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
+    const int g = c / P.CG;
+    Panel<T, D> a, b, x, y;
+    panel_load(a, pf_mat<T, D>(P.cf, c), L);
+    panel_load(b, pf_mat<T, D>(P.cb, c), L);
+    panel_load(x, grp_mat<T, D>(P, 2, g), L);
+    panel_load(y, grp_mat<T, D>(P, 3, g), L);
+    Ops::store(lds[0], a, L);
+    Ops::store(lds[1], b, L);
+    __syncthreads();
+    Ops::gemm3(a, lds[0], x, L, true);  // cf[c]
+    Ops::gemm3(b, lds[1], y, L, true);  // cb[c]
+    panel_load(x, pf_mat<T, D>(P.tf, c), L);
+    __syncthreads();
+    Ops::store_ct(lds[0], x, L);
+    Ops::store(lds[1], a, L);
+    __syncthreads();
+    Ops::gemm3(y, lds[0], b, L, true);  // tf^dag cb
+    Ops::load_ct(x, lds[1], L);
+    __syncthreads();
+    Ops::store(lds[0], y, L);
+    __syncthreads();
+    Ops::gemm3(a, lds[0], x, L, true);  // N
+    const bool raw = (P.flags & RUN_RAWDG) != 0;
+    double wr = 1.0, wi = 0.0;
+    if (!raw) {
+      const double gr = gp(P.g)[0], gi = gp(P.g)[1], n = sqrt(gr * gr + gi * gi);
+      if (n > 0) {
+        wr = gr / n;
+        wi = gi / n;
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double ar = (double)a.re[rb][r], ai = (double)a.im[rb][r];
+        a.re[rb][r] = (T)(wr * ar - wi * ai);
+        a.im[rb][r] = (T)(wr * ai + wi * ar);
+      }
+    Ops::store_ct(lds[1], a, L);
+    __syncthreads();
+    Ops::load(b, lds[1], L);  // (w N)^dag
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb) {
+      x.re[rb] = (T)0.5 * (a.im[rb] - b.im[rb]);
+      x.im[rb] = (T)0.5 * (b.re[rb] - a.re[rb]);
+      y.re[rb] = (T)0.5 * (a.re[rb] + b.re[rb]);
+      y.im[rb] = (T)0.5 * (a.im[rb] + b.im[rb]);
+    }
+    panel_store(pf_mat<T, D>(P.mc, c), x, L);
+    if (raw) panel_store(pf_mat<T, D>(P.cb, c), y, L);
+    __syncthreads();
+  }
+}
+
+// The gradient entries of slice k from the Hermitian Z (planar in LDS):
+// t_j = Tr(Hc[j] Z) in FP64, a real sum.  part: 0, Z of Y; 1, Z of Y'
+// (RUN_RAWDG).
+__device__ __forceinline__ void seg_grad_put(const ProbDesc& P, int j, int k, int part, double t) {
+  const double dt = P.dt * gp(P.vscale)[0];
+  if (P.flags & RUN_RAWDG) {
+    // dg/du[j][k] = -i dt Tr(Z(N)^dag Hc[j]) with N = Y' + i Y
+    gp(P.grad)[2 * ((size_t)j * P.N + k) + part] = -dt * t;
+  } else {
+    const double gr = gp(P.g)[0], gi = gp(P.g)[1];
+    gp(P.grad)[(size_t)j * P.N + k] = -2.0 * dt / ((double)P.d * P.d) * sqrt(gr * gr + gi * gi) * t;
+  }
+}
+
+constexpr int kSegEpi = 8;  // dense controls reduced together
+
+template <typename T, int D>
+__device__ __forceinline__ void seg_epilogue(const ProbDesc& P, int k, int part, const T* zl, double zscale,
+                                             const SegTab<T, D>* tab, double* red, bool mono, const Lane& L) {
+  using v4 = typename Prec<T>::v4;
+  constexpr int NV = D / 16;
+  constexpr int NT = 4 * D;
+  constexpr int NW = D / 16;
+  constexpr int SD = Mat<T, D>::SD;
+  if (mono) {
+    // lane group jj = t / D takes row a = t % D of controls jj + 4 i
+    constexpr int CPT = 4;
+    constexpr int GV = D / CPT;  // lanes per reduced value
+    const int a = threadIdx.x % D, jj = threadIdx.x / D;
+    const T* mv = reinterpret_cast<const T*>(P.mval);
+    for (int j0 = 0; j0 < P.m; j0 += 4 * CPT) {
+      double v[CPT];
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) {
+        const int j = j0 + jj + 4 * i;
+        v[i] = 0;
+        if (j < P.m) {
+          const int e = j * D + a;
+          const int col = tab ? (int)tab->col[e] : gp(P.mcol)[e];
+          const double x = (double)(tab ? tab->vr[e] : gp(mv)[2 * e]), y = (double)(tab ? tab->vi[e] : gp(mv)[2 * e + 1]);
+          const int off = lds_off<T, D>(a, col);
+          v[i] = (double)zl[off] * x + (double)zl[D * SD + off] * y;  // Re(conj(z) h)
+        }
+      }
+      const double t = group_sum_many<CPT, D>(v, L.lane);
+      const int j = j0 + jj + 4 * (a / GV);
+      if (a % GV == 0 && j < P.m) seg_grad_put(P, j, k, part, zscale * t);
+    }
+    return;
+  }
+  const int e0 = 4 * threadIdx.x;
+  const T* H = reinterpret_cast<const T*>(P.Hint);
+  for (int j0 = 0, grp = 0; j0 < P.m; j0 += kSegEpi, ++grp) {
+    double v[kSegEpi];
+#pragma unroll
+    for (int jj = 0; jj < kSegEpi; ++jj) {
+      v[jj] = 0;
+      if (j0 + jj < P.m) {
+        const T* Hj = H + (size_t)(j0 + jj + 1) * 2 * D * D + e0;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+          const int e = e0 + 4 * NT * q;
+          const v4 hr = Prec<T>::gld4(Hj + 4 * NT * q), hi = Prec<T>::gld4(Hj + D * D + 4 * NT * q);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int off = lds_off<T, D>(e / D, e % D + i);
+            v[jj] += (double)zl[off] * (double)hr[i] + (double)zl[D * SD + off] * (double)hi[i];
+          }
+        }
+      }
+    }
+    const double t = wave_sum_many<kSegEpi>(v, L.lane);
+    double* rg = red + (grp & 1) * kSegEpi * NW;
+    if ((L.lane & 7) == 0) rg[(L.lane >> 3) * NW + L.w] = t;
+    __syncthreads();
+    if ((int)threadIdx.x < kSegEpi && j0 + (int)threadIdx.x < P.m) {
+      double a = 0;
+      for (int w = 0; w < NW; ++w) a += rg[threadIdx.x * NW + w];
+      seg_grad_put(P, j0 + threadIdx.x, k, part, zscale * a);
+    }
+  }
+}
+
+// Y <- U Y U^dag = Y + G + G^dag + G D^dag with G = D Y, D = U - I: lds0 holds
+// D, lds1 is free; ends with a barrier.
+template <typename T, int D, typename Ops>
+__device__ __forceinline__ void conjugate_by(Panel<T, D>& Y, T f, void* lds0, void* lds1, const Lane& L) {
+  constexpr T CI = (T)1 / Ops::C;
+  Panel<T, D> G, acc;
+  Ops::mul(G, lds0, Y, L);
+  panel_scale(G, CI);
+  Ops::store(lds1, G, L);
+  __syncthreads();
+  Ops::mul_ct(acc, lds1, lds0, L);
+  panel_fma(G, CI, acc);  // G + G D^dag
+  Ops::load_ct(acc, lds1, L);
+  panel_fma(G, (T)1, acc);
+  panel_fma(Y, f, G);
+  __syncthreads();
+}
+
+// The gradient of the slices [ka, kb) of segment sg of chunk c.  SQ: slices
+// with s > 0 among them; without, their doublings would take the registers of
+// every slice (133 of them spilled at d = 64 in FP32).
+template <typename T, int D, typename Ops, bool SQ>
+__device__ __forceinline__ void seg_grad_body(const ProbDesc& P, int c, int sg, int ka, int kb, int kbase, int part,
+                                              bool mono, void* la, void* lb, SegTab<T, D>& tab, double* red,
+                                              const Lane& L) {
+  constexpr T C = Ops::C, CI = (T)1 / Ops::C;
+  T* pt = static_cast<T*>(lb);  // planar
+  const SegTab<T, D>* tb = seg_tab_load<T, D>(tab, P, ka, kb, mono) ? &tab : nullptr;
+  Panel<T, D> Y, Z, Q, R;
+  panel_load(Y, pf_mat<T, D>(part ? P.cb : P.mc, c), L);
+  panel_scale(Y, C);
+  if (sg > 0) {  // Y at the segment's start
+    panel_load(R, pf_mat<T, D>(P.bloc, ka - kbase), L);
+    panel_scale(R, C);
+    Ops::store(la, R, L);
+    __syncthreads();
+    conjugate_by<T, D, Ops>(Y, (T)1, la, lb, L);
+  }
+  for (int k = ka; k < kb; ++k) {
     const int sqk = gp(P.sq)[k];
     int s, q, qb;
     unpack_sq(sqk, s, q, qb);
-    const bool mono = (sqk & kPlanMono) != 0;
-    Panel<float, D> R1, R2;
-    panel_load(R2, pf_mat<float, D>(P.bloc, k - W.rg.kbase), L);  // c W_k
-    // c A_k^dag / 2^s
-    if (mono) {
-      assemble_panel<D>(R1, lds[0], P, k, -ldexp(P.dt * kF16Scale, -s), true, L);
+    const int m = plan_order(sqk);
+    assemble_panel<T, D>(R, lb, P, k, ldexp(P.dt * (double)C, -s), mono, tb, k - ka, L);
+    Ops::store_nct(la, R, L);  // A = -A^dag (every wavefront has left the previous slice's products)
+    __syncthreads();
+    // Q = C_n / n!, of norm at most (2 |A|)^n / n! |Y|: in FP16's range for
+    // every plan.  It joins Y and Z while the next product runs.
+    Q = Y;
+    panel_zero(Y);
+    panel_zero(Z);
+    T yk = 1, zk = 1;
+    auto gather = [&](int rb) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        Z.re[rb][r] = fma(zk, Q.re[rb][r], Z.re[rb][r]);
+        Z.im[rb][r] = fma(zk, Q.im[rb][r], Z.im[rb][r]);
+        if (SQ) {
+          Y.re[rb][r] = fma(yk, Q.re[rb][r], Y.re[rb][r]);
+          Y.im[rb][r] = fma(yk, Q.im[rb][r], Y.im[rb][r]);
+        } else {
+          Y.re[rb][r] += Q.re[rb][r];
+          Y.im[rb][r] += Q.im[rb][r];
+        }
+      }
+    };
+    for (int n = 1; n <= m; ++n) {
+      Ops::mul(R, la, Q, L, gather);
+      if (n > 1) __syncthreads();  // the previous transpose has been read
+      panel_to_lds_ct(pt, R, L);
       __syncthreads();
-    } else {
-      panel_load(R1, pf_mat<float, D>(P.hk, k - W.rg.kbase), L);
-      panel_scale(R1, -1.0f);
+      panel_from_lds(Q, pt, L);
+      const T ck = CI * (T)(1.0 / n);
+      zk = (T)(1.0 / (n + 1));
+      if (SQ && s > 0) yk = 0;  // Y waits for the whole slice's propagator
+#pragma unroll
+      for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          Q.re[rb][r] = (Q.re[rb][r] + R.re[rb][r]) * ck;
+          Q.im[rb][r] = (Q.im[rb][r] + R.im[rb][r]) * ck;
+        }
     }
-    frechet_panel<D>(R2, R1, lds[0], lds[1], s, qb, L);
-    panel_scale(R2, kF16Inv);
-    gradient_epilogue<float, D>(P, k, R2, L, lds[0], red, mono);
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb) gather(rb);
+    if constexpr (SQ) {
+      if (s > 0) {
+        assemble_panel<T, D>(Q, lb, P, k, ldexp(P.dt * (double)C, -s), mono, tb, k - ka, L);
+        taylor_delta<T, D, Ops>(R, Q, la, 0, q, L);
+        for (int j = 0;; ++j) {
+          __syncthreads();
+          Ops::store(la, R, L);
+          __syncthreads();
+          if (j == s) break;
+          conjugate_by<T, D, Ops>(Z, (T)0.5, la, lb, L);
+          Ops::mul(Q, la, R, L);
+          panel_scale(R, (T)2);
+          panel_fma(R, CI, Q);
+        }
+        conjugate_by<T, D, Ops>(Y, (T)1, la, lb, L);
+      }
+    }
+    __syncthreads();
+    panel_to_lds_ct(pt, Z, L);  // Z = Z^dag
+    __syncthreads();
+    seg_epilogue<T, D>(P, k, part, pt, (double)CI, tb, red, mono, L);
+  }
+}
+
+// One workgroup per segment, and the problems without any s > 0 (*P.squared).
+template <typename T, int D, typename Ops, bool PERSIST>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_seg_grad(Work W) {
+  constexpr int LB = StdOps<T, D>::BYTES > Ops::BYTES ? StdOps<T, D>::BYTES : Ops::BYTES;
+  __shared__ __align__(16) unsigned char la[Ops::BYTES];
+  __shared__ __align__(16) unsigned char lb[LB];
+  __shared__ SegTab<T, D> tab;
+  __shared__ double red[2 * kSegEpi * (D / 16)];
+  Lane L;
+  const Items I(W);
+  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+    const SegItem g = seg_split(item, W.rg, I, W.descs);
+    if (g.ka < g.kb) {
+      const ProbDesc P = W.descs[I.desc(g.p)];  // a copy: stores cannot alias it
+      const bool mono = (gp(P.sq)[g.ka] & kPlanMono) != 0;
+      if (gp(P.squared)[0] == 0)
+        seg_grad_body<T, D, Ops, false>(P, g.c, g.s, g.ka, g.kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, red, L);
+    }
     if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
     __syncthreads();
+  }
+}
+
+// The problems with squared slices: a grid that leaves at once when there is
+// none, its workgroups spread over the problems and then over their segments.
+template <typename T, int D, typename Ops>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_seg_grad_sq(Work W) {
+  constexpr int LB = StdOps<T, D>::BYTES > Ops::BYTES ? StdOps<T, D>::BYTES : Ops::BYTES;
+  __shared__ __align__(16) unsigned char la[Ops::BYTES];
+  __shared__ __align__(16) unsigned char lb[LB];
+  __shared__ SegTab<T, D> tab;
+  __shared__ double red[2 * kSegEpi * (D / 16)];
+  Lane L;
+  const Items I(W);
+  const int per = max(1, (int)gridDim.x / max(I.nprob, 1));  // workgroups of a problem
+  const int rank = (int)blockIdx.x / max(I.nprob, 1);
+  if (rank >= per) return;
+  for (int p = (int)blockIdx.x % max(I.nprob, 1); p < I.nprob; p += gridDim.x) {
+    const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
+    if (gp(P.squared)[0] == 0) continue;
+    const int sc = seg_count(P.D, P.L), h = seg_len(P.D, P.L);
+    const int c0 = W.rg.c_n > 0 ? W.rg.c_lo : 0, cn = W.rg.c_n > 0 ? W.rg.c_n : P.P;
+    for (int x = rank; x < cn * sc; x += per) {
+      const int c = c0 + x / sc, sg = x % sc;
+      const int ka = c * P.L + sg * h, kb = min(min(P.N, (c + 1) * P.L), ka + h);
+      if (ka >= kb) continue;
+      const bool mono = (gp(P.sq)[ka] & kPlanMono) != 0;
+      seg_grad_body<T, D, Ops, true>(P, c, sg, ka, kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, red, L);
+      __syncthreads();
+    }
   }
 }
 
@@ -2887,116 +3255,143 @@ static inline int grid_of(const Launch& L, int items, int cap) {
   return items < 1 ? 1 : (cap > 0 && items > cap ? cap : items);
 }
 
-// The FP16-split policy of the Hermitian FP32 path.
-template <typename Ops>
-constexpr bool kF16Path = false;
-template <int D>
-constexpr bool kF16Path<F16Ops<D>> = true;
-
+// The general-generator path at D <= 64 (Ops: the LDS policy of the adjoint's
+// products; the other stages run on StdOps).
 template <typename T, int D, typename Ops>
 static void stage_small(int stage, const Launch& L, const Range& rg, double ur) {
+  using Std = StdOps<T, D>;
   constexpr int NT = Mat<T, D>::NT;
-  constexpr bool F16 = kF16Path<Ops>;
-  // The forward scans, carries and chunk products: a chain of N slices and full-size
-  // factors, whose errors reach Tr(V^dag X_N) (two FP16 numbers keep 22-23 bits)
-  using COps = StdOps<T, D>;
   hipStream_t st = L.stream;
-  const int dirs = (L.flags & RUN_BWD) ? 2 : 1;
   const int grad = (L.flags & RUN_GRAD) ? 1 : 0;
   const Range all = {0, L.uniformN, 0, L.uniformP, rg.kbase};
-  const Work dyn = L.dyn ? Work{L.descs, 0, 0, nullptr, Range{0, 0, 0, 0, 0}, L.dyn} : Work{};
   switch (stage) {
-    case ST_PREP: {
-      Work w = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * (L.max_m + 2), nullptr,
-                                  Range{0, L.max_m + 2, 0, 0, 0}, nullptr};
-      hipLaunchKernelGGL((k_prep<T, D>), dim3(grid_of(L, w.total, 0)), dim3(256), 0, st, w);
-      break;
-    }
     case ST_PLAN: {
-      Work w = L.dyn ? dyn : slice_work(L, all);
-      hipLaunchKernelGGL(k_plan, dim3(L.dyn ? L.dyn_grid : (w.total + 255) / 256), dim3(256), 0, st, w, ur, grad);
+      Work w = slice_work(L, all);
+      hipLaunchKernelGGL(k_plan, dim3((w.total + 255) / 256), dim3(256), 0, st, w, ur, grad);
       break;
     }
     case ST_EXPM: {
-      // the split-BF16 policy serves the adjoint only (launch_stage)
-      if constexpr (F16) {
-        Work w = L.dyn ? dyn : slice_work(L, rg);
-        if (L.dyn) hipLaunchKernelGGL((k_expm_f16<D, true>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
-        else hipLaunchKernelGGL((k_expm_f16<D, false>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
-      } else if constexpr (kStdLds<T, D, Ops>) {
-      Work w = L.dyn ? dyn : slice_work(L, rg);
-      if (L.dyn) hipLaunchKernelGGL((k_expm<T, D, Ops, true>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
-      else hipLaunchKernelGGL((k_expm<T, D, Ops, false>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
-      }
+      Work w = slice_work(L, rg);
+      hipLaunchKernelGGL((k_expm<T, D, Std, false>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
       break;
     }
     case ST_SCAN:
     case ST_BSCAN: {
-      if constexpr (F16 || kStdLds<T, D, Ops>) {
-      Work w = L.dyn ? dyn : chunk_work(L, rg);
+      Work w = chunk_work(L, rg);
       // a recompute sweep runs the forward and backward passes of a segment
       // together (they are independent once mc is known)
-      const bool both = !F16 && stage == ST_SCAN && rg.recompute && !L.dyn;
+      const bool both = stage == ST_SCAN && rg.recompute;
       const int dir = stage == ST_BSCAN ? 1 : (both ? -1 : 0);
       const dim3 grid(grid_of(L, w.total, 0), both ? 2 : 1);
-      if constexpr (F16) {
-        // the forward pass leaves the chunk totals only; with them k_wscan_f16
-        // needs no stored products, so a recompute sweep has no forward pass
-        if (stage == ST_SCAN && !rg.recompute) {
-          if (L.dyn) hipLaunchKernelGGL((k_scan_local<T, D, COps, true>), grid, dim3(NT), 0, st, w, 2, (T)kF16Inv);
-          else hipLaunchKernelGGL((k_scan_local<T, D, COps, false>), grid, dim3(NT), 0, st, w, 2, (T)kF16Inv);
-        } else {
-          if (L.dyn) hipLaunchKernelGGL((k_wscan_f16<D, true>), grid, dim3(NT), 0, st, w);
-          else hipLaunchKernelGGL((k_wscan_f16<D, false>), grid, dim3(NT), 0, st, w);
-        }
-      } else {
-        if (L.dyn) hipLaunchKernelGGL((k_scan_local<T, D, Ops, true>), grid, dim3(NT), 0, st, w, dir, (T)1);
-        else hipLaunchKernelGGL((k_scan_local<T, D, Ops, false>), grid, dim3(NT), 0, st, w, dir, (T)1);
-      }
-      if constexpr (sizeof(T) == 4) {
-        if (stage == ST_SCAN && !rg.recompute) {
-          if (L.dyn) hipLaunchKernelGGL((k_reun<D, true>), dim3(grid.x), dim3(NT), 0, st, w);
-          else hipLaunchKernelGGL((k_reun<D, false>), dim3(grid.x), dim3(NT), 0, st, w);
-        }
-      }
-      }
-      break;
-    }
-    case ST_CARRY: {
-      int CG, PG;
-      carry_groups(L.uniformP, CG, PG);
-      Work wg = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * PG, nullptr, Range{0, 0, 0, PG, 0}, nullptr};
-      hipLaunchKernelGGL((k_carry_grp<T, D, COps>), dim3(grid_of(L, wg.total, 0), dirs), dim3(NT), 0, st, wg);
-      Work w = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob, nullptr, all, nullptr};
-      hipLaunchKernelGGL((k_carry_top<T, D, COps>), dim3(grid_of(L, L.nprob, 0), dirs), dim3(NT), 0, st, w);
+      hipLaunchKernelGGL((k_scan_local<T, D, Std, false>), grid, dim3(NT), 0, st, w, dir);
       break;
     }
     case ST_MC: {
-      Work w = L.dyn ? dyn : chunk_work(L, all);
-      hipLaunchKernelGGL((k_mc<T, D, COps>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
+      Work w = chunk_work(L, all);
+      hipLaunchKernelGGL((k_mc<T, D, Std>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
       break;
     }
     case ST_ADJ: {
-      Work w = L.dyn ? dyn : slice_work(L, rg);
+      Work w = slice_work(L, rg);
       const dim3 grid(grid_of(L, w.total, 0));
-      if constexpr (F16) {
-        if (L.dyn) hipLaunchKernelGGL((k_adjoint_f16<D, true>), grid, dim3(NT), 0, st, w);
-        else hipLaunchKernelGGL((k_adjoint_f16<D, false>), grid, dim3(NT), 0, st, w);
-      } else if constexpr (kSampleLast<T, D, Ops>) {
-        if (L.dyn) {
-          hipLaunchKernelGGL((k_adjoint<T, D, Ops, true, 2>), grid, dim3(NT), 0, st, w);
-          hipLaunchKernelGGL((k_adjoint<T, D, Ops, true, 1>), grid, dim3(NT), 0, st, w);
-        } else {
-          hipLaunchKernelGGL((k_adjoint<T, D, Ops, false, 2>), grid, dim3(NT), 0, st, w);
-          hipLaunchKernelGGL((k_adjoint<T, D, Ops, false, 1>), grid, dim3(NT), 0, st, w);
-        }
+      if constexpr (kSampleLast<T, D, Ops>) {
+        hipLaunchKernelGGL((k_adjoint<T, D, Ops, false, 2>), grid, dim3(NT), 0, st, w);
+        hipLaunchKernelGGL((k_adjoint<T, D, Ops, false, 1>), grid, dim3(NT), 0, st, w);
       } else {
-        if (L.dyn) hipLaunchKernelGGL((k_adjoint<T, D, Ops, true>), grid, dim3(NT), 0, st, w);
-        else hipLaunchKernelGGL((k_adjoint<T, D, Ops, false>), grid, dim3(NT), 0, st, w);
+        hipLaunchKernelGGL((k_adjoint<T, D, Ops, false>), grid, dim3(NT), 0, st, w);
       }
       break;
     }
   }
+}
+
+// Preparation and carry at D <= 64, the same for both paths.
+template <typename T, int D>
+static void stage_common(int stage, const Launch& L, const Range& rg) {
+  constexpr int NT = Mat<T, D>::NT;
+  hipStream_t st = L.stream;
+  const int dirs = (L.flags & RUN_BWD) ? 2 : 1;
+  const Range all = {0, L.uniformN, 0, L.uniformP, rg.kbase};
+  const Work dyn = L.dyn ? Work{L.descs, 0, 0, nullptr, Range{0, 0, 0, 0, 0}, L.dyn} : Work{};
+  if (stage == ST_PREP) {
+    Work w = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * (L.max_m + 2), nullptr,
+                                Range{0, L.max_m + 2, 0, 0, 0}, nullptr};
+    hipLaunchKernelGGL((k_prep<T, D>), dim3(grid_of(L, w.total, 0)), dim3(256), 0, st, w);
+  } else {  // ST_CARRY
+    int CG, PG;
+    carry_groups(L.uniformP, CG, PG);
+    Work wg = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * PG, nullptr, Range{0, 0, 0, PG, 0}, nullptr};
+    hipLaunchKernelGGL((k_carry_grp<T, D, StdOps<T, D>>), dim3(grid_of(L, wg.total, 0), dirs), dim3(NT), 0, st, wg);
+    Work w = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob, nullptr, all, nullptr};
+    hipLaunchKernelGGL((k_carry_top<T, D, StdOps<T, D>>), dim3(grid_of(L, L.nprob, 0), dirs), dim3(NT), 0, st, w);
+  }
+}
+
+// The Hermitian path at D <= 64 (segments; Ops: the policy of the products
+// whose errors stay local).
+template <typename T, int D, typename Ops>
+static void stage_seg(int stage, const Launch& L, const Range& rg, double ur) {
+  constexpr int NT = Mat<T, D>::NT;
+  hipStream_t st = L.stream;
+  const int grad = (L.flags & RUN_GRAD) ? 1 : 0;
+  const Range all = {0, L.uniformN, 0, L.uniformP, rg.kbase};
+  const Work dyn = L.dyn ? Work{L.descs, 0, 0, nullptr, Range{0, 0, 0, 0, 0}, L.dyn} : Work{};
+  const Work segs = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * rg.c_n * seg_count(D, L.chunk), nullptr, rg, nullptr};
+  switch (stage) {
+    case ST_PLAN: {
+      Work w = L.dyn ? dyn : slice_work(L, all);
+      const int comm = (L.flags & RUN_STATE) ? 0 : 4;
+      hipLaunchKernelGGL(k_plan, dim3(L.dyn ? L.dyn_grid : (w.total + 255) / 256), dim3(256), 0, st, w, ur,
+                         grad | comm);
+      break;
+    }
+    case ST_EXPM: {
+      const dim3 grid(grid_of(L, segs.total, 0));
+      if (L.dyn) hipLaunchKernelGGL((k_seg_fwd<T, D, Ops, true>), grid, dim3(NT), 0, st, segs);
+      else hipLaunchKernelGGL((k_seg_fwd<T, D, Ops, false>), grid, dim3(NT), 0, st, segs);
+      break;
+    }
+    case ST_SCAN: {
+      Work w = L.dyn ? dyn : chunk_work(L, rg);
+      const dim3 grid(grid_of(L, w.total, 0));
+      if (L.dyn) hipLaunchKernelGGL((k_seg_join<T, D, true>), grid, dim3(NT), 0, st, w);
+      else hipLaunchKernelGGL((k_seg_join<T, D, false>), grid, dim3(NT), 0, st, w);
+      if constexpr (sizeof(T) == 4) {
+        if (!rg.recompute) {
+          if (L.dyn) hipLaunchKernelGGL((k_reun<D, true>), grid, dim3(NT), 0, st, w);
+          else hipLaunchKernelGGL((k_reun<D, false>), grid, dim3(NT), 0, st, w);
+        }
+      }
+      break;
+    }
+    case ST_MC: {
+      Work w = L.dyn ? dyn : chunk_work(L, all);
+      hipLaunchKernelGGL((k_seg_y<T, D>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
+      break;
+    }
+    case ST_ADJ: {
+      const dim3 grid(grid_of(L, segs.total, 0), (L.flags & RUN_RAWDG) ? 2 : 1);
+      if (L.dyn) hipLaunchKernelGGL((k_seg_grad<T, D, Ops, true>), grid, dim3(NT), 0, st, segs);
+      else hipLaunchKernelGGL((k_seg_grad<T, D, Ops, false>), grid, dim3(NT), 0, st, segs);
+      const dim3 sq(L.dyn ? 256 : std::max(1, std::min(segs.total, 256)), grid.y);
+      hipLaunchKernelGGL((k_seg_grad_sq<T, D, Ops>), sq, dim3(NT), 0, st, segs);
+      break;
+    }
+  }
+}
+
+// One stage at D <= 64: SOps for Hermitian Hamiltonians, GOps for the adjoint
+// of the block form (general generators).
+template <typename T, int D, typename SOps, typename GOps>
+static void stage_le64(int stage, const Launch& L, const Range& rg, double ur) {
+  // The complex dg/du needs the series of two Hermitian parts: 2 m products,
+  // which pays on the FP16 matrix cores only (FP64, m = 10: 20 against the
+  // block form's 13; 256 problems of d = 16: 4.17 ms against 2.54).
+  constexpr bool F16 = !std::is_same<SOps, StdOps<T, D>>::value;
+  const bool block = (L.flags & RUN_GENERAL) || (!F16 && (L.flags & RUN_RAWDG));
+  if (stage == ST_PREP || stage == ST_CARRY) stage_common<T, D>(stage, L, rg);
+  else if (block) stage_small<T, D, GOps>(stage, L, rg, ur);
+  else stage_seg<T, D, SOps>(stage, L, rg, ur);
 }
 
 template <typename T>
@@ -3063,42 +3458,29 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
   bool ok = true;
   if (precision == 0) {
     switch (D) {
-      case 16: stage_small<double, 16, StdOps<double, 16>>(stage, L, rg, ur64); break;
-      case 32: stage_small<double, 32, StdOps<double, 32>>(stage, L, rg, ur64); break;
-      case 64: stage_small<double, 64, StdOps<double, 64>>(stage, L, rg, ur64); break;
+      case 16: stage_le64<double, 16, StdOps<double, 16>, StdOps<double, 16>>(stage, L, rg, ur64); break;
+      case 32: stage_le64<double, 32, StdOps<double, 32>, StdOps<double, 32>>(stage, L, rg, ur64); break;
+      case 64: stage_le64<double, 64, StdOps<double, 64>, StdOps<double, 64>>(stage, L, rg, ur64); break;
       case 128: stage_128<double>(stage, L, rg, ur64); break;
       default: ok = false;
     }
   } else if (precision == 1) {
     switch (D) {
-      case 16: stage_small<float, 16, StdOps<float, 16>>(stage, L, rg, ur32); break;
-      case 32:
-        if (L.flags & RUN_GENERAL) stage_small<float, 32, StdOps<float, 32>>(stage, L, rg, ur32);
-        else stage_small<float, 32, F16Ops<32>>(stage, L, rg, ur32);
-        break;
-      case 64:
-        if (L.flags & RUN_GENERAL) stage_small<float, 64, StdOps<float, 64>>(stage, L, rg, ur32);
-        else stage_small<float, 64, F16Ops<64>>(stage, L, rg, ur32);
-        break;
+      case 16: stage_le64<float, 16, F16Ops<16>, StdOps<float, 16>>(stage, L, rg, ur32); break;
+      case 32: stage_le64<float, 32, F16Ops<32>, StdOps<float, 32>>(stage, L, rg, ur32); break;
+      case 64: stage_le64<float, 64, F16Ops<64>, StdOps<float, 64>>(stage, L, rg, ur32); break;
       case 128: stage_128<float>(stage, L, rg, ur32); break;
       default: ok = false;
     }
   } else if (precision == 2) {
-    // split-BF16 products in the adjoint (the Frechet series and its trace
-    // contractions, the dominant kernel); the exponentials, scans, carries and
-    // chunk products stay FP32.  Split products in the forward chain as well
-    // leave an absolute error in Tr(V^dag X_N) several times larger, which
-    // the gradient of a member with a small |g| cannot absorb.
-    const bool adj = stage == ST_ADJ;
+    // general generators: split-BF16 products in the adjoint (the Frechet
+    // series and its trace contractions, the dominant kernel); the exponentials,
+    // scans, carries and chunk products stay FP32, whose errors reach
+    // Tr(V^dag X_N).  Hermitian Hamiltonians: the FP32 precision's kernels,
+    // whose split-FP16 products are as cheap and keep six bits more.
     switch (D) {
-      case 32:
-        if (adj) stage_small<float, 32, Bf3Ops<32>>(stage, L, rg, ur32);
-        else stage_small<float, 32, StdOps<float, 32>>(stage, L, rg, ur32);
-        break;
-      case 64:
-        if (adj) stage_small<float, 64, Bf3Ops<64>>(stage, L, rg, ur32);
-        else stage_small<float, 64, StdOps<float, 64>>(stage, L, rg, ur32);
-        break;
+      case 32: stage_le64<float, 32, F16Ops<32>, Bf3Ops<32>>(stage, L, rg, ur32); break;
+      case 64: stage_le64<float, 64, F16Ops<64>, Bf3Ops<64>>(stage, L, rg, ur32); break;
       default: ok = false;
     }
   } else {

@@ -12,11 +12,15 @@
 //    so the remainder after degree qb is at most
 //    |E| r^qb/qb! * 1/(1 - r/(qb+1)); qb (>= 2) is the least degree for which
 //    the factor of |E| is at most ur.
+//  * commutator series sum_n ad_X^n / n! and sum_n ad_X^n / (n + 1)! (Hermitian
+//    path at d <= 64): |ad_X| <= 2 r, so the exponential's rule at 2 r bounds
+//    both remainders; m is that degree.
 // Among s in [s0, s0 + 6], s0 = least s >= 0 with r <= 1, the value that
 // minimises the number of complex d x d products of the path is taken:
 //    exp:       (q - 1) + s    (Horner; expm_products(q) + s where the expm
 //                                 runs Paterson-Stockmeyer: FP32 at D = 128)
-//    gradient:  + frechet_products(qb) + 3 s   (block polynomial, squarings)
+//    gradient:  + frechet_products(qb) + 3 s   (block polynomial, squarings),
+//               or plan_cost's count for the commutator series
 // (where the adjoint reuses the expm's X^2 it saves one product for every s
 // alike, so the choice does not depend on that).
 #pragma once
@@ -27,6 +31,7 @@ namespace qoc {
 
 struct SlicePlan {
   int s, q, qb;
+  int m;  // commutator series: degree
 };
 
 #if defined(__HIPCC__)
@@ -35,12 +40,18 @@ struct SlicePlan {
 #define QOC_HD
 #endif
 
+// 1 / n as a literal of the unrolled loops below (no divisions: three of these
+// searches per candidate s and slice).
+QOC_HD constexpr double plan_inv(int n) { return 1.0 / n; }
+
 QOC_HD inline int taylor_degree(double r, double ur) {
   int q = 1;
   double t = r * r * 0.5;  // r^(q+1)/(q+1)!
-  while (q < 30 && t / (1.0 - r / (q + 2)) > ur) {
-    ++q;
-    t *= r / (q + 1);
+#pragma unroll
+  for (int n = 1; n < 30; ++n) {
+    if (!(t > ur * (1.0 - r * plan_inv(n + 2)))) break;
+    q = n + 1;
+    t *= r * plan_inv(n + 2);
   }
   return q;
 }
@@ -48,9 +59,11 @@ QOC_HD inline int taylor_degree(double r, double ur) {
 QOC_HD inline int frechet_degree(double r, double ur) {
   int qb = 2;
   double t = r * r * 0.5;  // r^qb/qb!
-  while (qb < 31 && t / (1.0 - r / (qb + 1)) > ur) {
-    ++qb;
-    t *= r / qb;
+#pragma unroll
+  for (int n = 2; n < 31; ++n) {
+    if (!(t > ur * (1.0 - r * plan_inv(n + 1)))) break;
+    qb = n + 1;
+    t *= r * plan_inv(n + 1);
   }
   return qb;
 }
@@ -67,6 +80,11 @@ QOC_HD inline double inv_factorial(int n) {
 // the last step (q >= 3); X + X^2 / 2 at q = 2.
 QOC_HD inline int expm_products(int q) { return q < 2 ? 0 : (q == 2 ? 1 : 2 + (q - 3) / 2); }
 
+// Complex d x d products of a Taylor polynomial of degree at least q in
+// k_seg_fwd's evaluation: Horner, the degree-4 and degree-8 forms,
+// Paterson-Stockmeyer with X^3 as the step.
+QOC_HD inline int taylor_products(int q) { return q <= 3 ? q - 1 : (q == 4 ? 2 : (q <= 8 ? 3 : 2 + (q - 1) / 3)); }
+
 // Complex d x d products of the degree-qb Taylor polynomial of the block
 // [[X, E], [0, X]] by Paterson-Stockmeyer with the block's square as the
 // step: three for the square, three per Horner step in the square that has a
@@ -74,32 +92,44 @@ QOC_HD inline int expm_products(int q) { return q < 2 ? 0 : (q == 2 ? 1 : 2 + (q
 // right block (the top left one is counted with the squarings).
 QOC_HD inline int frechet_products(int qb) { return 5 + 3 * (qb > 3 ? (qb - 3) / 2 : 0); }
 
-QOC_HD inline int plan_cost(int s, int q, int qb, bool grad, bool ps_expm) {
-  int cost = (ps_expm ? expm_products(q) : q - 1) + s;
-  if (grad) cost += frechet_products(qb) + 3 * s;
+// comm: the gradient's m products of the commutator series and, for s > 0,
+// the exponential again, s doublings and the step of Y.
+QOC_HD inline int plan_cost(int s, int q, int qb, int m, bool grad, bool ps_expm, bool comm) {
+  int cost = (comm ? taylor_products(q) : ps_expm ? expm_products(q) : q - 1) + s;
+  if (grad && comm) cost += m + (s > 0 ? taylor_products(q) + 2 + 3 * s : 0);
+  else if (grad) cost += frechet_products(qb) + 3 * s;
   return cost;
 }
 
-QOC_HD inline SlicePlan choose_plan(double theta, double ur, bool grad, bool ps_expm = false) {
+QOC_HD inline SlicePlan choose_plan(double theta, double ur, bool grad, bool ps_expm = false, bool comm = false) {
   int s0 = 0;
   while (ldexp(theta, -s0) > 1.0 && s0 < 60) ++s0;
-  SlicePlan best = {s0, 1, 2};
+  SlicePlan best = {s0, 1, 2, 1};
   int best_cost = 1 << 30;
   for (int s = s0; s <= s0 + 6; ++s) {
     double r = ldexp(theta, -s);
     int q = taylor_degree(r, ur);
     int qb = frechet_degree(r, ur);
-    int c = plan_cost(s, q, qb, grad, ps_expm);
+    int m = comm ? taylor_degree(2 * r, ur) : 0;
+    int c = plan_cost(s, q, qb, m, grad, ps_expm, comm);
+    // the degrees fall ever more slowly with s while each s adds the same:
+    // past the minimum the count only grows
+    if (c > best_cost) break;
     if (c < best_cost) {
       best_cost = c;
       best.s = s;
       best.q = q;
       best.qb = qb;
+      best.m = m;
     }
   }
   return best;
 }
 
-QOC_HD inline int pack_plan(SlicePlan p) { return p.s | (p.q << 8) | (p.qb << 16); }
+// s, q, qb in a byte each (bits 24 and 25 are the kernels' flags), m on top.
+QOC_HD inline int pack_plan(SlicePlan p) {
+  return (int)((unsigned)p.s | ((unsigned)p.q << 8) | ((unsigned)p.qb << 16) | ((unsigned)p.m << 26));
+}
+QOC_HD inline int plan_order(int sq) { return (int)((unsigned)sq >> 26); }
 
 }  // namespace qoc

@@ -741,6 +741,8 @@ int run_state_dev(int B, int d, int m, int N, const void* H0, const void* Hc, co
     P.g = small;
     P.F = F ? static_cast<double*>(F) + b : small + 2;
     P.diag = small + 4;
+    P.vscale = small + 8;
+    P.squared = reinterpret_cast<int*>(small + 9);
     P.reun_tol = -1.0;
     P.grad = grad ? static_cast<double*>(grad) + (size_t)m * N * b : nullptr;
     P.XN = psiN ? static_cast<double*>(psiN) + 2 * (size_t)d * b : nullptr;
@@ -762,7 +764,7 @@ int run_state_dev(int B, int d, int m, int N, const void* H0, const void* Hc, co
   L.total_slices = B * N;
   L.total_chunks = B;
   L.max_m = m;
-  L.flags = flags;
+  L.flags = flags | qoc::RUN_STATE;
   L.stream = st;
   const qoc::Range all = {0, N, 0, 1, 0, 0};
   e = qoc::launch_stage(opt.precision, Lo.D, qoc::ST_PREP, L, all);
