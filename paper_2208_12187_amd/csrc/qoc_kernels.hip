@@ -2250,6 +2250,11 @@ struct K128 {
   static constexpr int WPH = NW / HALVES;           // panels per staged part
 };
 
+// The three-product form in the FP32 expm and adjoint products at D = 128
+// (their registers allow it; the FP64 kernels already spill).
+template <typename T>
+constexpr bool k128Gauss = sizeof(T) == 4;
+
 // acc <- acc + a * (this wavefront's panel of the PF matrix M), one row block
 // at a time so that no second panel is held in registers.
 template <typename T>
@@ -2393,6 +2398,135 @@ __device__ __forceinline__ void gemm128(Panel<T, 128>& acc, T* lds, const T* M, 
   }
 }
 
+// The same product on the FP16 matrix cores (qoc_f16.hpp; Hermitian path,
+// FP32): M is staged whole as split planes, with the factor c = 4096, and the K
+// steps' values of B are split as they arrive.  How the left factor is staged:
+// as it is, as its conjugate transpose, or, since a conjugate transpose takes
+// one 8-byte write where the matrix takes four 2-byte ones, as -M^dag and M^dag
+// for anti-Hermitian and Hermitian M.
+enum Left128 : int { LEFT_PLAIN = 0, LEFT_CT, LEFT_ANTI, LEFT_HERM };
+
+struct H128 {
+  static constexpr int SB = 136;          // row stride in FP16 elements
+  static constexpr int PLANE = 128 * SB;
+  static constexpr int BYTES = 4 * PLANE * 2;
+  static constexpr float C = 4096.0f;
+};
+
+template <int MODE>
+__device__ __forceinline__ void stage128h(void* lds, const float* M, const Lane& L) {
+  constexpr int NB = 4;
+  unsigned short* p = static_cast<unsigned short*>(lds);
+  constexpr int PL = H128::PLANE, SB = H128::SB;
+#pragma unroll
+  for (int b0 = 0; b0 < 8; b0 += NB) {
+    f4 re[NB], im[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) pf_rb_load<float>(re[i], im[i], M, L.w, b0 + i, L.lane);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int rb = b0 + i;
+      u2v rh, rl, ih, il;
+#pragma unroll
+      for (int r = 0; r < 4; r += 2) {
+        unsigned h, l;
+        f16_split2(H128::C * re[i][r], H128::C * re[i][r + 1], h, l);
+        rh[r / 2] = MODE == LEFT_ANTI ? h ^ 0x80008000u : h;
+        rl[r / 2] = MODE == LEFT_ANTI ? l ^ 0x80008000u : l;
+        f16_split2(H128::C * im[i][r], H128::C * im[i][r + 1], h, l);
+        ih[r / 2] = (MODE == LEFT_CT || MODE == LEFT_HERM) ? h ^ 0x80008000u : h;
+        il[r / 2] = (MODE == LEFT_CT || MODE == LEFT_HERM) ? l ^ 0x80008000u : l;
+      }
+      if constexpr (MODE != LEFT_PLAIN) {
+        const int off = (16 * L.w + L.c16) * SB + Bf3Ops<32>::phys(16 * rb + 4 * L.g);
+        *reinterpret_cast<u2v*>(p + off) = rh;
+        *reinterpret_cast<u2v*>(p + PL + off) = rl;
+        *reinterpret_cast<u2v*>(p + 2 * PL + off) = ih;
+        *reinterpret_cast<u2v*>(p + 3 * PL + off) = il;
+      } else {
+        const int pc = Bf3Ops<32>::phys(16 * L.w + L.c16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int off = (16 * rb + 4 * L.g + r) * SB + pc, sh = 16 * (r & 1);
+          p[off] = (unsigned short)(rh[r / 2] >> sh);
+          p[PL + off] = (unsigned short)(rl[r / 2] >> sh);
+          p[2 * PL + off] = (unsigned short)(ih[r / 2] >> sh);
+          p[3 * PL + off] = (unsigned short)(il[r / 2] >> sh);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+template <int MODE>
+__device__ __forceinline__ void gemm128h(Panel<float, 128>& acc, void* lds, const float* M, const float* B,
+                                         const Lane& L, bool zero_acc, bool stage) {
+  using O = F16Ops<32>;
+  constexpr int PL = H128::PLANE, SB = H128::SB;
+  if (zero_acc) panel_zero(acc);
+  else panel_scale(acc, H128::C * H128::C);
+  __syncthreads();
+  if (stage) {
+    stage128h<MODE>(lds, M, L);
+    __syncthreads();
+  }
+  const unsigned short* p = static_cast<const unsigned short*>(lds);
+  const int base = L.c16 * SB + 8 * L.g;
+  f4 br[2], bi[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) pf_rb_load<float>(br[i], bi[i], B, L.w, i, L.lane);
+  h8v a[2][4];
+#pragma unroll
+  for (int pl = 0; pl < 4; ++pl) a[0][pl] = *reinterpret_cast<const h8v*>(p + pl * PL + base);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    u4v rh, rl, ih, il;
+#pragma unroll
+    for (int jp = 0; jp < 4; ++jp) {
+      const int i = jp >> 1, r = 2 * (jp & 1);
+      unsigned h, l;
+      f16_split2(H128::C * br[i][r], H128::C * br[i][r + 1], h, l);
+      rh[jp] = h;
+      rl[jp] = l;
+      f16_split2(H128::C * bi[i][r], H128::C * bi[i][r + 1], h, l);
+      ih[jp] = h;
+      il[jp] = l;
+    }
+    const h8v brh = __builtin_bit_cast(h8v, rh), brl = __builtin_bit_cast(h8v, rl);
+    const h8v bih = __builtin_bit_cast(h8v, ih), bil = __builtin_bit_cast(h8v, il);
+    const h8v nih = O::neg(bih), nil = O::neg(bil);
+    if (t < 3) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) pf_rb_load<float>(br[i], bi[i], B, L.w, 2 * (t + 1) + i, L.lane);
+    }
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) {
+      const int st = 8 * t + mb, cur = st & 1;
+      if (st + 1 < 32) {
+        const int off = base + 16 * ((st + 1) % 8) * SB + 32 * ((st + 1) / 8);
+#pragma unroll
+        for (int pl = 0; pl < 4; ++pl) a[cur ^ 1][pl] = *reinterpret_cast<const h8v*>(p + pl * PL + off);
+      }
+      O::step<false>(acc.re[mb], acc.im[mb], a[cur], brh, brl, bih, bil, nih, nil);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  panel_scale(acc, 1.0f / (H128::C * H128::C));
+}
+
+// acc (+)= M B by gemm128h (H) or gemm128.
+template <typename T, bool H, int MODE>
+__device__ __forceinline__ void mul128(Panel<T, 128>& acc, void* lds, const T* M, const T* B, const Lane& L,
+                                       bool zero_acc, bool stage = true) {
+  if constexpr (H) gemm128h<MODE>(acc, lds, M, B, L, zero_acc, stage);
+  else gemm128<T, MODE == LEFT_CT, k128Gauss<T>>(acc, static_cast<T*>(lds), M, B, L, zero_acc, stage);
+}
+
+template <typename T, bool H>
+constexpr int kLds128 = H ? H128::BYTES : K128<T>::LDS_ELEMS * (int)sizeof(T);
+
 // out = M^dag (both PF), through LDS part by part.
 template <typename T>
 __device__ __forceinline__ void transpose128(T* out, T* lds, const T* M, const Lane& L) {
@@ -2444,7 +2578,8 @@ __device__ __forceinline__ void assemble128(Panel<T, 128>& X, T* out, T* lds, co
   static_assert(2 * ROWS * SD <= K128<T>::LDS_ELEMS, "LDS too small");
   T* lim = lds + ROWS * SD;
   const T* H = reinterpret_cast<const T*>(P.Hint);
-  const T f = (T)(sgn * c);
+  // the factor in two numbers of type T (as in assemble_panel)
+  const T f = (T)(sgn * c), fl = (T)(sgn * c - (double)f);
 #pragma unroll
   for (int pass = 0; pass < PASSES; ++pass) {
     const int e0 = 4 * (threadIdx.x + pass * NV * NT);
@@ -2506,8 +2641,8 @@ __device__ __forceinline__ void assemble128(Panel<T, 128>& X, T* out, T* lds, co
         for (int i = 0; i < 4; ++i) {
           const int off = row * SD + ((col + i) & ~15) + Prec<T>::perm((col + i) & 15);
           const T r = lds[off], im = lim[off];
-          lds[off] = f * im;  // -i f (r + i im)
-          lim[off] = -f * r;
+          lds[off] = fma(f, im, fl * im);  // -i f (r + i im)
+          lim[off] = -fma(f, r, fl * r);
         }
       }
     } else {
@@ -2518,8 +2653,8 @@ __device__ __forceinline__ void assemble128(Panel<T, 128>& X, T* out, T* lds, co
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int off = row * SD + ((col + i) & ~15) + Prec<T>::perm((col + i) & 15);
-          lds[off] = f * hi[v][i];   // -i f (hr + i hi)
-          lim[off] = -f * hr[v][i];
+          lds[off] = fma(f, hi[v][i], fl * hi[v][i]);  // -i f (hr + i hi)
+          lim[off] = -fma(f, hr[v][i], fl * hr[v][i]);
         }
       }
     }
@@ -2681,19 +2816,15 @@ __device__ __forceinline__ void gradient_epilogue128(const ProbDesc& P, int k, c
 template <typename T>
 constexpr bool kKeepX2 = sizeof(T) == 4;
 
-// The three-product form in the FP32 expm and adjoint products at D = 128
-// (their registers allow it; the FP64 kernels already spill).
-template <typename T>
-constexpr bool k128Gauss = sizeof(T) == 4;
-
 template <typename T>
 __device__ __forceinline__ T* slot_mat(void* scratch, int i) {
   return reinterpret_cast<T*>(scratch) + ((size_t)blockIdx.x * kScratchMats + i) * K128<T>::ELEMS;
 }
 
-template <typename T>
+template <typename T, bool H>
 __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
-  __shared__ T lds[K128<T>::LDS_ELEMS];
+  __shared__ __align__(16) unsigned char ldsb[kLds128<T, H>];
+  T* lds = reinterpret_cast<T*>(ldsb);
   Lane L;
   T* SX = slot_mat<T>(scratch, 0);
   T* SR = slot_mat<T>(scratch, 1);
@@ -2720,8 +2851,8 @@ __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
     // the products it saves.)  FP64, whose kernels spill, runs Horner.
     if (kKeepX2<T> && q >= 2) {
       T* S2 = slot_mat<T>(scratch, 2);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SX, L, true);
-      if ((P.flags & RUN_GRAD) && P.x2) panel_store(pf_mat<T, 128>(P.x2, k - W.rg.kbase), acc, L);
+      mul128<T, H, LEFT_ANTI>(acc, lds, SX, SX, L, true);
+      if (!H && (P.flags & RUN_GRAD) && P.x2) panel_store(pf_mat<T, 128>(P.x2, k - W.rg.kbase), acc, L);
       if (q == 2) {
         panel_scale(acc, (T)0.5);
         panel_axpy_pf(acc, (T)1, SX, L);  // X + X2 / 2
@@ -2746,28 +2877,28 @@ __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
           panel_load(acc, SX, L);
           panel_scale(acc, (T)inv_factorial(2 * t + 3));
           panel_add_identity(acc, L, (T)inv_factorial(2 * t + 2));
-          gemm128<T, false, k128Gauss<T>>(acc, lds, S2, SR, L, false, !staged);
+          mul128<T, H, LEFT_HERM>(acc, lds, S2, SR, L, false, !staged);
           staged = true;
           panel_store(SR, acc, L);
         }
         panel_load(acc, SX, L);
-        gemm128<T, false, k128Gauss<T>>(acc, lds, S2, SR, L, false, !staged);  // X + X2 C
+        mul128<T, H, LEFT_HERM>(acc, lds, S2, SR, L, false, !staged);  // X + X2 C
       }
     } else if (q >= 2) {
       panel_scale(acc, (T)(1.0 / q));
       panel_add_identity(acc, L, (T)1);
       panel_store(SR, acc, L);
       for (int i = q - 1; i >= 2; --i) {
-        gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SR, L, true);
+        mul128<T, H, LEFT_ANTI>(acc, lds, SX, SR, L, true);
         panel_scale(acc, (T)(1.0 / i));
         panel_add_identity(acc, L, (T)1);
         panel_store(SR, acc, L);
       }
-      gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SR, L, true);
+      mul128<T, H, LEFT_ANTI>(acc, lds, SX, SR, L, true);
     }
     for (int j = 0; j < s; ++j) {
       panel_store(SR, acc, L);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, SR, SR, L, true);
+      mul128<T, H, LEFT_PLAIN>(acc, lds, SR, SR, L, true);
       panel_axpy_pf(acc, (T)2, SR, L);
     }
     panel_store(pf_mat<T, 128>(P.delta, k - W.rg.kbase), acc, L);
@@ -2869,9 +3000,12 @@ __device__ __noinline__ void reunitarise128(const ProbDesc& P, float* Ypf, float
   __syncthreads();
 }
 
-template <typename T>
+// H: the backward pass on the FP16 matrix cores; the forward one, whose errors
+// add up over the chain, is always in precision T.
+template <typename T, bool H>
 __global__ __launch_bounds__(512) void k_scan128(Work W, int dir) {
-  __shared__ T lds[K128<T>::LDS_ELEMS];
+  __shared__ __align__(16) unsigned char ldsb[kLds128<T, H>];
+  T* lds = reinterpret_cast<T*>(ldsb);
   __shared__ double red[8];
   const int bwd = dir < 0 ? (int)blockIdx.y : dir;  // dir < 0: both passes, one per blockIdx.y
   Lane L;
@@ -2900,7 +3034,8 @@ __global__ __launch_bounds__(512) void k_scan128(Work W, int dir) {
       panel_store(pf_mat<T, 128>(P.bloc, k1 - 1 - W.rg.kbase), acc, L);
       for (int k = k1 - 1; k >= k0; --k) {
         T* cur = pf_mat<T, 128>(P.bloc, k - W.rg.kbase);
-        gemm128<T, true>(acc, lds, pf_mat<T, 128>(P.delta, k - W.rg.kbase), cur, L, true);
+        if constexpr (H) gemm128h<LEFT_CT>(acc, lds, pf_mat<T, 128>(P.delta, k - W.rg.kbase), cur, L, true, true);
+        else gemm128<T, true>(acc, lds, pf_mat<T, 128>(P.delta, k - W.rg.kbase), cur, L, true);
         panel_axpy_pf(acc, (T)1, cur, L);
         if (k > k0) panel_store(pf_mat<T, 128>(P.bloc, k - 1 - W.rg.kbase), acc, L);
       }
@@ -3106,9 +3241,13 @@ __device__ __forceinline__ void sampled_gradient128(const ProbDesc& P, int k, co
 }
 
 // Same steps as k_adjoint, with the chain state in scratch (see above).
-template <typename T>
+// H: on the FP16 matrix cores, where X2 costs less to form than to read back,
+// and W is kept at its size (the block is halved at each squaring instead), so
+// that every factor stays in FP16's range whatever s.
+template <typename T, bool H>
 __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
-  __shared__ T lds[K128<T>::LDS_ELEMS];
+  __shared__ __align__(16) unsigned char ldsb[kLds128<T, H>];
+  T* lds = reinterpret_cast<T*>(ldsb);
   __shared__ double red[2 * kEpiGroup * 2 * 8];
   Lane L;
   T* S0 = slot_mat<T>(scratch, 0);
@@ -3128,14 +3267,14 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
     Panel<T, 128> acc;
     // W = bloc[k] xprev[k]^dag (bloc carries mc[c])
     transpose128<T>(S0, lds, pf_mat<T, 128>(P.xprev, k - W.rg.kbase), L);
-    gemm128<T, false, k128Gauss<T>>(acc, lds, pf_mat<T, 128>(P.bloc, k - W.rg.kbase), S0, L, true);
+    mul128<T, H, LEFT_PLAIN>(acc, lds, pf_mat<T, 128>(P.bloc, k - W.rg.kbase), S0, L, true);
     // E = W / 2^s
-    panel_scale(acc, (T)ldexp(1.0, -s));
+    if (!H) panel_scale(acc, (T)ldexp(1.0, -s));
     panel_store(SE, acc, L);
     // X = A^dag / 2^s: the expm pass's A / 2^s negated (A = -i dt H_k with H_k
     // Hermitian), or its conjugate transpose for general generators (own
     // panel; the barrier at the start of the next product publishes SX)
-    if (P.flags & RUN_GENERAL) {
+    if (!H && (P.flags & RUN_GENERAL)) {
       transpose128<T>(SX, lds, pf_mat<T, 128>(P.hk, k - W.rg.kbase), L);
     } else {
       panel_load(acc, pf_mat<T, 128>(P.hk, k - W.rg.kbase), L);
@@ -3145,12 +3284,12 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
     // The block polynomial by Paterson-Stockmeyer as in k_adjoint: M^2 =
     // [[X2, S], [0, X2]] into S0 (X2) and S1 (S), the running C = [[C1, C2],
     // [0, C1]] in SR1 and SR2.
-    if (kKeepX2<T> && q >= 2 && P.x2 && !(P.flags & RUN_GENERAL))
-      panel_load(acc, pf_mat<T, 128>(P.x2, k - W.rg.kbase), L);  // kept by the expm
-    else gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SX, L, true);
+    const bool kept = !H && kKeepX2<T> && q >= 2 && P.x2 && !(P.flags & RUN_GENERAL);
+    if (kept) panel_load(acc, pf_mat<T, 128>(P.x2, k - W.rg.kbase), L);  // by the expm
+    else mul128<T, H, LEFT_ANTI>(acc, lds, SX, SX, L, true);
     panel_store(S0, acc, L);
-    gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SE, L, true);
-    gemm128<T, false, k128Gauss<T>>(acc, lds, SE, SX, L, false);
+    mul128<T, H, LEFT_ANTI>(acc, lds, SX, SE, L, true, kept);
+    mul128<T, H, LEFT_PLAIN>(acc, lds, SE, SX, L, false);
     panel_store(S1, acc, L);
     const int top = (qb - 2) / 2;
     int t;
@@ -3188,19 +3327,19 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
       const T a = (T)inv_factorial(2 * t + 2), b = (T)inv_factorial(2 * t + 3);
       panel_load(acc, SE, L);
       panel_scale(acc, b);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, S1, SR1, L, false);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR2, L, false);
+      mul128<T, H, LEFT_PLAIN>(acc, lds, S1, SR1, L, false);
+      mul128<T, H, LEFT_HERM>(acc, lds, S0, SR2, L, false);
       panel_store(SR2, acc, L);  // b E + S C1 + X2 C2
       panel_load(acc, SX, L);
       panel_scale(acc, b);
       panel_add_identity(acc, L, a);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR1, L, false, false);
+      mul128<T, H, LEFT_HERM>(acc, lds, S0, SR1, L, false, false);
       panel_store(SR1, acc, L);  // a I + b X + X2 C1
       x2_staged = true;
     }
     if constexpr (sizeof(T) == 4) {
       if ((sqk & kPlanSampled) && P.m <= kSample128Max) {  // s = 0: only the entries the controls read
-        sampled_gradient128(P, k, L, lds, red, S0, S1, SR1, SR2, SE, x2_staged);
+        sampled_gradient128(P, k, L, lds, red, S0, S1, SR1, SR2, SE, !H && x2_staged);
         __syncthreads();
         continue;
       }
@@ -3208,25 +3347,26 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
     // Q = E + X2 C2 + S C1 and, when squaring follows, D1 = X + X2 C1 (into
     // S1 once every wavefront has staged S; Q waits in the own panel of SE).
     panel_load(acc, SE, L);
-    gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR2, L, false, !x2_staged);
-    gemm128<T, false, k128Gauss<T>>(acc, lds, S1, SR1, L, false);
+    mul128<T, H, LEFT_HERM>(acc, lds, S0, SR2, L, false, !x2_staged);
+    mul128<T, H, LEFT_PLAIN>(acc, lds, S1, SR1, L, false);
     if (s > 0) {
       panel_store(SE, acc, L);
       panel_load(acc, SX, L);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR1, L, false);
+      mul128<T, H, LEFT_HERM>(acc, lds, S0, SR1, L, false);
       panel_store(S1, acc, L);
       panel_load(acc, SE, L);
     }
     for (int j = 0; j < s; ++j) {
       panel_store(S0, acc, L);                        // Q
-      gemm128<T, false, k128Gauss<T>>(acc, lds, S1, S0, L, true);   // D1 Q
-      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, S1, L, false);  // + Q D1
-      panel_axpy_pf(acc, (T)2, S0, L);                // Q <- 2Q + D1 Q + Q D1
+      mul128<T, H, LEFT_PLAIN>(acc, lds, S1, S0, L, true);   // D1 Q
+      mul128<T, H, LEFT_PLAIN>(acc, lds, S0, S1, L, false);  // + Q D1
+      if (H) panel_scale(acc, (T)0.5);
+      panel_axpy_pf(acc, H ? (T)1 : (T)2, S0, L);     // Q <- 2Q + D1 Q + Q D1 (H: half of it)
       if (j + 1 < s) {
         // Every wavefront's staging of the old Q and D1 ended before the
         // barrier inside the last product, so own panels may be replaced.
         panel_store(S0, acc, L);
-        gemm128<T, false, k128Gauss<T>>(acc, lds, S1, S1, L, true);
+        mul128<T, H, LEFT_PLAIN>(acc, lds, S1, S1, L, true);
         panel_axpy_pf(acc, (T)2, S1, L);              // D1 <- 2 D1 + D1^2
         panel_store(S1, acc, L);
         panel_load(acc, S0, L);
@@ -3394,7 +3534,8 @@ static void stage_le64(int stage, const Launch& L, const Range& rg, double ur) {
   else stage_seg<T, D, SOps>(stage, L, rg, ur);
 }
 
-template <typename T>
+// H: Hermitian Hamiltonians in FP32, on the FP16 matrix cores.
+template <typename T, bool H>
 static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
   hipStream_t st = L.stream;
   const int dirs = (L.flags & RUN_BWD) ? 2 : 1;
@@ -3417,7 +3558,7 @@ static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
     }
     case ST_EXPM: {
       Work w = L.dyn ? dyn : slice_work(L, rg);
-      hipLaunchKernelGGL(k_expm128<T>, dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
+      hipLaunchKernelGGL((k_expm128<T, H>), dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
       break;
     }
     case ST_SCAN:
@@ -3425,7 +3566,7 @@ static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
       Work w = L.dyn ? dyn : chunk_work(L, rg);
       const bool both = stage == ST_SCAN && rg.recompute && !L.dyn;
       const int dir = stage == ST_BSCAN ? 1 : (both ? -1 : 0);
-      hipLaunchKernelGGL(k_scan128<T>, dim3(grid_of(L, w.total, 0), both ? 2 : 1), dim3(512), 0, st, w, dir);
+      hipLaunchKernelGGL((k_scan128<T, H>), dim3(grid_of(L, w.total, 0), both ? 2 : 1), dim3(512), 0, st, w, dir);
       break;
     }
     case ST_CARRY: {
@@ -3446,7 +3587,7 @@ static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
     }
     case ST_ADJ: {
       Work w = L.dyn ? dyn : slice_work(L, rg);
-      hipLaunchKernelGGL(k_adjoint128<T>, dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
+      hipLaunchKernelGGL((k_adjoint128<T, H>), dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
       break;
     }
   }
@@ -3461,7 +3602,7 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
       case 16: stage_le64<double, 16, StdOps<double, 16>, StdOps<double, 16>>(stage, L, rg, ur64); break;
       case 32: stage_le64<double, 32, StdOps<double, 32>, StdOps<double, 32>>(stage, L, rg, ur64); break;
       case 64: stage_le64<double, 64, StdOps<double, 64>, StdOps<double, 64>>(stage, L, rg, ur64); break;
-      case 128: stage_128<double>(stage, L, rg, ur64); break;
+      case 128: stage_128<double, false>(stage, L, rg, ur64); break;
       default: ok = false;
     }
   } else if (precision == 1) {
@@ -3469,7 +3610,10 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
       case 16: stage_le64<float, 16, F16Ops<16>, StdOps<float, 16>>(stage, L, rg, ur32); break;
       case 32: stage_le64<float, 32, F16Ops<32>, StdOps<float, 32>>(stage, L, rg, ur32); break;
       case 64: stage_le64<float, 64, F16Ops<64>, StdOps<float, 64>>(stage, L, rg, ur32); break;
-      case 128: stage_128<float>(stage, L, rg, ur32); break;
+      case 128:
+        if (L.flags & RUN_GENERAL) stage_128<float, false>(stage, L, rg, ur32);
+        else stage_128<float, true>(stage, L, rg, ur32);
+        break;
       default: ok = false;
     }
   } else if (precision == 2) {
