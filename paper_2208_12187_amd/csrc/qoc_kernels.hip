@@ -306,7 +306,7 @@ __global__ __launch_bounds__(256) void k_plan(Work W, double ur, int flags) {
 #pragma unroll 4
     for (int j = 0; j < P.m; ++j) th = fma(fabs(gp(P.u)[(size_t)j * P.N + k]), gp(P.norms)[j + 1], th);
     th *= P.dt;
-    const SlicePlan pl = choose_plan(th, ur, (flags & 1) != 0, (flags & 2) != 0, (flags & 4) != 0);
+    const SlicePlan pl = choose_plan(th, ur, flags);
     const int cf = controls_flags(P);
     if (pl.s > 0) atomicOr(P.squared, 1);
     P.sq[k] = pack_plan(pl) | (pl.s == 0 && (cf & 2) ? kPlanSampled : 0) | ((cf & 1) ? kPlanMono : 0);
@@ -1831,8 +1831,8 @@ __device__ __forceinline__ void taylor_delta(Panel<T, D>& R, const Panel<T, D>& 
   }
 }
 
-// The totals U_{kb-1} ... U_{ka} of the segments (into xprev at the segment's
-// first slice).  The exponentials' products run on Ops; the chain's, whose
+// The totals U_{kb-1} ... U_{ka} of the segments less I (into xprev at the
+// segment's first slice).  The exponentials' products run on Ops; the chain's, whose
 // errors add up over the N slices, always in precision T.
 template <typename T, int D, typename Ops, bool PERSIST>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_seg_fwd(Work W) {
@@ -1868,6 +1868,7 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
           panel_fma(S, (T)1, X);  // S <- S + Delta S
         }
       }
+      panel_add_identity(S, L, (T)-1);
       panel_store(pf_mat<T, D>(P.xprev, g.ka - W.rg.kbase), S, L);
     }
     if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
@@ -1891,6 +1892,7 @@ __global__ __launch_bounds__(4 * D) void k_seg_join(Work W) {
     Panel<T, D> S, nxt, acc;
     int k = c * P.L;
     panel_load(S, pf_mat<T, D>(P.xprev, k - W.rg.kbase), L);
+    panel_add_identity(S, L, (T)1);
     k += h;
     if (k < k1) panel_load(nxt, pf_mat<T, D>(P.xprev, k - W.rg.kbase), L);
     for (int i = 0; k < k1; ++i) {
@@ -1901,10 +1903,12 @@ __global__ __launch_bounds__(4 * D) void k_seg_join(Work W) {
       k += h;
       if (k < k1) panel_load(nxt, pf_mat<T, D>(P.xprev, k - W.rg.kbase), L);
       __syncthreads();
-      // four real products: the three-product form's larger error in these
-      // full-size factors doubled the gradient's
+      // S <- S + (T - I) S, in four real products: the three-product form's
+      // larger error in these factors doubled the gradient's, and T S rounds
+      // every sum at the size of S (at d = 128 a chunk's residual |Y^dag Y - I|
+      // was 4.5e-6 after two of them instead of 1.7e-6)
       Ops::gemm(acc, lds[i & 1], S, L, true);
-      S = acc;
+      panel_fma(S, (T)1, acc);
     }
     if (!W.rg.recompute) panel_store(pf_mat<T, D>(P.tf, c), S, L);  // (k_reun follows in FP32)
     if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
@@ -2398,135 +2402,6 @@ __device__ __forceinline__ void gemm128(Panel<T, 128>& acc, T* lds, const T* M, 
   }
 }
 
-// The same product on the FP16 matrix cores (qoc_f16.hpp; Hermitian path,
-// FP32): M is staged whole as split planes, with the factor c = 4096, and the K
-// steps' values of B are split as they arrive.  How the left factor is staged:
-// as it is, as its conjugate transpose, or, since a conjugate transpose takes
-// one 8-byte write where the matrix takes four 2-byte ones, as -M^dag and M^dag
-// for anti-Hermitian and Hermitian M.
-enum Left128 : int { LEFT_PLAIN = 0, LEFT_CT, LEFT_ANTI, LEFT_HERM };
-
-struct H128 {
-  static constexpr int SB = 136;          // row stride in FP16 elements
-  static constexpr int PLANE = 128 * SB;
-  static constexpr int BYTES = 4 * PLANE * 2;
-  static constexpr float C = 4096.0f;
-};
-
-template <int MODE>
-__device__ __forceinline__ void stage128h(void* lds, const float* M, const Lane& L) {
-  constexpr int NB = 4;
-  unsigned short* p = static_cast<unsigned short*>(lds);
-  constexpr int PL = H128::PLANE, SB = H128::SB;
-#pragma unroll
-  for (int b0 = 0; b0 < 8; b0 += NB) {
-    f4 re[NB], im[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) pf_rb_load<float>(re[i], im[i], M, L.w, b0 + i, L.lane);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int rb = b0 + i;
-      u2v rh, rl, ih, il;
-#pragma unroll
-      for (int r = 0; r < 4; r += 2) {
-        unsigned h, l;
-        f16_split2(H128::C * re[i][r], H128::C * re[i][r + 1], h, l);
-        rh[r / 2] = MODE == LEFT_ANTI ? h ^ 0x80008000u : h;
-        rl[r / 2] = MODE == LEFT_ANTI ? l ^ 0x80008000u : l;
-        f16_split2(H128::C * im[i][r], H128::C * im[i][r + 1], h, l);
-        ih[r / 2] = (MODE == LEFT_CT || MODE == LEFT_HERM) ? h ^ 0x80008000u : h;
-        il[r / 2] = (MODE == LEFT_CT || MODE == LEFT_HERM) ? l ^ 0x80008000u : l;
-      }
-      if constexpr (MODE != LEFT_PLAIN) {
-        const int off = (16 * L.w + L.c16) * SB + Bf3Ops<32>::phys(16 * rb + 4 * L.g);
-        *reinterpret_cast<u2v*>(p + off) = rh;
-        *reinterpret_cast<u2v*>(p + PL + off) = rl;
-        *reinterpret_cast<u2v*>(p + 2 * PL + off) = ih;
-        *reinterpret_cast<u2v*>(p + 3 * PL + off) = il;
-      } else {
-        const int pc = Bf3Ops<32>::phys(16 * L.w + L.c16);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int off = (16 * rb + 4 * L.g + r) * SB + pc, sh = 16 * (r & 1);
-          p[off] = (unsigned short)(rh[r / 2] >> sh);
-          p[PL + off] = (unsigned short)(rl[r / 2] >> sh);
-          p[2 * PL + off] = (unsigned short)(ih[r / 2] >> sh);
-          p[3 * PL + off] = (unsigned short)(il[r / 2] >> sh);
-        }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-template <int MODE>
-__device__ __forceinline__ void gemm128h(Panel<float, 128>& acc, void* lds, const float* M, const float* B,
-                                         const Lane& L, bool zero_acc, bool stage) {
-  using O = F16Ops<32>;
-  constexpr int PL = H128::PLANE, SB = H128::SB;
-  if (zero_acc) panel_zero(acc);
-  else panel_scale(acc, H128::C * H128::C);
-  __syncthreads();
-  if (stage) {
-    stage128h<MODE>(lds, M, L);
-    __syncthreads();
-  }
-  const unsigned short* p = static_cast<const unsigned short*>(lds);
-  const int base = L.c16 * SB + 8 * L.g;
-  f4 br[2], bi[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) pf_rb_load<float>(br[i], bi[i], B, L.w, i, L.lane);
-  h8v a[2][4];
-#pragma unroll
-  for (int pl = 0; pl < 4; ++pl) a[0][pl] = *reinterpret_cast<const h8v*>(p + pl * PL + base);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    u4v rh, rl, ih, il;
-#pragma unroll
-    for (int jp = 0; jp < 4; ++jp) {
-      const int i = jp >> 1, r = 2 * (jp & 1);
-      unsigned h, l;
-      f16_split2(H128::C * br[i][r], H128::C * br[i][r + 1], h, l);
-      rh[jp] = h;
-      rl[jp] = l;
-      f16_split2(H128::C * bi[i][r], H128::C * bi[i][r + 1], h, l);
-      ih[jp] = h;
-      il[jp] = l;
-    }
-    const h8v brh = __builtin_bit_cast(h8v, rh), brl = __builtin_bit_cast(h8v, rl);
-    const h8v bih = __builtin_bit_cast(h8v, ih), bil = __builtin_bit_cast(h8v, il);
-    const h8v nih = O::neg(bih), nil = O::neg(bil);
-    if (t < 3) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) pf_rb_load<float>(br[i], bi[i], B, L.w, 2 * (t + 1) + i, L.lane);
-    }
-#pragma unroll
-    for (int mb = 0; mb < 8; ++mb) {
-      const int st = 8 * t + mb, cur = st & 1;
-      if (st + 1 < 32) {
-        const int off = base + 16 * ((st + 1) % 8) * SB + 32 * ((st + 1) / 8);
-#pragma unroll
-        for (int pl = 0; pl < 4; ++pl) a[cur ^ 1][pl] = *reinterpret_cast<const h8v*>(p + pl * PL + off);
-      }
-      O::step<false>(acc.re[mb], acc.im[mb], a[cur], brh, brl, bih, bil, nih, nil);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  panel_scale(acc, 1.0f / (H128::C * H128::C));
-}
-
-// acc (+)= M B by gemm128h (H) or gemm128.
-template <typename T, bool H, int MODE>
-__device__ __forceinline__ void mul128(Panel<T, 128>& acc, void* lds, const T* M, const T* B, const Lane& L,
-                                       bool zero_acc, bool stage = true) {
-  if constexpr (H) gemm128h<MODE>(acc, lds, M, B, L, zero_acc, stage);
-  else gemm128<T, MODE == LEFT_CT, k128Gauss<T>>(acc, static_cast<T*>(lds), M, B, L, zero_acc, stage);
-}
-
-template <typename T, bool H>
-constexpr int kLds128 = H ? H128::BYTES : K128<T>::LDS_ELEMS * (int)sizeof(T);
-
 // out = M^dag (both PF), through LDS part by part.
 template <typename T>
 __device__ __forceinline__ void transpose128(T* out, T* lds, const T* M, const Lane& L) {
@@ -2821,10 +2696,9 @@ __device__ __forceinline__ T* slot_mat(void* scratch, int i) {
   return reinterpret_cast<T*>(scratch) + ((size_t)blockIdx.x * kScratchMats + i) * K128<T>::ELEMS;
 }
 
-template <typename T, bool H>
+template <typename T>
 __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
-  __shared__ __align__(16) unsigned char ldsb[kLds128<T, H>];
-  T* lds = reinterpret_cast<T*>(ldsb);
+  __shared__ T lds[K128<T>::LDS_ELEMS];
   Lane L;
   T* SX = slot_mat<T>(scratch, 0);
   T* SR = slot_mat<T>(scratch, 1);
@@ -2849,10 +2723,9 @@ __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
     // of Horner's q - 1, and X2 on the way.  (Taking X2 from Horner's first
     // product as k_expm does cost this kernel more in scratch traffic than
     // the products it saves.)  FP64, whose kernels spill, runs Horner.
-    if (kKeepX2<T> && q >= 2) {
+    if (sizeof(T) == 4 && q >= 2) {
       T* S2 = slot_mat<T>(scratch, 2);
-      mul128<T, H, LEFT_ANTI>(acc, lds, SX, SX, L, true);
-      if (!H && (P.flags & RUN_GRAD) && P.x2) panel_store(pf_mat<T, 128>(P.x2, k - W.rg.kbase), acc, L);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SX, L, true);
       if (q == 2) {
         panel_scale(acc, (T)0.5);
         panel_axpy_pf(acc, (T)1, SX, L);  // X + X2 / 2
@@ -2877,28 +2750,28 @@ __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
           panel_load(acc, SX, L);
           panel_scale(acc, (T)inv_factorial(2 * t + 3));
           panel_add_identity(acc, L, (T)inv_factorial(2 * t + 2));
-          mul128<T, H, LEFT_HERM>(acc, lds, S2, SR, L, false, !staged);
+          gemm128<T, false, k128Gauss<T>>(acc, lds, S2, SR, L, false, !staged);
           staged = true;
           panel_store(SR, acc, L);
         }
         panel_load(acc, SX, L);
-        mul128<T, H, LEFT_HERM>(acc, lds, S2, SR, L, false, !staged);  // X + X2 C
+        gemm128<T, false, k128Gauss<T>>(acc, lds, S2, SR, L, false, !staged);  // X + X2 C
       }
     } else if (q >= 2) {
       panel_scale(acc, (T)(1.0 / q));
       panel_add_identity(acc, L, (T)1);
       panel_store(SR, acc, L);
       for (int i = q - 1; i >= 2; --i) {
-        mul128<T, H, LEFT_ANTI>(acc, lds, SX, SR, L, true);
+        gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SR, L, true);
         panel_scale(acc, (T)(1.0 / i));
         panel_add_identity(acc, L, (T)1);
         panel_store(SR, acc, L);
       }
-      mul128<T, H, LEFT_ANTI>(acc, lds, SX, SR, L, true);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SR, L, true);
     }
     for (int j = 0; j < s; ++j) {
       panel_store(SR, acc, L);
-      mul128<T, H, LEFT_PLAIN>(acc, lds, SR, SR, L, true);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, SR, SR, L, true);
       panel_axpy_pf(acc, (T)2, SR, L);
     }
     panel_store(pf_mat<T, 128>(P.delta, k - W.rg.kbase), acc, L);
@@ -3000,12 +2873,9 @@ __device__ __noinline__ void reunitarise128(const ProbDesc& P, float* Ypf, float
   __syncthreads();
 }
 
-// H: the backward pass on the FP16 matrix cores; the forward one, whose errors
-// add up over the chain, is always in precision T.
-template <typename T, bool H>
+template <typename T>
 __global__ __launch_bounds__(512) void k_scan128(Work W, int dir) {
-  __shared__ __align__(16) unsigned char ldsb[kLds128<T, H>];
-  T* lds = reinterpret_cast<T*>(ldsb);
+  __shared__ T lds[K128<T>::LDS_ELEMS];
   __shared__ double red[8];
   const int bwd = dir < 0 ? (int)blockIdx.y : dir;  // dir < 0: both passes, one per blockIdx.y
   Lane L;
@@ -3034,8 +2904,7 @@ __global__ __launch_bounds__(512) void k_scan128(Work W, int dir) {
       panel_store(pf_mat<T, 128>(P.bloc, k1 - 1 - W.rg.kbase), acc, L);
       for (int k = k1 - 1; k >= k0; --k) {
         T* cur = pf_mat<T, 128>(P.bloc, k - W.rg.kbase);
-        if constexpr (H) gemm128h<LEFT_CT>(acc, lds, pf_mat<T, 128>(P.delta, k - W.rg.kbase), cur, L, true, true);
-        else gemm128<T, true>(acc, lds, pf_mat<T, 128>(P.delta, k - W.rg.kbase), cur, L, true);
+        gemm128<T, true>(acc, lds, pf_mat<T, 128>(P.delta, k - W.rg.kbase), cur, L, true);
         panel_axpy_pf(acc, (T)1, cur, L);
         if (k > k0) panel_store(pf_mat<T, 128>(P.bloc, k - 1 - W.rg.kbase), acc, L);
       }
@@ -3241,13 +3110,9 @@ __device__ __forceinline__ void sampled_gradient128(const ProbDesc& P, int k, co
 }
 
 // Same steps as k_adjoint, with the chain state in scratch (see above).
-// H: on the FP16 matrix cores, where X2 costs less to form than to read back,
-// and W is kept at its size (the block is halved at each squaring instead), so
-// that every factor stays in FP16's range whatever s.
-template <typename T, bool H>
+template <typename T>
 __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
-  __shared__ __align__(16) unsigned char ldsb[kLds128<T, H>];
-  T* lds = reinterpret_cast<T*>(ldsb);
+  __shared__ T lds[K128<T>::LDS_ELEMS];
   __shared__ double red[2 * kEpiGroup * 2 * 8];
   Lane L;
   T* S0 = slot_mat<T>(scratch, 0);
@@ -3267,14 +3132,14 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
     Panel<T, 128> acc;
     // W = bloc[k] xprev[k]^dag (bloc carries mc[c])
     transpose128<T>(S0, lds, pf_mat<T, 128>(P.xprev, k - W.rg.kbase), L);
-    mul128<T, H, LEFT_PLAIN>(acc, lds, pf_mat<T, 128>(P.bloc, k - W.rg.kbase), S0, L, true);
+    gemm128<T, false, k128Gauss<T>>(acc, lds, pf_mat<T, 128>(P.bloc, k - W.rg.kbase), S0, L, true);
     // E = W / 2^s
-    if (!H) panel_scale(acc, (T)ldexp(1.0, -s));
+    panel_scale(acc, (T)ldexp(1.0, -s));
     panel_store(SE, acc, L);
     // X = A^dag / 2^s: the expm pass's A / 2^s negated (A = -i dt H_k with H_k
     // Hermitian), or its conjugate transpose for general generators (own
     // panel; the barrier at the start of the next product publishes SX)
-    if (!H && (P.flags & RUN_GENERAL)) {
+    if (P.flags & RUN_GENERAL) {
       transpose128<T>(SX, lds, pf_mat<T, 128>(P.hk, k - W.rg.kbase), L);
     } else {
       panel_load(acc, pf_mat<T, 128>(P.hk, k - W.rg.kbase), L);
@@ -3284,12 +3149,10 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
     // The block polynomial by Paterson-Stockmeyer as in k_adjoint: M^2 =
     // [[X2, S], [0, X2]] into S0 (X2) and S1 (S), the running C = [[C1, C2],
     // [0, C1]] in SR1 and SR2.
-    const bool kept = !H && kKeepX2<T> && q >= 2 && P.x2 && !(P.flags & RUN_GENERAL);
-    if (kept) panel_load(acc, pf_mat<T, 128>(P.x2, k - W.rg.kbase), L);  // by the expm
-    else mul128<T, H, LEFT_ANTI>(acc, lds, SX, SX, L, true);
+    gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SX, L, true);
     panel_store(S0, acc, L);
-    mul128<T, H, LEFT_ANTI>(acc, lds, SX, SE, L, true, kept);
-    mul128<T, H, LEFT_PLAIN>(acc, lds, SE, SX, L, false);
+    gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SE, L, true, false);
+    gemm128<T, false, k128Gauss<T>>(acc, lds, SE, SX, L, false);
     panel_store(S1, acc, L);
     const int top = (qb - 2) / 2;
     int t;
@@ -3327,19 +3190,19 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
       const T a = (T)inv_factorial(2 * t + 2), b = (T)inv_factorial(2 * t + 3);
       panel_load(acc, SE, L);
       panel_scale(acc, b);
-      mul128<T, H, LEFT_PLAIN>(acc, lds, S1, SR1, L, false);
-      mul128<T, H, LEFT_HERM>(acc, lds, S0, SR2, L, false);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, S1, SR1, L, false);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR2, L, false);
       panel_store(SR2, acc, L);  // b E + S C1 + X2 C2
       panel_load(acc, SX, L);
       panel_scale(acc, b);
       panel_add_identity(acc, L, a);
-      mul128<T, H, LEFT_HERM>(acc, lds, S0, SR1, L, false, false);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR1, L, false, false);
       panel_store(SR1, acc, L);  // a I + b X + X2 C1
       x2_staged = true;
     }
     if constexpr (sizeof(T) == 4) {
       if ((sqk & kPlanSampled) && P.m <= kSample128Max) {  // s = 0: only the entries the controls read
-        sampled_gradient128(P, k, L, lds, red, S0, S1, SR1, SR2, SE, !H && x2_staged);
+        sampled_gradient128(P, k, L, lds, red, S0, S1, SR1, SR2, SE, x2_staged);
         __syncthreads();
         continue;
       }
@@ -3347,26 +3210,25 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
     // Q = E + X2 C2 + S C1 and, when squaring follows, D1 = X + X2 C1 (into
     // S1 once every wavefront has staged S; Q waits in the own panel of SE).
     panel_load(acc, SE, L);
-    mul128<T, H, LEFT_HERM>(acc, lds, S0, SR2, L, false, !x2_staged);
-    mul128<T, H, LEFT_PLAIN>(acc, lds, S1, SR1, L, false);
+    gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR2, L, false, !x2_staged);
+    gemm128<T, false, k128Gauss<T>>(acc, lds, S1, SR1, L, false);
     if (s > 0) {
       panel_store(SE, acc, L);
       panel_load(acc, SX, L);
-      mul128<T, H, LEFT_HERM>(acc, lds, S0, SR1, L, false);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, SR1, L, false);
       panel_store(S1, acc, L);
       panel_load(acc, SE, L);
     }
     for (int j = 0; j < s; ++j) {
       panel_store(S0, acc, L);                        // Q
-      mul128<T, H, LEFT_PLAIN>(acc, lds, S1, S0, L, true);   // D1 Q
-      mul128<T, H, LEFT_PLAIN>(acc, lds, S0, S1, L, false);  // + Q D1
-      if (H) panel_scale(acc, (T)0.5);
-      panel_axpy_pf(acc, H ? (T)1 : (T)2, S0, L);     // Q <- 2Q + D1 Q + Q D1 (H: half of it)
+      gemm128<T, false, k128Gauss<T>>(acc, lds, S1, S0, L, true);   // D1 Q
+      gemm128<T, false, k128Gauss<T>>(acc, lds, S0, S1, L, false);  // + Q D1
+      panel_axpy_pf(acc, (T)2, S0, L);                // Q <- 2Q + D1 Q + Q D1
       if (j + 1 < s) {
         // Every wavefront's staging of the old Q and D1 ended before the
         // barrier inside the last product, so own panels may be replaced.
         panel_store(S0, acc, L);
-        mul128<T, H, LEFT_PLAIN>(acc, lds, S1, S1, L, true);
+        gemm128<T, false, k128Gauss<T>>(acc, lds, S1, S1, L, true);
         panel_axpy_pf(acc, (T)2, S1, L);              // D1 <- 2 D1 + D1^2
         panel_store(S1, acc, L);
         panel_load(acc, S0, L);
@@ -3377,6 +3239,8 @@ __global__ __launch_bounds__(512) void k_adjoint128(Work W, void* scratch) {
     __syncthreads();
   }
 }
+
+#include "qoc_seg128.hpp"
 
 // ---------------------------------------------------------------- launchers
 
@@ -3480,7 +3344,7 @@ static void stage_seg(int stage, const Launch& L, const Range& rg, double ur) {
   switch (stage) {
     case ST_PLAN: {
       Work w = L.dyn ? dyn : slice_work(L, all);
-      const int comm = (L.flags & RUN_STATE) ? 0 : 4;
+      const int comm = (L.flags & RUN_STATE) ? 0 : PLAN_COMM;
       hipLaunchKernelGGL(k_plan, dim3(L.dyn ? L.dyn_grid : (w.total + 255) / 256), dim3(256), 0, st, w, ur,
                          grad | comm);
       break;
@@ -3534,8 +3398,8 @@ static void stage_le64(int stage, const Launch& L, const Range& rg, double ur) {
   else stage_seg<T, D, SOps>(stage, L, rg, ur);
 }
 
-// H: Hermitian Hamiltonians in FP32, on the FP16 matrix cores.
-template <typename T, bool H>
+// FP64, and general generators in FP32.
+template <typename T>
 static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
   hipStream_t st = L.stream;
   const int dirs = (L.flags & RUN_BWD) ? 2 : 1;
@@ -3553,12 +3417,12 @@ static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
     case ST_PLAN: {
       Work w = L.dyn ? dyn : slice_work(L, all);
       hipLaunchKernelGGL(k_plan, dim3(L.dyn ? L.dyn_grid : (w.total + 255) / 256), dim3(256), 0, st, w, ur,
-                         grad | (kKeepX2<T> ? 2 : 0));
+                         grad | (sizeof(T) == 4 ? PLAN_PS : 0));
       break;
     }
     case ST_EXPM: {
       Work w = L.dyn ? dyn : slice_work(L, rg);
-      hipLaunchKernelGGL((k_expm128<T, H>), dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
+      hipLaunchKernelGGL((k_expm128<T>), dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
       break;
     }
     case ST_SCAN:
@@ -3566,7 +3430,7 @@ static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
       Work w = L.dyn ? dyn : chunk_work(L, rg);
       const bool both = stage == ST_SCAN && rg.recompute && !L.dyn;
       const int dir = stage == ST_BSCAN ? 1 : (both ? -1 : 0);
-      hipLaunchKernelGGL((k_scan128<T, H>), dim3(grid_of(L, w.total, 0), both ? 2 : 1), dim3(512), 0, st, w, dir);
+      hipLaunchKernelGGL((k_scan128<T>), dim3(grid_of(L, w.total, 0), both ? 2 : 1), dim3(512), 0, st, w, dir);
       break;
     }
     case ST_CARRY: {
@@ -3587,9 +3451,49 @@ static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
     }
     case ST_ADJ: {
       Work w = L.dyn ? dyn : slice_work(L, rg);
-      hipLaunchKernelGGL((k_adjoint128<T, H>), dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
+      hipLaunchKernelGGL((k_adjoint128<T>), dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
       break;
     }
+  }
+}
+
+// Hermitian Hamiltonians at D = 128 in FP32.
+static void stage_seg128(int stage, const Launch& L, const Range& rg, double ur) {
+  hipStream_t st = L.stream;
+  const int grad = (L.flags & RUN_GRAD) ? 1 : 0;
+  const int parts = (L.flags & RUN_RAWDG) ? 2 : 1;
+  const Range all = {0, L.uniformN, 0, L.uniformP, rg.kbase};
+  const Work dyn = L.dyn ? Work{L.descs, 0, 0, nullptr, Range{0, 0, 0, 0, 0}, L.dyn} : Work{};
+  const Work segs = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * rg.c_n * seg_count(128, L.chunk), nullptr, rg, nullptr};
+  const int cap = kScratchSlots;  // each workgroup owns a region of the scratch
+  switch (stage) {
+    case ST_PLAN: {
+      Work w = L.dyn ? dyn : slice_work(L, all);
+      hipLaunchKernelGGL(k_plan, dim3(L.dyn ? L.dyn_grid : (w.total + 255) / 256), dim3(256), 0, st, w, ur,
+                         grad | PLAN_PS | ((L.flags & RUN_STATE) ? 0 : PLAN_COMM | PLAN_HORNER));
+      break;
+    }
+    case ST_EXPM:
+      hipLaunchKernelGGL(k_seg_fwd128, dim3(grid_of(L, segs.total, cap)), dim3(512), 0, st, segs, L.scratch);
+      break;
+    case ST_SCAN: {
+      Work w = L.dyn ? dyn : chunk_work(L, rg);
+      hipLaunchKernelGGL(k_seg_join128, dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
+      break;
+    }
+    case ST_MC: {
+      Work w = L.dyn ? dyn : chunk_work(L, all);
+      hipLaunchKernelGGL(k_seg_y128, dim3(grid_of(L, w.total, cap)), dim3(512), 0, st, w, L.scratch);
+      break;
+    }
+    case ST_ADJ: {
+      const dim3 grid(std::min(grid_of(L, segs.total, cap), cap / parts), parts);
+      hipLaunchKernelGGL(k_seg_grad128, grid, dim3(512), 0, st, segs, L.scratch);
+      hipLaunchKernelGGL(k_seg_grad_sq128, grid, dim3(512), 0, st, segs, L.scratch);
+      break;
+    }
+    case ST_BSCAN: break;  // (none)
+    default: stage_128<float>(stage, L, rg, ur);  // preparation and carry
   }
 }
 
@@ -3602,7 +3506,7 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
       case 16: stage_le64<double, 16, StdOps<double, 16>, StdOps<double, 16>>(stage, L, rg, ur64); break;
       case 32: stage_le64<double, 32, StdOps<double, 32>, StdOps<double, 32>>(stage, L, rg, ur64); break;
       case 64: stage_le64<double, 64, StdOps<double, 64>, StdOps<double, 64>>(stage, L, rg, ur64); break;
-      case 128: stage_128<double, false>(stage, L, rg, ur64); break;
+      case 128: stage_128<double>(stage, L, rg, ur64); break;
       default: ok = false;
     }
   } else if (precision == 1) {
@@ -3611,8 +3515,8 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
       case 32: stage_le64<float, 32, F16Ops<32>, StdOps<float, 32>>(stage, L, rg, ur32); break;
       case 64: stage_le64<float, 64, F16Ops<64>, StdOps<float, 64>>(stage, L, rg, ur32); break;
       case 128:
-        if (L.flags & RUN_GENERAL) stage_128<float, false>(stage, L, rg, ur32);
-        else stage_128<float, true>(stage, L, rg, ur32);
+        if (L.flags & RUN_GENERAL) stage_128<float>(stage, L, rg, ur32);
+        else stage_seg128(stage, L, rg, ur32);
         break;
       default: ok = false;
     }

@@ -95,13 +95,33 @@ QOC_HD inline int frechet_products(int qb) { return 5 + 3 * (qb > 3 ? (qb - 3) /
 // comm: the gradient's m products of the commutator series and, for s > 0,
 // the exponential again, s doublings and the step of Y.
 QOC_HD inline int plan_cost(int s, int q, int qb, int m, bool grad, bool ps_expm, bool comm) {
-  int cost = (comm ? taylor_products(q) : ps_expm ? expm_products(q) : q - 1) + s;
-  if (grad && comm) cost += m + (s > 0 ? taylor_products(q) + 2 + 3 * s : 0);
+  const int expm = ps_expm ? expm_products(q) : comm ? taylor_products(q) : q - 1;
+  int cost = expm + s;
+  if (grad && comm) cost += m + (s > 0 ? expm + 2 + 3 * s : 0);
   else if (grad) cost += frechet_products(qb) + 3 * s;
   return cost;
 }
 
-QOC_HD inline SlicePlan choose_plan(double theta, double ur, bool grad, bool ps_expm = false, bool comm = false) {
+// Least degree n >= 1 at which the remainder of sum_n x^n / (n + 1)! after degree
+// n - 1, x^n / (n + 1)! * 1/(1 - x/(n + 2)), is at most ur.
+QOC_HD inline int phi_degree(double x, double ur) {
+  int q = 1;
+  double t = x * 0.5;  // x^n/(n+1)!
+#pragma unroll
+  for (int n = 1; n < 30; ++n) {
+    if (!(t > ur * (1.0 - x * plan_inv(n + 2)))) break;
+    q = n + 1;
+    t *= x * plan_inv(n + 2);
+  }
+  return q;
+}
+
+// What the plan is for: a gradient; Paterson-Stockmeyer exponentials; the
+// commutator series; that summed by Horner's rule.
+enum PlanFlags : int { PLAN_GRAD = 1, PLAN_PS = 2, PLAN_COMM = 4, PLAN_HORNER = 8 };
+
+QOC_HD inline SlicePlan choose_plan(double theta, double ur, int flags) {
+  const bool grad = (flags & PLAN_GRAD) != 0, ps_expm = (flags & PLAN_PS) != 0, comm = (flags & PLAN_COMM) != 0;
   int s0 = 0;
   while (ldexp(theta, -s0) > 1.0 && s0 < 60) ++s0;
   SlicePlan best = {s0, 1, 2, 1};
@@ -111,6 +131,10 @@ QOC_HD inline SlicePlan choose_plan(double theta, double ur, bool grad, bool ps_
     int q = taylor_degree(r, ur);
     int qb = frechet_degree(r, ur);
     int m = comm ? taylor_degree(2 * r, ur) : 0;
+    if (flags & PLAN_HORNER) {
+      const int mz = phi_degree(2 * r, ur);
+      m = m > mz ? m : mz;
+    }
     int c = plan_cost(s, q, qb, m, grad, ps_expm, comm);
     // the degrees fall ever more slowly with s while each s adds the same:
     // past the minimum the count only grows
