@@ -188,6 +188,21 @@ int qoc_trace_gradient_dev(int B, int d, int m, int N, const void* H0, const voi
                            void* workspace, size_t ws_bytes, const qoc_options* opt);
 
 /*
+ * The whole Jacobian of one problem's X_N in its controls (Hermitian, d <= 64):
+ *   J[a d + b][j N + k] = Re d(X_N)_ab / du[j][k],  J[d^2 + a d + b][j N + k] the imaginary part,
+ * float64 device memory, rows of ld >= m N entries of which the first m N are
+ * written; U_total receives X_N (complex128, d x d).  The values are those of d^2
+ * qoc_trace_gradient_dev problems with the targets e_a e_b^T, from one forward
+ * pass.  workspace holds qoc_jacobian_workspace_size bytes (0 where the call is
+ * not supported), 256-byte aligned.  opt's chunk and hbm_budget are not used.
+ */
+size_t qoc_jacobian_workspace_size(int d, int m, int N, int precision);
+
+int qoc_jacobian_dev(int d, int m, int N, const void* H0, const void* Hc, const void* u, double dt,
+                     void* J, size_t ld, void* U_total, void* workspace, size_t ws_bytes,
+                     const qoc_options* opt);
+
+/*
  * qoc_gradient_dev without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same batch layout, outputs, options and

@@ -170,11 +170,18 @@ double reun_tol(const qoc_options& o) {
   return o.reunitarise_tol;
 }
 
+// Output of a Jacobian call, and its m N stored matrices.
+struct JacOut {
+  double* J;
+  size_t ld;
+  void* mats;
+};
+
 // Enqueue the path for a uniform batch whose inputs and outputs are in
 // device memory.  flags: qoc::RUN_* bits.
 int run_dev(int B, int d, int m, int N, const void* H0, const void* Hc, const void* u, double dt, const void* V,
             void* F, void* grad, void* XN, void* ws, size_t ws_bytes, const qoc_options* opt_in, int flags,
-            void* g_out = nullptr) {
+            void* g_out = nullptr, const JacOut* jac = nullptr) {
   const qoc_options opt = opt_in ? *opt_in : defaults();
   int rc = check_dims(B, d, m, N, opt.precision);
   if (rc) return rc;
@@ -220,12 +227,14 @@ int run_dev(int B, int d, int m, int N, const void* H0, const void* Hc, const vo
   L.total_slices = B * N;
   L.total_chunks = B * Lo.P;
   L.max_m = m;
-  L.flags = flags | (opt.generators ? qoc::RUN_GENERAL : 0);
+  // (the Jacobian's slices are planned as the gradient's)
+  L.flags = flags | (opt.generators ? qoc::RUN_GENERAL : 0) | (jac ? qoc::RUN_GRAD : 0);
   L.stream = st;
   L.scratch = Lo.scratch_bytes ? base + Lo.scratch : nullptr;
   L.dyn = nullptr;
   L.dyn_grid = 0;
   e = enqueue(opt.precision, Lo, L, N, flags);
+  if (e == hipSuccess && jac) e = qoc::launch_jacobian(opt.precision, Lo.D, L, d, m, N, jac->mats, jac->J, jac->ld);
   if (e != hipSuccess) return fail(QOC_ERR_DEVICE, "kernel launch: %s", hipGetErrorString(e));
   return QOC_OK;
 }
@@ -513,6 +522,31 @@ int qoc_gradient_dev_noalloc(int B, int d, int m, int N, const void* H0, const v
   if (!ws) return QOC_ERR_DEVICE;
   return run_dev(B, d, m, N, H0, Hc, u, dt, V, F, grad, nullptr, ws, QOC_NOALLOC_SCRATCH_BYTES, &opt,
                  qoc::RUN_FID | qoc::RUN_BWD | qoc::RUN_GRAD);
+}
+
+size_t qoc_jacobian_workspace_size(int d, int m, int N, int precision) {
+  if (check_dims(1, d, m, N, precision) || qoc::padded_dim(d) > 64) return 0;
+  const Layout Lo = make_layout(1, d, m, N, precision, 0, 0);
+  return Lo.total + (size_t)m * N * 2 * Lo.D * Lo.D * qoc::elem_size(precision);
+}
+
+int qoc_jacobian_dev(int d, int m, int N, const void* H0, const void* Hc, const void* u, double dt, void* J, size_t ld,
+                     void* U_total, void* workspace, size_t ws_bytes, const qoc_options* opt_in) {
+  qoc_options opt = opt_in ? *opt_in : defaults();
+  const int rc = check_dims(1, d, m, N, opt.precision);
+  if (rc) return rc;
+  if (qoc::padded_dim(d) > 64 || opt.generators)
+    return fail(QOC_ERR_UNSUPPORTED, "the Jacobian takes Hermitian Hamiltonians with d <= 64");
+  if (!J || !U_total) return fail(QOC_ERR_ARG, "J and U_total must be non-null");
+  if (ld < (size_t)m * N) return fail(QOC_ERR_ARG, "rows of J hold %zu entries, %zu needed", ld, (size_t)m * N);
+  const size_t need = qoc_jacobian_workspace_size(d, m, N, opt.precision);
+  if (ws_bytes < need) return fail(QOC_ERR_ARG, "workspace holds %zu bytes, %zu needed", ws_bytes, need);
+  opt.chunk = 0;
+  opt.hbm_budget = 0;
+  const size_t base = make_layout(1, d, m, N, opt.precision, 0, 0).total;
+  const JacOut jac = {static_cast<double*>(J), ld, static_cast<char*>(workspace) + base};
+  return run_dev(1, d, m, N, H0, Hc, u, dt, nullptr, nullptr, nullptr, U_total, workspace, base, &opt, 0, nullptr,
+                 &jac);
 }
 
 int qoc_slice_plan(int d, int m, int N, const qoc_z* H0, const qoc_z* Hc, const double* u, double dt,

@@ -139,6 +139,12 @@ void set_last_error(const char* msg);
 // Enqueue one stage of the path.  Returns a hipError_t.
 hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const Range& rg);
 
+// dX_N / du of the one problem of L (D <= 64, Hermitian), after the forward stages
+// with every slice stored and X_N in the descriptor's XN: rows of ld doubles into
+// J, by way of m N stored matrices in mats.
+hipError_t launch_jacobian(int precision, int D, const Launch& L, int d, int m, int N, void* mats, double* J,
+                           size_t ld);
+
 // ---------------------------------------------------------------- workspace layout
 
 constexpr size_t kAlign = 256;

@@ -3539,4 +3539,6 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
   return hipGetLastError();
 }
 
+#include "qoc_jac.hpp"
+
 }  // namespace qoc

@@ -44,6 +44,8 @@ EXPORTS = (
     "qoc_gradient_dev",
     "qoc_gradient_dev_noalloc",
     "qoc_trace_gradient_dev",
+    "qoc_jacobian_workspace_size",
+    "qoc_jacobian_dev",
     "qoc_slice_plan",
     "qoc_state_workspace_size",
     "qoc_state_propagate",
@@ -119,6 +121,9 @@ def lib() -> ctypes.CDLL:
     L.qoc_gradient_dev.argtypes = [i32, i32, i32, i32, vp, vp, vp, dbl, vp, vp, vp, vp, sz, opt]
     L.qoc_gradient_dev_noalloc.argtypes = [i32, i32, i32, i32, vp, vp, vp, dbl, vp, vp, vp, opt]
     L.qoc_trace_gradient_dev.argtypes = [i32, i32, i32, i32, vp, vp, vp, dbl, vp, vp, vp, vp, sz, opt]
+    L.qoc_jacobian_workspace_size.argtypes = [i32, i32, i32, i32]
+    L.qoc_jacobian_workspace_size.restype = sz
+    L.qoc_jacobian_dev.argtypes = [i32, i32, i32, vp, vp, vp, dbl, vp, sz, vp, vp, sz, opt]
     L.qoc_slice_plan.argtypes = [i32, i32, i32, vp, vp, vp, dbl, i32, i32, vp]
     L.qoc_state_workspace_size.argtypes = [i32, i32, i32, i32, i32]
     L.qoc_state_workspace_size.restype = sz
@@ -146,7 +151,7 @@ def lib() -> ctypes.CDLL:
     L.qoc_last_error.restype = ctypes.c_char_p
     L.qoc_version.restype = ctypes.c_char_p
     for name in ("qoc_stage_timing", "qoc_stage_times", "qoc_propagate", "qoc_fidelity", "qoc_gradient", "qoc_propagate_dev", "qoc_fidelity_dev",
-                 "qoc_gradient_dev", "qoc_gradient_dev_noalloc", "qoc_trace_gradient_dev", "qoc_slice_plan",
+                 "qoc_gradient_dev", "qoc_gradient_dev_noalloc", "qoc_trace_gradient_dev", "qoc_jacobian_dev", "qoc_slice_plan",
                  "qoc_state_propagate",
                  "qoc_state_gradient", "qoc_state_propagate_dev", "qoc_state_gradient_dev"):
         getattr(L, name).restype = ctypes.c_int
@@ -403,6 +408,36 @@ class Runner:
         _check(lib().qoc_propagate_dev(b.B, b.d, b.m, b.N, b.H0.data_ptr(), b.Hc.data_ptr(), b.u.data_ptr(), b.dt,
                                        out.data_ptr(), self.ws.data_ptr(), self.ws_bytes, ctypes.byref(o)))
         return out
+
+
+class JacobianRunner(Runner):
+    """Owns the workspace for Jacobians of one problem (Hermitian, d <= 64)."""
+
+    def __init__(self, d, m, N, precision="fp64", device="cuda"):
+        import torch
+
+        self.generators = self.dense_controls = False
+        self.B, self.d, self.m, self.N = 1, d, m, N
+        self.precision, self.chunk, self.hbm_budget = precision, 0, 0
+        self.ws_bytes = int(lib().qoc_jacobian_workspace_size(d, m, N, PRECISIONS[precision]))
+        self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=device)
+        self.device = device
+
+    def jacobian(self, b: Batch, J, XN=None, stream=None):
+        """Enqueue the first m N columns of J (2 d^2 rows, float64): the real and
+        the imaginary parts of d(X_N)_ab / du."""
+        import torch
+
+        self._shape_ok(b)
+        if J.shape[0] != 2 * self.d ** 2 or J.shape[1] < self.m * self.N or J.stride(1) != 1 or J.dtype != torch.float64:
+            raise ValueError("J must be a float64 row-major tensor of 2 d^2 rows of at least m N entries")
+        if XN is None:
+            XN = torch.empty((self.d, self.d), dtype=torch.complex128, device=self.ws.device)
+        o = self._opt(stream)
+        _check(lib().qoc_jacobian_dev(b.d, b.m, b.N, b.H0.data_ptr(), b.Hc.data_ptr(), b.u.data_ptr(), b.dt,
+                                      J.data_ptr(), J.stride(0), XN.data_ptr(), self.ws.data_ptr(), self.ws_bytes,
+                                      ctypes.byref(o)))
+        return J
 
 
 class StateBatch:

@@ -9,9 +9,10 @@ is d (1 - sqrt(F)).  Minimising f maximises the fidelity.
 Where the work runs:
   * X_N: qoc_propagate_dev (libqoc kernels).
   * The Jacobian J (2 d^2 x (m N + 1)): its rows d(X_N)_ab/du come from
-    qoc_trace_gradient_dev on a batch of d^2 copies of the problem with the
-    targets V_ab = e_a e_b^T (Tr(V_ab^dag X_N) = (X_N)_ab); the phi column is
-    vec(-i e^{i phi} V).  J stays in device memory.
+    qoc_jacobian_dev, above d = 64 from qoc_trace_gradient_dev on a batch of
+    d^2 copies of the problem with the targets V_ab = e_a e_b^T
+    (Tr(V_ab^dag X_N) = (X_N)_ab); the phi column is vec(-i e^{i phi} V).  J
+    stays in device memory.
   * The thin SVD of J (App. B) is a library call on the device
     (torch.linalg.svd, rocSOLVER), once per accepted step, as the paper does
     it once per update.
@@ -49,6 +50,12 @@ class GrapeLSQ:
         c128 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.complex128)).to(device)
         self.H0, self.Hc, self.V = c128(p.H0), c128(p.Hc), c128(p.V)
         d, n2 = self.d, self.d * self.d
+        self.one = qoc.Runner(1, d, self.m, self.N, precision, device=device)
+        self.evals = 0
+        self.jacobians = 0
+        self.whole = qoc.JacobianRunner(d, self.m, self.N, precision, device) if d <= 64 else None
+        if self.whole is not None:
+            return
         # batch of d^2 copies with the unit targets e_a e_b^T, row-major (a, b)
         self.Hb = self.H0.unsqueeze(0).expand(n2, d, d).contiguous()
         self.Hcb = self.Hc.unsqueeze(0).expand(n2, self.m, d, d).contiguous()
@@ -56,10 +63,7 @@ class GrapeLSQ:
         idx = torch.arange(n2, device=device)
         E[idx, idx // d, idx % d] = 1.0
         self.E = E
-        self.one = qoc.Runner(1, d, self.m, self.N, precision, device=device)
         self.many = qoc.Runner(n2, d, self.m, self.N, precision, device=device)
-        self.evals = 0
-        self.jacobians = 0
 
     def _u(self, x):
         return x[:-1].reshape(1, self.m, self.N)
@@ -79,13 +83,18 @@ class GrapeLSQ:
         import torch
 
         n2 = self.d * self.d
+        self.jacobians += 1
+        if self.whole is not None:
+            J = torch.empty((2 * n2, self.m * self.N + 1), dtype=torch.float64, device=self.device)
+            self.whole.jacobian(qoc.Batch(self.H0[None], self.Hc[None], self._u(x), self.dt, None), J)
+            J[:, -1] = torch.view_as_real((-1j * torch.exp(1j * x[-1]) * self.V).reshape(n2)).T.reshape(-1)
+            return J
         ub = self._u(x).expand(n2, self.m, self.N).contiguous()
         b = qoc.Batch(self.Hb, self.Hcb, ub, self.dt, self.E)
         _, dg = self.many.trace_gradient(b)                      # (d^2, m, N): d(X_N)_ab / du
         rows = dg.reshape(n2, self.m * self.N)
         dphi = (-1j * torch.exp(1j * x[-1]) * self.V).reshape(n2, 1)
         Jc = torch.cat([rows, dphi], dim=1)
-        self.jacobians += 1
         return torch.cat([Jc.real, Jc.imag], dim=0)
 
     def trace_gradient(self, x, W):
