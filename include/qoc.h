@@ -233,10 +233,14 @@ int qoc_gradient_dev_noalloc(int B, int d, int m, int N, const void* H0, const v
  *   F = |g|^2,   grad[j*N + k] = dF/du[j*N + k]  (exact derivative of the piecewise-constant model),
  *
  * with psi_0 and the target chi unit vectors of d complex entries (qoc_z).
- * No d x d propagator is formed: each slice is applied to a vector (and to
- * the costate lam_k = U_k^dag lam_{k+1}, lam_N = chi) by a Taylor polynomial
- * of the slice's plan (qoc_slice_plan), and the derivative is the plan's
- * truncated Frechet series taken between the costate and the state.  FP64
+ * Each slice is applied to a vector (and to the costate lam_k = U_k^dag
+ * lam_{k+1}, lam_N = chi) by a Taylor polynomial of the slice's plan
+ * (qoc_slice_plan), and the derivative is the plan's truncated Frechet series
+ * taken between the costate and the state.  With d <= 64, N >= 64 and a batch
+ * that single chains would not fill the chip with (FP32 512, 256 and 64
+ * problems at d <= 16, 32 and 64, FP64 512, 96 and 32), the N slices are cut
+ * into chunks whose propagators are formed; results of batches on different
+ * sides of that line differ by rounding.  FP64
  * and FP32 only (QOC_BF16X3 returns QOC_ERR_UNSUPPORTED); opt->validate also
  * checks |psi0| = |chi| = 1 within 1e-8 (QOC_ERR_NOT_UNITARY otherwise);
  * chunk, hbm_budget, reunitarise_tol and diagnostics are ignored.

@@ -138,6 +138,14 @@ struct Lane {
   }
 };
 
+// A workgroup barrier that orders LDS accesses only: __syncthreads() also waits
+// for every global load and store in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // LDS offset of logical element (row, col).
 template <typename T, int D>
 __device__ __forceinline__ int lds_off(int row, int col) {

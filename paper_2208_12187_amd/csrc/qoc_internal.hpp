@@ -139,6 +139,9 @@ void set_last_error(const char* msg);
 // Enqueue one stage of the path.  Returns a hipError_t.
 hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const Range& rg);
 
+// The chunk totals of B state problems (descriptors' L and chunks; D <= 64).
+hipError_t launch_state_totals(int precision, int D, const ProbDesc* descs, int B, int chunks, hipStream_t st);
+
 // dX_N / du of the one problem of L (D <= 64, Hermitian), after the forward stages
 // with every slice stored and X_N in the descriptor's XN: rows of ld doubles into
 // J, by way of m N stored matrices in mats.

@@ -3539,6 +3539,109 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- state path: chunk totals
+
+// The propagators of the state path's chunks less I, planar and row-major in tf
+// (D <= 64):
+// the identity carried through the chunk's slices as the states are, by the
+// Taylor polynomial's action (q products per part of a slice, no exponential).
+// In FP32 the sums over the slices are compensated (S and what their rounding
+// dropped): of the chunk's errors only the products' stay, which scale with A_k.
+// Each slice's factor also carries a scale of its own between 1 and 3/2: the
+// entries that are the same in every slice then round differently in each, and
+// their errors do not add up over the N slices.
+template <typename T, int D, typename Ops>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_state_total(
+    const ProbDesc* descs, int chunks) {
+  constexpr T C = Ops::C, CI = (T)1 / Ops::C;
+  __shared__ __align__(16) unsigned char la[Ops::BYTES];
+  __shared__ __align__(16) unsigned char lb[StdOps<T, D>::BYTES];
+  __shared__ SegTab<T, D> tab;
+  Lane L;
+  const ProbDesc P = descs[blockIdx.x / chunks];  // a copy: stores cannot alias it
+  const int c = blockIdx.x % chunks;
+  const int k0 = c * P.L, k1 = min(P.N, k0 + P.L);
+  const bool mono = (gp(P.sq)[k0] & kPlanMono) != 0;
+  const SegTab<T, D>* tb = nullptr;
+  constexpr bool COMP = sizeof(T) == 4;
+  Panel<T, D> S, X, R, E;
+  panel_zero(S);
+  panel_zero(E);
+  panel_add_identity(S, L, C);
+  for (int k = k0; k < k1; ++k) {
+    const int ki = (k - k0) % kSegMax;
+    if (ki == 0) {
+      __syncthreads();  // the tables have been read
+      tb = seg_tab_load<T, D>(tab, P, k, min(k1, k + kSegMax), mono) ? &tab : nullptr;
+    }
+    int s, q, qb;
+    unpack_sq(gp(P.sq)[k], s, q, qb);
+    const double scale = COMP ? 1.0 + (k & 15) / 32.0 : 1.0;
+    const T back = (T)(1.0 / ((double)C * scale));
+    assemble_panel<T, D>(X, lb, P, k, ldexp(P.dt * (double)C * scale, -s), mono, tb, ki, L);
+    Ops::store_nct(la, X, L);  // X = -X^dag
+    __syncthreads();
+    for (int r = 0; r < (1 << s); ++r) {
+      R = S;
+      for (int i = q; i > 1; --i) {
+        Ops::mul(X, la, R, L);
+        R = S;
+        panel_fma(R, back * (T)(1.0 / i), X);
+      }
+      Ops::mul(X, la, R, L);
+      if constexpr (COMP) {
+        panel_scale(X, back);
+        panel_fma(X, (T)1, E);
+        auto add = [](T& a, T& e, T b) {  // a + e <- a + b (two-sum)
+          const T t = a + b, z = t - a;
+          e = (a - (t - z)) + (b - z);
+          a = t;
+        };
+#pragma unroll
+        for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            T a = S.re[rb][i], e;
+            add(a, e, X.re[rb][i]);
+            S.re[rb][i] = a;
+            E.re[rb][i] = e;
+            a = S.im[rb][i];
+            add(a, e, X.im[rb][i]);
+            S.im[rb][i] = a;
+            E.im[rb][i] = e;
+          }
+      } else {
+        panel_fma(S, back, X);
+      }
+    }
+  }
+  panel_add_identity(S, L, -C);
+  panel_fma(S, (T)1, E);
+  T* o = static_cast<T*>(P.tf) + (size_t)c * 2 * D * D;
+#pragma unroll
+  for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int e = (16 * rb + Prec<T>::rowmap(r, L.g)) * D + 16 * L.w + L.c16;
+      o[e] = CI * S.re[rb][r];
+      o[D * D + e] = CI * S.im[rb][r];
+    }
+}
+
+hipError_t launch_state_totals(int precision, int D, const ProbDesc* descs, int B, int chunks, hipStream_t st) {
+  const dim3 grid(B * chunks), nt(4 * D);
+  switch (D + (precision == 0 ? 1000 : 0)) {
+    case 16: hipLaunchKernelGGL((k_state_total<float, 16, F16Ops<16>>), grid, nt, 0, st, descs, chunks); break;
+    case 32: hipLaunchKernelGGL((k_state_total<float, 32, F16Ops<32>>), grid, nt, 0, st, descs, chunks); break;
+    case 64: hipLaunchKernelGGL((k_state_total<float, 64, F16Ops<64>>), grid, nt, 0, st, descs, chunks); break;
+    case 1016: hipLaunchKernelGGL((k_state_total<double, 16, StdOps<double, 16>>), grid, nt, 0, st, descs, chunks); break;
+    case 1032: hipLaunchKernelGGL((k_state_total<double, 32, StdOps<double, 32>>), grid, nt, 0, st, descs, chunks); break;
+    case 1064: hipLaunchKernelGGL((k_state_total<double, 64, StdOps<double, 64>>), grid, nt, 0, st, descs, chunks); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 #include "qoc_jac.hpp"
 
 }  // namespace qoc

@@ -5,8 +5,10 @@
 //   psi_{k+1} = U_k psi_k,       lam_N = chi,  lam_k = U_k^dag lam_{k+1}
 //   g = <chi|psi_N>,  F = |g|^2,  dF/du[j][k] = 2 Re(conj(g) lam_{k+1}^dag L(A_k, E_j) psi_k)
 //
-// with A_k = -i dt H_k and E_j = -i dt Hc[j].  Nothing here forms a d x d
-// propagator: every step is the action of a matrix on vectors.
+// with A_k = -i dt H_k and E_j = -i dt Hc[j].  Every step is the action of a
+// matrix on vectors, except that batches too small to fill the chip with one chain
+// each first form the propagators of chunks of slices (k_state_total), so that the
+// chains run chunk by chunk at once.
 //
 //  * U_k psi is applied as T_q(A_k/R)^R psi, R = 2^s, with the (s, q, qb)
 //    plan of the matrix path: Horner on the vector in delta form,
@@ -62,6 +64,17 @@ constexpr int kChainBlock = 64;
 // Consecutive slices per gradient workgroup (H0 and the row tables are loaded
 // once for them).
 constexpr int kGradSlices = 8;
+
+// 1 / n!, n <= kStateQMax (a table: the divisions of a running product took a
+// third of the gradient kernel).
+struct InvFact {
+  double v[kStateQMax + 1];
+  constexpr InvFact() : v{} {
+    v[0] = 1.0;
+    for (int n = 1; n <= kStateQMax; ++n) v[n] = v[n - 1] / n;
+  }
+};
+__constant__ InvFact kInvFact = InvFact();
 
 template <typename T>
 struct cpx {
@@ -294,9 +307,116 @@ __device__ __forceinline__ double rows_sum(double v, double* red) {
 
 // ---------------------------------------------------------------- chains
 
-// One workgroup per (problem, direction).  Forward: psi_0 -> psi_N, storing
+// The end of a forward chain: g = <chi|psi_N> in FP64, F and psi_N.
+template <typename T, int D>
+__device__ __forceinline__ void state_end(const ProbDesc& P, int row, int cg, T xr, T xi, double* red) {
+  double gr = 0, gi = 0;
+  if (row < P.d) {
+    const double cr = P.chiz ? P.chiz[2 * row] : 0.0, ci = P.chiz ? P.chiz[2 * row + 1] : 0.0;
+    gr = cr * (double)xr + ci * (double)xi;
+    gi = cr * (double)xi - ci * (double)xr;
+  }
+  gr = rows_sum<D>(gr, red);
+  gi = rows_sum<D>(gi, red + SV<D>::NW);
+  if (threadIdx.x == 0 && P.chiz) {
+    P.g[0] = gr;
+    P.g[1] = gi;
+    P.F[0] = gr * gr + gi * gi;
+  }
+  if (P.XN && cg == 0 && row < P.d) {
+    P.XN[2 * row] = (double)xr;
+    P.XN[2 * row + 1] = (double)xi;
+  }
+}
+
+// Chunked chains: one workgroup per (problem, direction) takes the states at the
+// chunks' ends through the chunk totals (costates through their conjugate
+// transposes), the next totals' entries loading while one is applied.  The
+// vector and its sums are FP64 in both precisions: the chain waits for memory.
+template <typename T, int D>
+__global__ __launch_bounds__(SV<D>::NT) void k_state_top(StateWork W) {
+  constexpr int TPR = SV<D>::TPR, CPT = SV<D>::CPT;
+  static_assert(TPR == 4, "four lanes per row, four columns each in turn");
+  __shared__ __align__(16) double zb[2][2][D];
+  __shared__ double red[2 * SV<D>::NW];
+  const int bwd = blockIdx.y;
+  const ProbDesc P = W.descs[blockIdx.x];  // a copy: stores cannot alias it
+  const int row = threadIdx.x / TPR, cg = threadIdx.x % TPR;
+  const double* src = bwd ? P.chiz : P.psi0z;
+  double xr = 0, xi = 0;
+  if (row < P.d) {
+    xr = src[2 * row];
+    xi = src[2 * row + 1];
+  }
+  cpx<T>* store = reinterpret_cast<cpx<T>*>(bwd ? P.lam : P.psi);
+  if (cg == 0 && store) vec_put(store, (size_t)(bwd ? P.N : 0) * D + row, (T)xr, (T)xi);
+  constexpr int AHEAD = sizeof(T) * CPT <= 64 ? 4 : 2;  // totals in registers
+  const double sgn = bwd ? -1.0 : 1.0;
+  T nr[AHEAD][CPT], ni[AHEAD][CPT];
+  auto load = [&](int step, int q) {
+    if (step >= P.P) return;
+    const T* M = static_cast<const T*>(P.tf) + (size_t)(bwd ? P.P - 1 - step : step) * 2 * D * D;
+#pragma unroll
+    for (int v = 0; v < CPT / 4; ++v) {  // columns 16 v + 4 cg ... of the row
+      const int col = 16 * v + 4 * cg;
+      if (bwd) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          nr[q][4 * v + i] = gp(M)[(col + i) * D + row];
+          ni[q][4 * v + i] = gp(M)[D * D + (col + i) * D + row];
+        }
+      } else {
+        const typename Prec<T>::v4 a = Prec<T>::gld4(M + row * D + col), b = Prec<T>::gld4(M + D * D + row * D + col);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          nr[q][4 * v + i] = a[i];
+          ni[q][4 * v + i] = b[i];
+        }
+      }
+    }
+  };
+#pragma unroll
+  for (int q = 0; q < AHEAD; ++q) load(q, q);
+  for (int s0 = 0; s0 < P.P; s0 += AHEAD)
+#pragma unroll
+  for (int q = 0; q < AHEAD; ++q) {
+    const int step = s0 + q, buf = q & 1;
+    if (step >= P.P) break;
+    if (cg == 0) {
+      zb[buf][0][row] = xr;
+      zb[buf][1][row] = xi;
+    }
+    lds_barrier();  // (the totals of later steps keep loading)
+    double yr = 0, yi = 0;
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      const int col = 16 * (i / 4) + 4 * cg + i % 4;
+      const double zr = zb[buf][0][col], zi = zb[buf][1][col], a = (double)nr[q][i], b = sgn * (double)ni[q][i];
+      yr = fma(a, zr, yr);
+      yi = fma(a, zi, yi);
+      yr = fma(-b, zi, yr);
+      yi = fma(b, zr, yi);
+    }
+    load(step + AHEAD, q);
+#pragma unroll
+    for (int o = TPR / 2; o > 0; o >>= 1) {
+      yr += __shfl_xor(yr, o, 64);
+      yi += __shfl_xor(yi, o, 64);
+    }
+    xr += yr;
+    xi += yi;
+    const int c = bwd ? P.P - 1 - step : step;
+    if (cg == 0 && store)
+      vec_put(store, (size_t)(bwd ? c * P.L : min(P.N, (c + 1) * P.L)) * D + row, (T)xr, (T)xi);
+  }
+  if (!bwd) state_end<double, D>(P, row, cg, xr, xi, red);
+}
+
+// One workgroup per (problem, direction, chunk).  Forward: psi_0 -> psi_N, storing
 // every psi_k, then g, F (and psi_N when asked for).  Backward: chi -> lam_0,
-// storing every lam_k.  Each slice is applied as T_q(+-A_k/R)^R.
+// storing every lam_k.  Each slice is applied as T_q(+-A_k/R)^R.  Of several
+// chunks each starts from the state that k_state_top stored at its end and
+// leaves out its last slice, whose result is the neighbour's start.
 // MONO: the row-table path (every control has at most one nonzero per row, at
 // most kStateMonoMax controls) or the dense one; both are launched and each
 // workgroup leaves at once when its problem takes the other.
@@ -314,6 +434,9 @@ __global__ __launch_bounds__(SV<D>::NT) void k_state_chain(StateWork W) {
   const int d = P.d, m = P.m, N = P.N;
   if (state_mono<D>(P) != MONO) return;
   constexpr bool mono = MONO;
+  const bool whole = P.P == 1;
+  const int k0 = blockIdx.z * P.L, k1 = min(N, k0 + P.L);  // whole: L = N
+  const int steps = whole ? N : k1 - k0 - 1;
   HRow<T, D> H;
   CtlRegs<T, D> CR;
   if constexpr (MONO) {
@@ -325,21 +448,25 @@ __global__ __launch_bounds__(SV<D>::NT) void k_state_chain(StateWork W) {
   // the chain's vector: x[row], held by every lane of the row group
   const double* src = bwd ? P.chiz : P.psi0z;
   T xr = 0, xi = 0;
-  if (row < d) {
-    xr = (T)src[2 * row];
-    xi = (T)src[2 * row + 1];
-  }
   cpx<T>* store = reinterpret_cast<cpx<T>*>(bwd ? P.lam : P.psi);
-  if (cg == 0 && store) vec_put(store, (size_t)(bwd ? N : 0) * D + row, xr, xi);
+  if (whole) {
+    if (row < d) {
+      xr = (T)src[2 * row];
+      xi = (T)src[2 * row + 1];
+    }
+    if (cg == 0 && store) vec_put(store, (size_t)(bwd ? N : 0) * D + row, xr, xi);
+  } else {
+    vec_get(store, (size_t)(bwd ? k1 : k0) * D + row, xr, xi);
+  }
   int buf = 0;
-  for (int step = 0; step < N; ++step) {
-    const int k = bwd ? N - 1 - step : step;
+  for (int step = 0; step < steps; ++step) {
+    const int k = bwd ? k1 - 1 - step : k0 + step;
     const int bi = step % kChainBlock;  // position in the block of slices staged in LDS
     if (bi == 0) {
       // the plans (and, on the row-table path, the amplitudes) of the next
       // kChainBlock slices in chain order: one round trip per block
       __syncthreads();  // the previous block's entries have been read
-      const int nb = min(kChainBlock, N - step);
+      const int nb = min(kChainBlock, steps - step);
       for (int e = threadIdx.x; e < nb; e += SV<D>::NT) sqb[e] = gp(P.sq)[bwd ? k - e : k + e];
       if constexpr (MONO)
         for (int e = threadIdx.x; e < m * nb; e += SV<D>::NT) {
@@ -358,7 +485,7 @@ __global__ __launch_bounds__(SV<D>::NT) void k_state_chain(StateWork W) {
       T dr = 0, di = 0;  // delta
       for (int i = q; i >= 1; --i) {
         if (cg == 0) zb[buf][row] = cpx<T>{xr + dr, xi + di};
-        __syncthreads();
+        lds_barrier();  // (the store of the last state keeps going)
         T yr, yi;
         row_apply_r<T, D>(H, zb[buf], mono ? &CR : nullptr, cg, yr, yi);
         const T f = (T)(c / i);
@@ -371,26 +498,7 @@ __global__ __launch_bounds__(SV<D>::NT) void k_state_chain(StateWork W) {
     }
     if (cg == 0 && store) vec_put(store, (size_t)(bwd ? k : k + 1) * D + row, xr, xi);
   }
-  if (!bwd) {
-    // g = <chi|psi_N> in FP64
-    double gr = 0, gi = 0;
-    if (row < d) {
-      const double cr = P.chiz ? P.chiz[2 * row] : 0.0, ci = P.chiz ? P.chiz[2 * row + 1] : 0.0;
-      gr = cr * (double)xr + ci * (double)xi;
-      gi = cr * (double)xi - ci * (double)xr;
-    }
-    gr = rows_sum<D>(gr, red);
-    gi = rows_sum<D>(gi, red + NW);
-    if (threadIdx.x == 0 && P.chiz) {
-      P.g[0] = gr;
-      P.g[1] = gi;
-      P.F[0] = gr * gr + gi * gi;
-    }
-    if (P.XN && cg == 0 && row < d) {
-      P.XN[2 * row] = (double)xr;
-      P.XN[2 * row + 1] = (double)xi;
-    }
-  }
+  if (!bwd && whole) state_end<T, D>(P, row, cg, xr, xi, red);
 }
 
 // ---------------------------------------------------------------- gradient
@@ -489,15 +597,13 @@ __global__ __launch_bounds__(SV<D>::NT) void k_state_grad(StateWork W) {
           const int col = ctl.col[e];
           const double hr = (double)ctl.val[e].re, hi = (double)ctl.val[e].im;
           double sr = 0, si = 0;
-          double f0 = 1.0;  // 1 / (i + 1)!
           for (int i = 0; i < qbe; ++i) {
-            f0 /= (double)(i + 1);
             // w = sum_{l <= qb - 1 - i} b_l[col] / (i + l + 1)!
-            double wr = 0, wi = 0, f = f0;
+            double wr = 0, wi = 0;
             for (int l = 0; l + i < qbe; ++l) {
+              const double f = kInvFact.v[i + l + 1];
               wr += f * (double)bv[l][col].re;
               wi += f * (double)bv[l][col].im;
-              f /= (double)(i + l + 2);
             }
             // conj(a_i[row]) * val * w
             const double ar = (double)av[i][row].re, ai = (double)av[i][row].im;
@@ -516,18 +622,15 @@ __global__ __launch_bounds__(SV<D>::NT) void k_state_grad(StateWork W) {
         HRow<T, D> C;
         row_load<T, D>(C.re, C.im, Hint + (size_t)(j + 1) * 2 * D * D, row, cg * CPT);
         double sr = 0, si = 0;
-        double f0 = 1.0;  // 1 / (l + 1)!
         for (int l = 0; l < qbe; ++l) {
           T hr, hi;
           row_apply<T, D>(C, bv[l], nullptr, us, 0, row, cg, hr, hi);
-          f0 /= (double)(l + 1);
           // sum_{i <= qb - 1 - l} conj(a_i[row]) / (i + l + 1)!
-          double f = f0;
           double wr = 0, wi = 0;
           for (int i = 0; i + l < qbe; ++i) {
+            const double f = kInvFact.v[i + l + 1];
             wr += f * (double)av[i][row].re;
             wi += f * (double)av[i][row].im;
-            f /= (double)(i + l + 2);
           }
           sr += wr * (double)hr + wi * (double)hi;
           si += wr * (double)hi - wi * (double)hr;
@@ -601,11 +704,20 @@ __global__ __launch_bounds__(SV<D>::NT) void k_state_grad(StateWork W) {
 }
 
 template <typename T, int D>
-static hipError_t launch_state(const StateWork& W, int B, int N, int grad, hipStream_t st) {
-  const dim3 cg(B, grad ? 2 : 1), gg(B * ((N + kGradSlices - 1) / kGradSlices)), nt(SV<D>::NT);
+static hipError_t launch_state(const StateWork& W, int B, int N, int chunks, int grad, hipStream_t st) {
+  const dim3 cg(B, grad ? 2 : 1, chunks), gg(B * ((N + kGradSlices - 1) / kGradSlices)), nt(SV<D>::NT);
   stage_mark(ST_SCHAIN, true, st);
-  hipLaunchKernelGGL((k_state_chain<T, D, true>), cg, nt, 0, st, W);
-  hipLaunchKernelGGL((k_state_chain<T, D, false>), cg, nt, 0, st, W);
+  if constexpr (D <= 64) {
+    if (chunks > 1) {
+      const hipError_t e = launch_state_totals(sizeof(T) == 8 ? 0 : 1, D, W.descs, B, chunks, st);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((k_state_top<T, D>), dim3(B, cg.y), nt, 0, st, W);
+    }
+  }
+  if (grad || chunks == 1) {  // (the states inside the chunks are the gradient's)
+    hipLaunchKernelGGL((k_state_chain<T, D, true>), cg, nt, 0, st, W);
+    hipLaunchKernelGGL((k_state_chain<T, D, false>), cg, nt, 0, st, W);
+  }
   stage_mark(ST_SCHAIN, false, st);
   if (grad) {
     stage_mark(ST_SGRAD, true, st);
@@ -616,21 +728,21 @@ static hipError_t launch_state(const StateWork& W, int B, int N, int grad, hipSt
   return hipGetLastError();
 }
 
-static hipError_t launch_state_path(int precision, int D, const StateWork& W, int B, int N, int grad,
-                                    hipStream_t st) {
+static hipError_t launch_state_path(int precision, int D, const StateWork& W, int B, int N, int chunks,
+                                    int grad, hipStream_t st) {
   if (precision == 0) {
     switch (D) {
-      case 16: return launch_state<double, 16>(W, B, N, grad, st);
-      case 32: return launch_state<double, 32>(W, B, N, grad, st);
-      case 64: return launch_state<double, 64>(W, B, N, grad, st);
-      case 128: return launch_state<double, 128>(W, B, N, grad, st);
+      case 16: return launch_state<double, 16>(W, B, N, chunks, grad, st);
+      case 32: return launch_state<double, 32>(W, B, N, chunks, grad, st);
+      case 64: return launch_state<double, 64>(W, B, N, chunks, grad, st);
+      case 128: return launch_state<double, 128>(W, B, N, chunks, grad, st);
     }
   } else if (precision == 1) {
     switch (D) {
-      case 16: return launch_state<float, 16>(W, B, N, grad, st);
-      case 32: return launch_state<float, 32>(W, B, N, grad, st);
-      case 64: return launch_state<float, 64>(W, B, N, grad, st);
-      case 128: return launch_state<float, 128>(W, B, N, grad, st);
+      case 16: return launch_state<float, 16>(W, B, N, chunks, grad, st);
+      case 32: return launch_state<float, 32>(W, B, N, chunks, grad, st);
+      case 64: return launch_state<float, 64>(W, B, N, chunks, grad, st);
+      case 128: return launch_state<float, 128>(W, B, N, chunks, grad, st);
     }
   }
   return hipErrorInvalidValue;
@@ -654,9 +766,25 @@ int sfail(int code, const char* fmt, ...) {
   return code;
 }
 
+// Slices per chunk: the chunks' propagators cost matrix products (B N D^3 of
+// them in all) and shorten the chain of N slices to about 2 sqrt(8 N) steps, so
+// the line is the batch at which single chains would fill the chip as well.
+// N = 500, gradient, single chain -> chunked (ms): FP32 d = 16, B = 512 1.60 ->
+// 1.19; d = 32, B = 256 2.33 -> 1.72; d = 64, B = 64 2.36 -> 1.68, B = 16 1.78 ->
+// 0.58.  FP64 d = 16, B = 512 5.1 -> 4.1; d = 32, B = 64 3.8 -> 2.7, B = 256 7.2 ->
+// 9.5; d = 64, B = 16 4.9 -> 3.3, B = 64 9.8 -> 13.1.  Below 64 slices the chunks
+// are too short to gain.
+int state_chunk(int B, int D, int N, int precision) {
+  const bool f64 = precision == QOC_FP64;
+  const int most = D == 16 ? 512 : D == 32 ? (f64 ? 96 : 256) : f64 ? 32 : 64;
+  if (D > 64 || B > most || N < 64) return N;
+  return qoc::engine_chunk(N);
+}
+
 struct StateLayout {
   int D;
-  size_t esize, desc_bytes, Hint, norms, mono, sq, psi, lam, small, per_prob, total;
+  int L, P;  // slices per chunk, chunks (1: one chain through all slices)
+  size_t esize, desc_bytes, Hint, norms, mono, sq, psi, lam, tf, small, per_prob, total;
 };
 
 StateLayout make_state_layout(int B, int d, int m, int N, int precision) {
@@ -672,6 +800,9 @@ StateLayout make_state_layout(int B, int d, int m, int N, int precision) {
   Lo.sq = o; o = align_up(o + (size_t)N * 4);
   Lo.psi = o; o = align_up(o + (size_t)(N + 1) * vec);
   Lo.lam = o; o = align_up(o + (size_t)(N + 1) * vec);
+  Lo.L = state_chunk(B, Lo.D, N, precision);
+  Lo.P = (N + Lo.L - 1) / Lo.L;
+  Lo.tf = o; o = align_up(o + (Lo.P > 1 ? (size_t)Lo.P * mat : 0));
   Lo.small = o; o = align_up(o + 128);
   Lo.per_prob = o;
   Lo.desc_bytes = align_up((size_t)B * sizeof(ProbDesc));
@@ -723,8 +854,9 @@ int run_state_dev(int B, int d, int m, int N, const void* H0, const void* Hc, co
     P.D = Lo.D;
     P.m = m;
     P.N = N;
-    P.L = N;
-    P.P = 1;
+    P.L = Lo.L;
+    P.P = Lo.P;
+    P.tf = pb + Lo.tf;
     P.CG = P.PG = 1;
     P.flags = flags;
     P.dt = dt;
@@ -771,7 +903,7 @@ int run_state_dev(int B, int d, int m, int N, const void* H0, const void* Hc, co
   if (e == hipSuccess) e = qoc::launch_stage(opt.precision, Lo.D, qoc::ST_PLAN, L, all);
   if (e == hipSuccess) {
     const qoc::StateWork W = {L.descs, B, flags};
-    e = qoc::launch_state_path(opt.precision, Lo.D, W, B, N, with_grad ? 1 : 0, st);
+    e = qoc::launch_state_path(opt.precision, Lo.D, W, B, N, Lo.P, with_grad ? 1 : 0, st);
   }
   if (e != hipSuccess) return sfail(QOC_ERR_DEVICE, "kernel launch: %s", hipGetErrorString(e));
   return QOC_OK;
