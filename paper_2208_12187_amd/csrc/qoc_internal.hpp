@@ -183,8 +183,10 @@ inline int engine_chunk(int N) { return std::max(1, (int)ceil(sqrt(N / 8.0))); }
 // Segments of a chunk of L slices (Hermitian path at D <= 64), and slices per
 // segment: at most kSegMax, as even as they come.
 constexpr int kSegMax = 8;
-__host__ __device__ inline int seg_max(int D) { return D == 16 ? 2 : D == 128 ? 4 : kSegMax; }
-__host__ __device__ inline int seg_count(int D, int L) { return (L + seg_max(D) - 1) / seg_max(D); }
+__host__ __device__ inline int seg_max(int D, int L) {
+  return D == 16 || L <= (D == 128 ? 12 : 16) ? 2 : D == 128 || L <= 24 ? 4 : kSegMax;
+}
+__host__ __device__ inline int seg_count(int D, int L) { return (L + seg_max(D, L) - 1) / seg_max(D, L); }
 __host__ __device__ inline int seg_len(int D, int L) { return (L + seg_count(D, L) - 1) / seg_count(D, L); }
 
 // The carry over the P chunk totals runs in groups of CG =

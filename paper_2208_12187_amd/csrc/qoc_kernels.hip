@@ -1585,7 +1585,8 @@ __device__ __forceinline__ SegItem seg_split(int item, const Range& rg, const It
 template <typename T, int D>
 struct SegTab {
   // two workgroups of the d = 64 FP32 gradient kernel share a CU's 160 KB
-  static constexpr int ENT = (sizeof(T) == 4 && D == 64) ? 12 * D : 16 * D;
+  // (four of the d = 32 FP64 one)
+  static constexpr int ENT = (sizeof(T) == 4 && D == 64) ? 12 * D : (sizeof(T) == 8 && D == 32) ? 10 * D : 16 * D;
   static constexpr int MAXM = ENT / D;
   T vr[ENT], vi[ENT];
   unsigned char col[ENT];
@@ -1838,8 +1839,9 @@ template <typename T, int D, typename Ops, bool PERSIST>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_seg_fwd(Work W) {
   using Std = StdOps<T, D>;
   constexpr T CI = (T)1 / Ops::C;
-  __shared__ __align__(16) unsigned char la[Ops::BYTES];
-  __shared__ __align__(16) unsigned char lb[Std::BYTES];
+  // one buffer for the assembly and every left factor: at d = 32 in FP64 two
+  // would leave a CU six wavefronts
+  __shared__ __align__(16) unsigned char la[Ops::BYTES > Std::BYTES ? Ops::BYTES : Std::BYTES];
   __shared__ SegTab<T, D> tab;
   Lane L;
   const Items I(W);
@@ -1853,7 +1855,7 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
       for (int k = g.ka; k < g.kb; ++k) {
         int s, q, qb;
         unpack_sq(gp(P.sq)[k], s, q, qb);
-        assemble_panel<T, D>(X, lb, P, k, ldexp(P.dt * (double)Ops::C, -s), mono, tb, k - g.ka, L);
+        assemble_panel<T, D>(X, la, P, k, ldexp(P.dt * (double)Ops::C, -s), mono, tb, k - g.ka, L);
         Ops::store_nct(la, X, L);  // X = -X^dag
         __syncthreads();
         taylor_delta<T, D, Ops>(R, X, la, s, q, L);
@@ -1862,9 +1864,10 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
           S = R;
           panel_add_identity(S, L, (T)1);
         } else {
-          Std::store(lb, R, L);  // (every wavefront has left assemble_panel)
+          __syncthreads();  // the exponential's last left factor has been read
+          Std::store(la, R, L);
           __syncthreads();
-          Std::gemm3(X, lb, S, L, true);
+          Std::gemm3(X, la, S, L, true);
           panel_fma(S, (T)1, X);  // S <- S + Delta S
         }
       }
@@ -2092,8 +2095,7 @@ __device__ __forceinline__ void conjugate_by(Panel<T, D>& Y, T f, void* lds0, vo
 // every slice (133 of them spilled at d = 64 in FP32).
 template <typename T, int D, typename Ops, bool SQ>
 __device__ __forceinline__ void seg_grad_body(const ProbDesc& P, int c, int sg, int ka, int kb, int kbase, int part,
-                                              bool mono, void* la, void* lb, SegTab<T, D>& tab, double* red,
-                                              const Lane& L) {
+                                              bool mono, void* la, void* lb, SegTab<T, D>& tab, const Lane& L) {
   constexpr T C = Ops::C, CI = (T)1 / Ops::C;
   T* pt = static_cast<T*>(lb);  // planar
   const SegTab<T, D>* tb = seg_tab_load<T, D>(tab, P, ka, kb, mono) ? &tab : nullptr;
@@ -2174,7 +2176,9 @@ __device__ __forceinline__ void seg_grad_body(const ProbDesc& P, int c, int sg, 
     __syncthreads();
     panel_to_lds_ct(pt, Z, L);  // Z = Z^dag
     __syncthreads();
-    seg_epilogue<T, D>(P, k, part, pt, (double)CI, tb, red, mono, L);
+    // (A is no longer needed: its buffer takes the sums)
+    static_assert(2 * kSegEpi * (D / 16) * 8 <= Ops::BYTES, "sums");
+    seg_epilogue<T, D>(P, k, part, pt, (double)CI, tb, static_cast<double*>(la), mono, L);
   }
 }
 
@@ -2185,7 +2189,6 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
   __shared__ __align__(16) unsigned char la[Ops::BYTES];
   __shared__ __align__(16) unsigned char lb[LB];
   __shared__ SegTab<T, D> tab;
-  __shared__ double red[2 * kSegEpi * (D / 16)];
   Lane L;
   const Items I(W);
   for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
@@ -2194,7 +2197,7 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
       const ProbDesc P = W.descs[I.desc(g.p)];  // a copy: stores cannot alias it
       const bool mono = (gp(P.sq)[g.ka] & kPlanMono) != 0;
       if (gp(P.squared)[0] == 0)
-        seg_grad_body<T, D, Ops, false>(P, g.c, g.s, g.ka, g.kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, red, L);
+        seg_grad_body<T, D, Ops, false>(P, g.c, g.s, g.ka, g.kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, L);
     }
     if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
     __syncthreads();
@@ -2209,7 +2212,6 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
   __shared__ __align__(16) unsigned char la[Ops::BYTES];
   __shared__ __align__(16) unsigned char lb[LB];
   __shared__ SegTab<T, D> tab;
-  __shared__ double red[2 * kSegEpi * (D / 16)];
   Lane L;
   const Items I(W);
   const int per = max(1, (int)gridDim.x / max(I.nprob, 1));  // workgroups of a problem
@@ -2225,7 +2227,7 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
       const int ka = c * P.L + sg * h, kb = min(min(P.N, (c + 1) * P.L), ka + h);
       if (ka >= kb) continue;
       const bool mono = (gp(P.sq)[ka] & kPlanMono) != 0;
-      seg_grad_body<T, D, Ops, true>(P, c, sg, ka, kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, red, L);
+      seg_grad_body<T, D, Ops, true>(P, c, sg, ka, kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, L);
       __syncthreads();
     }
   }
