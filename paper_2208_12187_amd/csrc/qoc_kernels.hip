@@ -2686,13 +2686,6 @@ __device__ __forceinline__ void gradient_epilogue128(const ProbDesc& P, int k, c
   }
 }
 
-// FP32 keeps X2 = (A_k / 2^s)^2 for the adjoint (where the workspace has room
-// for it); in FP64 the expm runs Horner and the adjoint forms X2 itself.  For
-// Hermitian H_k the adjoint's X = A_k^dag / 2^s = -A_k / 2^s has the same
-// square.
-template <typename T>
-constexpr bool kKeepX2 = sizeof(T) == 4;
-
 template <typename T>
 __device__ __forceinline__ T* slot_mat(void* scratch, int i) {
   return reinterpret_cast<T*>(scratch) + ((size_t)blockIdx.x * kScratchMats + i) * K128<T>::ELEMS;
@@ -2704,6 +2697,7 @@ __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
   Lane L;
   T* SX = slot_mat<T>(scratch, 0);
   T* SR = slot_mat<T>(scratch, 1);
+  T* S2 = slot_mat<T>(scratch, 2);
   const Items I(W);
   for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
     int p, k;
@@ -2717,64 +2711,42 @@ __global__ __launch_bounds__(512) void k_expm128(Work W, void* scratch) {
     // For the adjoint: X = A_k / 2^s in PF layout (its X, A_k^dag / 2^s, is
     // the exact negation), one coalesced store of this wavefront's panel.
     if (P.flags & RUN_GRAD) panel_store(pf_mat<T, 128>(P.hk, k - W.rg.kbase), acc, L);
-    // FP32: Paterson-Stockmeyer with X2 = X X as the step, X2 in slot 2 (and
-    // kept for the adjoint in gradient runs), C in SR:
+    // Paterson-Stockmeyer with X2 = X X as the step, X2 in slot 2, C in SR:
     //   p(X) - I = X + X2 C,  C = sum_{n=2..q} X^(n-2) / n!,  C <- D_t + X2 C,
     //   D_t = I / (2t+2)! + X / (2t+3)!
-    // (as k_adjoint's block polynomial): expm_products(q) products instead
-    // of Horner's q - 1, and X2 on the way.  (Taking X2 from Horner's first
-    // product as k_expm does cost this kernel more in scratch traffic than
-    // the products it saves.)  FP64, whose kernels spill, runs Horner.
-    if (sizeof(T) == 4 && q >= 2) {
-      T* S2 = slot_mat<T>(scratch, 2);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SX, L, true);
-      if (q == 2) {
-        panel_scale(acc, (T)0.5);
-        panel_axpy_pf(acc, (T)1, SX, L);  // X + X2 / 2
-      } else {
-        panel_store(S2, acc, L);
-        const int top = (q - 2) / 2;
-        int t;
-        if (q & 1) {  // C = I / (q-1)! + X / q!
-          t = top - 1;
-          panel_load(acc, SX, L);
-          panel_scale(acc, (T)inv_factorial(q));
-          panel_add_identity(acc, L, (T)inv_factorial(q - 1));
-        } else {  // C = I / (q-2)! + X / (q-1)! + X2 / q!
-          t = top - 2;
-          panel_scale(acc, (T)inv_factorial(q));
-          panel_axpy_pf(acc, (T)inv_factorial(q - 1), SX, L);
-          panel_add_identity(acc, L, (T)inv_factorial(q - 2));
-        }
-        panel_store(SR, acc, L);
-        bool staged = false;  // X2 already in LDS (from the previous product)
-        for (; t >= 0; --t) {  // C <- D_t + X2 C
-          panel_load(acc, SX, L);
+    // (as k_adjoint's block polynomial): expm_products(q) products, then s
+    // squarings, all by one instance of the product.  (Inlined at each of its
+    // uses it left FP64 276 spilled registers, which cost more than the products
+    // that Horner's rule takes beyond these.)
+    const int n = expm_products(q), top = (q - 2) / 2;
+    const bool even = (q & 1) == 0;
+    if (n == 0 && s > 0) panel_store(SR, acc, L);
+#pragma unroll 1
+    for (int i = 0; i < n + s; ++i) {
+      const bool square = i >= n, inner = i > 0 && i < n;
+      const int t = (even ? top - 1 : top) - i;  // inner: D_t, X at the last
+      if (inner) {
+        panel_load(acc, SX, L);
+        if (i < n - 1) {
           panel_scale(acc, (T)inv_factorial(2 * t + 3));
           panel_add_identity(acc, L, (T)inv_factorial(2 * t + 2));
-          gemm128<T, false, k128Gauss<T>>(acc, lds, S2, SR, L, false, !staged);
-          staged = true;
-          panel_store(SR, acc, L);
         }
-        panel_load(acc, SX, L);
-        gemm128<T, false, k128Gauss<T>>(acc, lds, S2, SR, L, false, !staged);  // X + X2 C
       }
-    } else if (q >= 2) {
-      panel_scale(acc, (T)(1.0 / q));
-      panel_add_identity(acc, L, (T)1);
-      panel_store(SR, acc, L);
-      for (int i = q - 1; i >= 2; --i) {
-        gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SR, L, true);
-        panel_scale(acc, (T)(1.0 / i));
-        panel_add_identity(acc, L, (T)1);
-        panel_store(SR, acc, L);
+      gemm128<T, false, k128Gauss<T>>(acc, lds, square ? SR : (inner ? S2 : SX), square || inner ? SR : SX, L, !inner,
+                                      i < 2 || !inner);
+      if (square) {
+        panel_axpy_pf(acc, (T)2, SR, L);
+      } else if (i == 0 && q == 2) {
+        panel_scale(acc, (T)0.5);
+        panel_axpy_pf(acc, (T)1, SX, L);  // X + X2 / 2
+      } else if (i == 0) {
+        // C = I / (q-2)! + X / (q-1)! + X2 / q! or I / (q-1)! + X / q!
+        panel_store(S2, acc, L);
+        panel_scale(acc, even ? (T)inv_factorial(q) : (T)0);
+        panel_axpy_pf(acc, (T)inv_factorial(even ? q - 1 : q), SX, L);
+        panel_add_identity(acc, L, (T)inv_factorial(even ? q - 2 : q - 1));
       }
-      gemm128<T, false, k128Gauss<T>>(acc, lds, SX, SR, L, true);
-    }
-    for (int j = 0; j < s; ++j) {
-      panel_store(SR, acc, L);
-      gemm128<T, false, k128Gauss<T>>(acc, lds, SR, SR, L, true);
-      panel_axpy_pf(acc, (T)2, SR, L);
+      if (i + 1 < n + s) panel_store(SR, acc, L);
     }
     panel_store(pf_mat<T, 128>(P.delta, k - W.rg.kbase), acc, L);
   }
@@ -3419,7 +3391,7 @@ static void stage_128(int stage, const Launch& L, const Range& rg, double ur) {
     case ST_PLAN: {
       Work w = L.dyn ? dyn : slice_work(L, all);
       hipLaunchKernelGGL(k_plan, dim3(L.dyn ? L.dyn_grid : (w.total + 255) / 256), dim3(256), 0, st, w, ur,
-                         grad | (sizeof(T) == 4 ? PLAN_PS : 0));
+                         grad | PLAN_PS);
       break;
     }
     case ST_EXPM: {
