@@ -120,8 +120,8 @@ constexpr int kPlanMono = 1 << 25;
 // A wavefront reads whole rows (64 / D of them at once, or half a row at a time
 // at D = 128), so that a matrix takes D^2 / 256 coalesced loads per thread with
 // no dependence between rows: latency-bound, one round trip deep (one thread
-// per row or column walked D dependent steps: 46 us at d = 64 and 128 us at
-// d = 128, now 6 and 11).
+// per row or column walked D dependent steps: one problem of d = 64, m = 12 took
+// 46 us, now 15; eight of d = 128, m = 14 take 86).
 template <typename T, int D>
 __device__ __forceinline__ void prep_one(const ProbDesc& P, int mat, double* colmax) {
   const int d = P.d, m = P.m;
@@ -811,12 +811,12 @@ constexpr int kExpmPairs = sizeof(T) == 4 ? 2 : 1;
 // The FP32 d = 64 expm (one slice per workgroup) takes a floor of four waves
 // per SIMD: it needs 130 VGPRs otherwise, and at 128 (two spilled) four
 // workgroups share a CU instead of three (expm 1.88 -> 1.80 ms on the d = 64
-// batch of 32).  The engine's persistent instance keeps the floor of two.
-template <typename T, int D, bool PERSIST>
-constexpr int kExpmWaves = (sizeof(T) == 4 && D == 64 && !PERSIST) ? 4 : kMinWaves<D>;
+// batch of 32).
+template <typename T, int D>
+constexpr int kExpmWaves = (sizeof(T) == 4 && D == 64) ? 4 : kMinWaves<D>;
 
-template <typename T, int D, typename Ops, bool PERSIST>
-__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kExpmWaves<T, D, PERSIST>)))
+template <typename T, int D, typename Ops>
+__global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kExpmWaves<T, D>)))
 void k_expm(Work W) {
   __shared__ __align__(16) unsigned char lds[Ops::BYTES];
   Lane L;
@@ -853,7 +853,7 @@ void k_expm(Work W) {
     panel_axpby(R, (T)1, acc, (T)2);
   }
   panel_store(pf_mat<T, D>(P.delta, k - W.rg.kbase), R, L);
-  if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
+  break;  // one item per workgroup: a single-trip loop
   __syncthreads();
   }
 }
@@ -952,7 +952,7 @@ __device__ __forceinline__ void reunitarise(const ProbDesc& P, Panel<float, D>& 
 template <typename T, int D>
 constexpr int kScanBufs = (sizeof(T) == 4 && D == 64) ? 1 : 2;
 
-template <typename T, int D, typename Ops, bool PERSIST>
+template <typename T, int D, typename Ops>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kMinWaves<D>)))
 void k_scan_local(Work W, int dir) {
   __shared__ __align__(16) unsigned char lds[kScanBufs<T, D>][Ops::BYTES];
@@ -985,7 +985,7 @@ void k_scan_local(Work W, int dir) {
     k = kn;
   }
   if (!bwd && !W.rg.recompute) panel_store(pf_mat<T, D>(P.tf, c), S, L);  // (k_reun follows in FP32)
-  if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
+  break;  // one item per workgroup: a single-trip loop
   __syncthreads();
   }
 }
@@ -1380,15 +1380,15 @@ constexpr bool kEarlyH = (sizeof(T) == 4 && D == 64) || (sizeof(T) == 8 && D == 
 // instances split the slices: MODE 1 takes those where it does not apply,
 // MODE 2 those where it does (s = 0, permutation controls), each returning at
 // once for the others, so that neither carries the other's registers.
-template <typename T, int D, typename Ops, bool PERSIST, int MODE = 0>
+template <typename T, int D, typename Ops, int MODE = 0>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kAdjWaves<T, D>)))
 void k_adjoint(Work W) {
   constexpr int NW = Mat<T, D>::NW;
   constexpr int AP = MODE == 2 ? 2 : 1;  // accumulator chain pairs of the sampling instance's products
   __shared__ __align__(16) unsigned char lds[2][Ops::BYTES];
   __shared__ double red[2 * kEpiDense * 2 * NW];
-  // sample_gather (not in the persistent grid, whose registers it would spill)
-  constexpr bool GATHER = MODE == 2 && !PERSIST;
+  // sample_gather
+  constexpr bool GATHER = MODE == 2;
   __shared__ __align__(16) float eg[GATHER ? 2 * kSampleGather * D : 1];
   Lane L;
   const Items I(W);
@@ -1401,10 +1401,7 @@ void k_adjoint(Work W) {
   unpack_sq(sqk, s, q, qb);
   if constexpr (MODE != 0) {
     const bool sampled = (sqk & kPlanSampled) != 0;  // uniform over the workgroup
-    if (sampled != (MODE == 2)) {
-      if constexpr (PERSIST) continue;
-      else return;
-    }
+    if (sampled != (MODE == 2)) return;
   }
   const bool mono = (sqk & kPlanMono) != 0;
   Panel<T, D> R1, R2, A1, A2;
@@ -1519,7 +1516,7 @@ void k_adjoint(Work W) {
   // 5. inner products with the controls (FP64), then the gradient
   gradient_epilogue<T, D>(P, k, A2, L, lds[0], red, mono);
   }
-  if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
+  break;  // one item per workgroup: a single-trip loop
   __syncthreads();
   }
 }
@@ -3250,7 +3247,7 @@ static void stage_small(int stage, const Launch& L, const Range& rg, double ur) 
     }
     case ST_EXPM: {
       Work w = slice_work(L, rg);
-      hipLaunchKernelGGL((k_expm<T, D, Std, false>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
+      hipLaunchKernelGGL((k_expm<T, D, Std>), dim3(grid_of(L, w.total, 0)), dim3(NT), 0, st, w);
       break;
     }
     case ST_SCAN:
@@ -3261,7 +3258,7 @@ static void stage_small(int stage, const Launch& L, const Range& rg, double ur) 
       const bool both = stage == ST_SCAN && rg.recompute;
       const int dir = stage == ST_BSCAN ? 1 : (both ? -1 : 0);
       const dim3 grid(grid_of(L, w.total, 0), both ? 2 : 1);
-      hipLaunchKernelGGL((k_scan_local<T, D, Std, false>), grid, dim3(NT), 0, st, w, dir);
+      hipLaunchKernelGGL((k_scan_local<T, D, Std>), grid, dim3(NT), 0, st, w, dir);
       break;
     }
     case ST_MC: {
@@ -3273,10 +3270,10 @@ static void stage_small(int stage, const Launch& L, const Range& rg, double ur) 
       Work w = slice_work(L, rg);
       const dim3 grid(grid_of(L, w.total, 0));
       if constexpr (kSampleLast<T, D, Ops>) {
-        hipLaunchKernelGGL((k_adjoint<T, D, Ops, false, 2>), grid, dim3(NT), 0, st, w);
-        hipLaunchKernelGGL((k_adjoint<T, D, Ops, false, 1>), grid, dim3(NT), 0, st, w);
+        hipLaunchKernelGGL((k_adjoint<T, D, Ops, 2>), grid, dim3(NT), 0, st, w);
+        hipLaunchKernelGGL((k_adjoint<T, D, Ops, 1>), grid, dim3(NT), 0, st, w);
       } else {
-        hipLaunchKernelGGL((k_adjoint<T, D, Ops, false>), grid, dim3(NT), 0, st, w);
+        hipLaunchKernelGGL((k_adjoint<T, D, Ops>), grid, dim3(NT), 0, st, w);
       }
       break;
     }
@@ -3523,7 +3520,8 @@ hipError_t launch_stage(int precision, int D, int stage, const Launch& L, const 
 // dropped): of the chunk's errors only the products' stay, which scale with A_k.
 // Each slice's factor also carries a scale of its own between 1 and 3/2: the
 // entries that are the same in every slice then round differently in each, and
-// their errors do not add up over the N slices.
+// their errors do not add up over the N slices.  1.04 ms at d = 64, m = 12, N =
+// 2000, 32 problems in FP32: q products per slice on the FP16 matrix cores.
 template <typename T, int D, typename Ops>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_state_total(
     const ProbDesc* descs, int chunks) {
