@@ -23,7 +23,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 METRIC = "GRAPE slice-steps/s (fwd+grad, d=64) vs plain FP64; p50/p99 request latency"
-PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16x3": 2500.0}
+# dense matrix-core peaks of the adjoint kernel's products: FP64, and FP16 in FP32 and
+# split BF16 (Hermitian Hamiltonians)
+PEAK_TFLOPS = {"fp64": 78.6, "fp32": 2500.0, "bf16x3": 2500.0}
 CFG = 3  # 6-qubit Ising chain, d = 64
 WORKLOADS = {2: "4-qubit Heisenberg chain", 3: "6-qubit Ising chain", 4: "7-qubit Heisenberg chain"}
 
@@ -52,8 +54,9 @@ def permutation_runs(Hc: np.ndarray, group: int = 4):
 
 
 def slice_flops(plan: np.ndarray, d: int, m: int, prec: str, runs=None) -> dict:
-    """MFMA flops per stage of the implemented algorithm for slices with plan
-    rows (s, q, qb), and the adjoint's count in the conventional 8 d^3 per
+    """MFMA flops per stage of the block form (general generators, and FP64 at
+    d > 64; the Hermitian path's are series_flops) for slices with plan rows
+    (s, q, qb), and the adjoint's count in the conventional 8 d^3 per
     complex product ("adjoint_8d3").
 
     Complex d x d products per slice: expm q - 1 + s (Horner; at d > 64 in
@@ -93,6 +96,37 @@ def slice_flops(plan: np.ndarray, d: int, m: int, prec: str, runs=None) -> dict:
     return {"expm": float((g_expm * n_exp).sum()), "scan": float(2 * g_scan * len(s)),
             "adjoint": float((g_adj * n_adj).sum()), "adjoint_8d3": float((8.0 * d ** 3 * n_adj).sum()),
             "adjoint_valu": valu}
+
+
+def series_orders(problems, plan: np.ndarray, prec: str) -> np.ndarray:
+    """Orders of the commutator series per slice: the least n with
+    x^(n+1)/(n+1)! <= ur (1 - x/(n+2)), x = 2 theta / 2^s, as the plan picks them
+    at d <= 64."""
+    ur = 2.0 ** -53 if prec == "fp64" else 2.0 ** -24
+    n1 = lambda H: np.abs(H).sum(axis=0).max()
+    theta = np.concatenate([p.dt * (n1(p.H0) + np.abs(p.u).T @ np.array([n1(H) for H in p.Hc])) for p in problems])
+    x = 2 * theta / 2.0 ** plan[:, 0]
+    n = np.ones(len(x))
+    t = x * x / 2
+    for k in range(1, 30):
+        on = (t > ur * (1 - x / (k + 2))) & (n == k)
+        n[on] = k + 1
+        t = t * x / (k + 2)
+    return n
+
+
+def series_flops(problems, plan: np.ndarray, d: int, prec: str) -> dict:
+    """Matrix-core flops of the Hermitian path at 16 < d <= 64 over all slices (s = 0;
+    the doublings of s > 0 are not counted): the exponential's products, one chain
+    product and the series' one product per order.  FP32 (and split BF16, which
+    runs the same kernels) takes three FP16 products per real one, 24 d^3 flops per
+    complex product, and its chain in FP32 by the three-product form, 6 d^3; FP64
+    takes the latter throughout."""
+    q, m = plan[:, 1], series_orders(problems, plan, prec)
+    n_exp = np.where(q <= 3, q - 1, np.where(q == 4, 2, np.where(q <= 8, 3, 2 + (q - 1) // 3)))
+    g = 6.0 * d ** 3 if prec == "fp64" else 24.0 * d ** 3
+    return {"expm": float(g * n_exp.sum()), "chain": 6.0 * d ** 3 * len(q), "adjoint": float(g * m.sum()),
+            "adjoint_8d3": float(8.0 * d ** 3 * m.sum())}
 
 
 def worst_rel_grad_err(grad, ref):
@@ -386,10 +420,8 @@ def main():
     batch = qoc.Batch.from_problems(problems)
     plans = {pr: np.concatenate([qoc.slice_plan(p.H0, p.Hc, p.u, p.dt, pr, True) for p in problems])
              for pr in ("fp32", "fp64", "bf16x3")}
-    runs = permutation_runs(problems[0].Hc)
-    flops = {pr: slice_flops(plans[pr], d, m, pr, runs) for pr in plans}
-    # the dense control kernels take every product (no sampled last step)
-    flops_dense = slice_flops(plans.get(args.precision, plans["fp32"]), d, m, args.precision)
+    flops = {pr: series_flops(problems, plans[pr], d, pr) for pr in plans}
+    flops_dense = flops[args.precision]
 
     def leg(prec, steps, bsz=B, bat=batch, dense_controls=False):
         r = qoc.Runner(bsz, d, m, N, prec, dense_controls=dense_controls)
@@ -416,12 +448,11 @@ def main():
                 ("stored rocprofv3 reading (profiles/k_adjoint_counters.json: FETCH_SIZE + WRITE_SIZE per "
                  "dispatch, each scaled by its reading for a plain 1 GiB copy), used because its kernel-source "
                  "hash matches this build; not measured in this run"),
-                "kernel": "k_adjoint", "avg_launch_ms": round(adj_ms / max(adj_n, 1), 4),
-                "cgemm_8d3_tflops": round(flops[args.precision]["adjoint_8d3"] / adj_avg_s / 1e12, 2),
-                "sampled_valu_tflops": round(flops[args.precision]["adjoint_valu"] / adj_avg_s / 1e12, 2)}
+                "kernel": "k_seg_grad", "avg_launch_ms": round(adj_ms / max(adj_n, 1), 4),
+                "cgemm_8d3_tflops": round(flops[args.precision]["adjoint_8d3"] / adj_avg_s / 1e12, 2)}
 
     def path_flops(pr):
-        return sum(v for k, v in flops[pr].items() if k not in ("adjoint_8d3", "adjoint_valu"))
+        return sum(v for k, v in flops[pr].items() if k != "adjoint_8d3")
 
     total_flops = path_flops(args.precision)
     stages = {k: round(v[0] / max(v[1], 1), 4) for k, v in head["stages"].items() if v[1]}

@@ -56,11 +56,16 @@ typedef enum {
 
 typedef enum {
   QOC_FP64 = 0,  /* complex128 GEMMs on FP64 MFMA */
-  QOC_FP32 = 1,  /* complex64 GEMMs on FP32 MFMA; norms, traces and inner products in FP64 */
-  QOC_BF16X3 = 2 /* the adjoint's complex products (the Frechet series and its traces)
-                    as three split-BF16 MFMA products (hi*hi + hi*lo + lo*hi) with FP32
-                    accumulation; propagators, scans and carries as QOC_FP32; FP32
-                    storage; FP64 norms, traces and inner products; 17 <= d <= 64 */
+  QOC_FP32 = 1,  /* complex64 storage; for Hermitian Hamiltonians the products whose
+                    errors stay local (exponentials, commutator series) as three split-FP16
+                    MFMA products (22 bits per factor, FP32 accumulation) and the chain
+                    products on FP32 MFMA, for general generators everything on FP32 MFMA;
+                    norms, traces and inner products in FP64 */
+  QOC_BF16X3 = 2 /* general generators: the adjoint's complex products (the Frechet series
+                    and its traces) as three split-BF16 MFMA products (hi*hi + hi*lo + lo*hi)
+                    with FP32 accumulation, the rest as QOC_FP32; Hermitian Hamiltonians: as
+                    QOC_FP32, whose split products keep more bits at the same cost;
+                    17 <= d <= 64 */
 } qoc_precision;
 
 typedef struct {
@@ -73,9 +78,9 @@ typedef struct {
                              the host and ignore it: a non-Hermitian or non-finite
                              input gives unspecified results there, never an error. */
   uint64_t hbm_budget;    /* bytes for the per-slice and per-chunk arrays of a call
-                             (stored propagators, and at d > 16 the slice
-                             Hamiltonians and, in QOC_FP32, the squares
-                             (A_k / 2^s)^2 kept for the adjoint); 0 = no limit.
+                             (four arrays of one stored matrix per slice, five in
+                             QOC_FP32, three at d <= 16; the segmented Hermitian
+                             path fills few of them); 0 = no limit.
                              When those arrays exceed it, slices are
                              processed in checkpoint segments and recomputed
                              for the gradient pass (same results, more work).
@@ -275,8 +280,9 @@ int qoc_state_gradient_dev(int B, int d, int m, int N, const void* H0, const voi
  * theta_k = dt (|H0|_1 + sum_j |u[j*N + k]| |Hc[j]|_1) bounds |dt H_k|_1;
  * q and qb are the least degrees whose Taylor remainder bounds at
  * r = theta_k / 2^s are at most the unit roundoff of the precision, and s
- * minimises the number of complex matrix products (with_gradient selects the
- * count of the gradient path).  Returns QOC_OK or QOC_ERR_ARG.
+ * minimises the number of complex matrix products of the Hermitian kernels
+ * (with_gradient selects the count of the gradient path: the commutator series,
+ * in FP64 at d > 64 the Frechet block).  Returns QOC_OK or QOC_ERR_ARG.
  */
 int qoc_slice_plan(int d, int m, int N, const qoc_z* H0, const qoc_z* Hc, const double* u,
                    double dt, int precision, int with_gradient, int32_t* plan);
