@@ -272,6 +272,7 @@ __device__ __forceinline__ void prep_one(const ProbDesc& P, int mat, double* col
       dst[pf_index<T, D>(w, 0, reg, lane)] = (T)re;
       dst[pf_index<T, D>(w, 1, reg, lane)] = (T)im;
     }
+    __syncthreads();  // the norm has been read: a persistent workgroup's next item may be another V
   }
 }
 
