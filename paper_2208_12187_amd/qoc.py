@@ -421,18 +421,26 @@ class JacobianRunner(Runner):
         self.precision, self.chunk, self.hbm_budget = precision, 0, 0
         self.ws_bytes = int(lib().qoc_jacobian_workspace_size(d, m, N, PRECISIONS[precision]))
         self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=device)
+        # X_N where the caller gives no buffer for it.  The kernels read it back, on a
+        # stream that need not be the current one: like the workspace it is the runner's.
+        self.XN = torch.empty((d, d), dtype=torch.complex128, device=device)
         self.device = device
 
     def jacobian(self, b: Batch, J, XN=None, stream=None):
         """Enqueue the first m N columns of J (2 d^2 rows, float64): the real and
-        the imaginary parts of d(X_N)_ab / du."""
+        the imaginary parts of d(X_N)_ab / du.  XN (complex128, d x d) receives X_N."""
         import torch
 
         self._shape_ok(b)
-        if J.shape[0] != 2 * self.d ** 2 or J.shape[1] < self.m * self.N or J.stride(1) != 1 or J.dtype != torch.float64:
-            raise ValueError("J must be a float64 row-major tensor of 2 d^2 rows of at least m N entries")
+        if (J.dim() != 2 or J.shape[0] != 2 * self.d ** 2 or J.shape[1] < self.m * self.N or J.stride(1) != 1
+                or J.dtype != torch.float64 or J.device != self.ws.device):
+            raise ValueError("J must be a float64 row-major tensor of 2 d^2 rows of at least m N entries "
+                             "on the runner's device")
         if XN is None:
-            XN = torch.empty((self.d, self.d), dtype=torch.complex128, device=self.ws.device)
+            XN = self.XN
+        elif (tuple(XN.shape) != (self.d, self.d) or XN.dtype != torch.complex128 or not XN.is_contiguous()
+                or XN.device != self.ws.device):
+            raise ValueError("XN must be a contiguous complex128 d x d tensor on the runner's device")
         o = self._opt(stream)
         _check(lib().qoc_jacobian_dev(b.d, b.m, b.N, b.H0.data_ptr(), b.Hc.data_ptr(), b.u.data_ptr(), b.dt,
                                       J.data_ptr(), J.stride(0), XN.data_ptr(), self.ws.data_ptr(), self.ws_bytes,
