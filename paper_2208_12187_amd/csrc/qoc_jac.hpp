@@ -5,8 +5,9 @@
 // the commutator series of one Hermitian matrix (one product per order), two
 // products more and no costate.  One workgroup takes a segment and kJacGroup of
 // the controls; it forms P at the segment's start from the carry and the joins
-// and carries it on with the slice's exponential.  Slices with s > 0 add the
-// derivatives of their 2^s parts.
+// and carries it on with the slice's exponential.  Slices with s > 0 take the
+// series on A / 2^s and double it s times, Phi <- (Phi + U^dag Phi U) / 2 with U the
+// propagator of the part covered so far: two products per control and doubling.
 //
 // At d = 16, m = 8, N = 1000 in FP64: 130 us, the latency of dependent products in
 // about two wavefronts per SIMD, and 16 us for k_jac_out.  (The d^2 rows as a batch
@@ -52,86 +53,117 @@ __global__ __launch_bounds__(4 * D) void k_jac(Work W, T* out) {
     int s, q, qb;
     unpack_sq(sqk, s, q, qb);
     const int m = plan_order(sqk);
-    const double part = ldexp(P.dt, -s);
-    for (int sub = 0; sub < (1 << s); ++sub) {
-      // Q = X_N P_{k-1}^dag
+    // Q = X_N P_{k-1}^dag
+    __syncthreads();
+    Ops::store(lb, Pk, L);
+#pragma unroll
+    for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * rb + Prec<T>::rowmap(r, L.g), col = 16 * L.w + L.c16;
+        const bool in = row < P.d && col < P.d;
+        const double* x = P.XN + 2 * ((size_t)row * P.d + col);
+        X.re[rb][r] = in ? (T)gp(x)[0] : (T)0;
+        X.im[rb][r] = in ? (T)gp(x)[1] : (T)0;
+      }
+    Ops::store(la, X, L);
+    __syncthreads();
+    Ops::load_ct(R, lb, L);
+    Ops::gemm(Q, la, R, L, true);
+    assemble_panel<T, D>(X, lb, P, k, ldexp(P.dt, -s), mono, tb, k - g.ka, L);
+    Ops::store_nct(la, X, L);  // A = -A^dag (assemble_panel ends with a barrier after Q's reads)
+    __syncthreads();
+    T* o = out + ((size_t)j0 * P.N + k) * mat;
+    const size_t oj = (size_t)P.N * mat;  // to the next control's matrix
+    // dX_N / du[j][k] = -i dt Q Phi P from Phi in Z
+    auto put = [&](T* dst, const Panel<T, D>& Z) {
+      Panel<T, D> C;
       __syncthreads();
-      Ops::store(lb, Pk, L);
+      Ops::store(lb, Z, L);
+      __syncthreads();
+      Ops::gemm(R, lb, Pk, L, true);
+      __syncthreads();
+      Ops::store(lb, Q, L);
+      __syncthreads();
+      Ops::gemm(C, lb, R, L, true);
+      const T f = (T)P.dt;
 #pragma unroll
       for (int rb = 0; rb < D / 16; ++rb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = 16 * rb + Prec<T>::rowmap(r, L.g), col = 16 * L.w + L.c16;
-          const bool in = row < P.d && col < P.d;
-          const double* x = P.XN + 2 * ((size_t)row * P.d + col);
-          X.re[rb][r] = in ? (T)gp(x)[0] : (T)0;
-          X.im[rb][r] = in ? (T)gp(x)[1] : (T)0;
+          const T re = C.re[rb][r];
+          C.re[rb][r] = f * C.im[rb][r];
+          C.im[rb][r] = -f * re;
         }
-      Ops::store(la, X, L);
-      __syncthreads();
-      Ops::load_ct(R, lb, L);
-      Ops::gemm(Q, la, R, L, true);
-      assemble_panel<T, D>(X, lb, P, k, part, mono, tb, k - g.ka, L);
-      Ops::store_nct(la, X, L);  // A = -A^dag (assemble_panel ends with a barrier after Q's reads)
-      __syncthreads();
-      for (int j = j0; j < j1; ++j) {
-        const T* H = reinterpret_cast<const T*>(P.Hint) + (j + 1) * mat;
-        Panel<T, D> C, Z;
+      panel_store(dst, C, L);
+    };
+    for (int j = j0; j < j1; ++j) {
+      const T* H = reinterpret_cast<const T*>(P.Hint) + (j + 1) * mat;
+      Panel<T, D> C, Z;
+#pragma unroll
+      for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int e = (16 * rb + Prec<T>::rowmap(r, L.g)) * D + 16 * L.w + L.c16;
+          C.re[rb][r] = gp(H)[e];
+          C.im[rb][r] = gp(H)[D * D + e];
+        }
+      Z = C;
+      for (int n = 1; n <= m; ++n) {  // C <- -[A, C] / n, Z <- Z + C / (n + 1)
+        Ops::mul(R, la, C, L);
+        __syncthreads();
+        panel_to_lds_ct(pt, R, L);
+        __syncthreads();
+        panel_from_lds(C, pt, L);
+        const T ck = (T)(-1.0 / n), zk = (T)(1.0 / (n + 1));
 #pragma unroll
         for (int rb = 0; rb < D / 16; ++rb)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int e = (16 * rb + Prec<T>::rowmap(r, L.g)) * D + 16 * L.w + L.c16;
-            C.re[rb][r] = gp(H)[e];
-            C.im[rb][r] = gp(H)[D * D + e];
+            C.re[rb][r] = (C.re[rb][r] + R.re[rb][r]) * ck;
+            C.im[rb][r] = (C.im[rb][r] + R.im[rb][r]) * ck;
+            Z.re[rb][r] = fma(zk, C.re[rb][r], Z.re[rb][r]);
+            Z.im[rb][r] = fma(zk, C.im[rb][r], Z.im[rb][r]);
           }
-        Z = C;
-        for (int n = 1; n <= m; ++n) {  // C <- -[A, C] / n, Z <- Z + C / (n + 1)
-          Ops::mul(R, la, C, L);
-          __syncthreads();
-          panel_to_lds_ct(pt, R, L);
-          __syncthreads();
-          panel_from_lds(C, pt, L);
-          const T ck = (T)(-1.0 / n), zk = (T)(1.0 / (n + 1));
-#pragma unroll
-          for (int rb = 0; rb < D / 16; ++rb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              C.re[rb][r] = (C.re[rb][r] + R.re[rb][r]) * ck;
-              C.im[rb][r] = (C.im[rb][r] + R.im[rb][r]) * ck;
-              Z.re[rb][r] = fma(zk, C.re[rb][r], Z.re[rb][r]);
-              Z.im[rb][r] = fma(zk, C.im[rb][r], Z.im[rb][r]);
-            }
-        }
-        __syncthreads();
-        Ops::store(lb, Z, L);
-        __syncthreads();
-        Ops::gemm(R, lb, Pk, L, true);
-        __syncthreads();
-        Ops::store(lb, Q, L);
-        __syncthreads();
-        Ops::gemm(C, lb, R, L, true);
-        T* o = out + ((size_t)j * P.N + k) * mat;
-        if (sub > 0) panel_load(Z, o, L);  // own panel
-        else panel_zero(Z);
-        const T f = (T)part;
-#pragma unroll
-        for (int rb = 0; rb < D / 16; ++rb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {  // -i dt / 2^s
-            Z.re[rb][r] += f * C.im[rb][r];
-            Z.im[rb][r] -= f * C.re[rb][r];
-          }
-        panel_store(o, Z, L);
       }
-      __syncthreads();
+      if (s == 0) put(o + (j - j0) * oj, Z);
+      else panel_store(o + (j - j0) * oj, Z, L);  // (own panel: read back by this wavefront)
+    }
+    __syncthreads();
+    if (s == 0) {
       taylor_delta<T, D, Ops>(R, X, la, 0, q, L);
       __syncthreads();
       Ops::store(la, R, L);
       __syncthreads();
-      Ops::gemm(R, la, Pk, L, true);
-      panel_fma(Pk, (T)1, R);
+    } else {
+      // R = U^dag - I from -A / 2^s = (A / 2^s)^dag, the left factor of the doublings
+      // and of its own squaring
+      Ops::store_ct(la, X, L);
+      panel_scale(X, (T)-1);
+      __syncthreads();
+      taylor_delta<T, D, Ops>(R, X, la, 0, q, L);
+      for (int i = 0; i < s; ++i) {
+        __syncthreads();
+        Ops::store(la, R, L);
+        __syncthreads();
+        for (int j = j0; j < j1; ++j) {
+          panel_load(X, o + (j - j0) * oj, L);
+          conjugate_by<T, D, Ops>(X, (T)0.5, la, lb, L);
+          panel_store(o + (j - j0) * oj, X, L);
+        }
+        Ops::mul(X, la, R, L);
+        panel_scale(R, (T)2);
+        panel_fma(R, (T)1, X);
+      }
+      __syncthreads();
+      Ops::store_ct(la, R, L);  // U - I, published by put's barriers
+      for (int j = j0; j < j1; ++j) {
+        panel_load(X, o + (j - j0) * oj, L);
+        put(o + (j - j0) * oj, X);
+      }
     }
+    Ops::gemm(R, la, Pk, L, true);
+    panel_fma(Pk, (T)1, R);
   }
 }
 
