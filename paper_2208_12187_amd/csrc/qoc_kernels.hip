@@ -1860,16 +1860,16 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
         panel_scale(R, CI);
         if (k == g.ka) {
           S = R;
-          panel_add_identity(S, L, (T)1);
         } else {
           __syncthreads();  // the exponential's last left factor has been read
           Std::store(la, R, L);
           __syncthreads();
+          // S + I <- (Delta + I)(S + I): nothing is rounded at the size of I
           Std::gemm3(X, la, S, L, true);
-          panel_fma(S, (T)1, X);  // S <- S + Delta S
+          panel_fma(S, (T)1, R);
+          panel_fma(S, (T)1, X);
         }
       }
-      panel_add_identity(S, L, (T)-1);
       panel_store(pf_mat<T, D>(P.xprev, g.ka - W.rg.kbase), S, L);
     }
     if constexpr (!PERSIST) break;  // one item per workgroup: a single-trip loop
