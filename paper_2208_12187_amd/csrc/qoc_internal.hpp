@@ -53,7 +53,8 @@ struct ProbDesc {
   void* grp;          // 4 x PG PF matrices: forward and backward group totals, then the
                       // forward and backward carries into each group
   double* g;          // complex128 Tr(V^dag X_N)
-  int* squared;       // nonzero: some slice's plan has s > 0
+  int* squared;       // [0] nonzero: some slice's plan has s > 0; [1], in the first problem of a
+                      // launch: the same of any of its problems
   double* vscale;     // power of two by which k_prep divided the stored target
   double* diag;       // [0] ||X_N^dag X_N - I||_F; [1] largest chunk residual (FP64
                       // bits, atomic max); [2] re-unitarisation steps (uint64 count)

@@ -128,7 +128,7 @@ __device__ __forceinline__ void prep_one(const ProbDesc& P, int mat, double* col
   if (mat == 0 && threadIdx.x == 0) {
     P.diag[1] = 0.0;
     P.diag[2] = 0.0;
-    *P.squared = 0;
+    P.squared[0] = P.squared[1] = 0;
   }
   if (mat <= m) {
     constexpr int LPR = D < 64 ? D : 64;  // lanes per row
@@ -309,7 +309,10 @@ __global__ __launch_bounds__(256) void k_plan(Work W, double ur, int flags) {
     th *= P.dt;
     const SlicePlan pl = choose_plan(th, ur, flags);
     const int cf = controls_flags(P);
-    if (pl.s > 0) atomicOr(P.squared, 1);
+    if (pl.s > 0) {  // (every writer writes the same)
+      gp(P.squared)[0] = 1;
+      gp(W.descs[I.desc(0)].squared)[1] = 1;
+    }
     P.sq[k] = pack_plan(pl) | (pl.s == 0 && (cf & 2) ? kPlanSampled : 0) | ((cf & 1) ? kPlanMono : 0);
   }
 }
@@ -1538,7 +1541,8 @@ void k_adjoint(Work W) {
 // for the block, and reads nothing per slice but its amplitudes.
 //
 // Slices with s > 0 take the series on A_k / 2^s and double it s times,
-// Z <- (Z + U Z U^dag) / 2 with U the propagator of the part covered so far.
+// Z <- (Z + U Z U^dag) / 2 with U the propagator of the part covered so far, which
+// starts from the exponential that k_seg_fwd has kept.
 //
 // The chunks are cut into segments of at most kSegMax slices, so that few
 // problems still fill the chip: k_seg_fwd forms the segment totals, k_seg_join
@@ -1549,6 +1553,12 @@ void k_adjoint(Work W) {
 // Two workgroups per CU (two waves per SIMD) where registers and LDS allow it.
 template <typename T, int D>
 constexpr int kSegWaves = (sizeof(T) == 8 && D == 64) ? 1 : 2;
+// The workspace has a second array for the exponentials of squared problems.
+template <int D>
+constexpr bool kKeepU = D >= 32;
+// Workgroups that fill the chip's 256 CUs with kSegWaves wavefronts per SIMD.
+template <typename T, int D>
+constexpr int kSqGrid = 256 * 4 * kSegWaves<T, D> / (D / 16);
 
 // Item -> (problem, chunk, segment), and the segment's slices [ka, kb).
 struct SegItem {
@@ -1736,13 +1746,14 @@ struct T8 {
 
 // R = C (exp(A) - I) from the panel X = C A / 2^s (A anti-Hermitian), whose left
 // factor is in lds already (and is replaced there): the Taylor polynomial of a
-// degree of at least q in taylor_products(q) products, then s squarings.
+// degree of at least q in taylor_products(q) products, then s squarings.  part (a
+// PF matrix, or null): receives C (exp(A / 2^s) - I) where s > 0.
 //  * q <= 3: Horner in delta form with the one left factor, R <- (X + X R) / i;
 //  * q = 4: X + A2 (I / 2 + X / 6 + A2 / 24);  q <= 8: T8;
 //  * above: Paterson-Stockmeyer with A3 as the step.
 template <typename T, int D, typename Ops>
 __device__ __forceinline__ void taylor_delta(Panel<T, D>& R, const Panel<T, D>& X, void* lds, int s, int q,
-                                             const Lane& L) {
+                                             const Lane& L, T* part = nullptr) {
   constexpr T C = Ops::C, CI = (T)1 / Ops::C;
   Panel<T, D> acc;
   if (q <= 3) {
@@ -1820,6 +1831,7 @@ __device__ __forceinline__ void taylor_delta(Panel<T, D>& R, const Panel<T, D>& 
       }
     }
   }
+  if (s > 0 && part) panel_store(part, R, L);
   for (int j = 0; j < s; ++j) {
     __syncthreads();
     Ops::store(lds, R, L);
@@ -1849,6 +1861,9 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
       const ProbDesc P = W.descs[I.desc(g.p)];  // a copy: stores cannot alias it
       const bool mono = (gp(P.sq)[g.ka] & kPlanMono) != 0;
       const SegTab<T, D>* tb = seg_tab_load<T, D>(tab, P, g.ka, g.kb, mono) ? &tab : nullptr;
+      // a gradient with squared slices: the exponentials before and after their
+      // squarings, as k_seg_grad_sq takes them
+      const bool keep = (P.flags & RUN_GRAD) && gp(P.squared)[0] != 0;
       Panel<T, D> S, X, R;
       for (int k = g.ka; k < g.kb; ++k) {
         int s, q, qb;
@@ -1856,7 +1871,8 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
         assemble_panel<T, D>(X, la, P, k, ldexp(P.dt * (double)Ops::C, -s), mono, tb, k - g.ka, L);
         Ops::store_nct(la, X, L);  // X = -X^dag
         __syncthreads();
-        taylor_delta<T, D, Ops>(R, X, la, s, q, L);
+        taylor_delta<T, D, Ops>(R, X, la, s, q, L, keep ? pf_mat<T, D>(P.delta, k - W.rg.kbase) : nullptr);
+        if (kKeepU<D> && keep) panel_store(pf_mat<T, D>(P.hk, k - W.rg.kbase), R, L);
         panel_scale(R, CI);
         if (k == g.ka) {
           S = R;
@@ -2156,8 +2172,7 @@ __device__ __forceinline__ void seg_grad_body(const ProbDesc& P, int c, int sg, 
     for (int rb = 0; rb < D / 16; ++rb) gather(rb);
     if constexpr (SQ) {
       if (s > 0) {
-        assemble_panel<T, D>(Q, lb, P, k, ldexp(P.dt * (double)C, -s), mono, tb, k - ka, L);
-        taylor_delta<T, D, Ops>(R, Q, la, 0, q, L);
+        panel_load(R, pf_mat<T, D>(P.delta, k - kbase), L);  // C (exp(A / 2^s) - I)
         for (int j = 0;; ++j) {
           __syncthreads();
           Ops::store(la, R, L);
@@ -2177,6 +2192,107 @@ __device__ __forceinline__ void seg_grad_body(const ProbDesc& P, int c, int sg, 
     // (A is no longer needed: its buffer takes the sums)
     static_assert(2 * kSegEpi * (D / 16) * 8 <= Ops::BYTES, "sums");
     seg_epilogue<T, D>(P, k, part, pt, (double)CI, tb, static_cast<double*>(la), mono, L);
+  }
+}
+
+// The same for the slices [wa, wb) of a segment that starts at ka, with slices of
+// s > 0 among them, where k_seg_fwd has kept every slice's U - I (kKeepU): Y passes the
+// slices by their propagators, those before wa too.  One panel V is Y or Z in turn
+// (Y is put by while a slice's series runs) and one loop takes every conjugation, so
+// that there is one instance of each product: the registers do not hold more.
+template <typename T, int D, typename Ops>
+__device__ __forceinline__ void seg_grad_pieces(const ProbDesc& P, int c, int sg, int ka, int wa, int wb, int kbase,
+                                                int part, bool mono, void* la, void* lb, SegTab<T, D>& tab,
+                                                const Lane& L) {
+  constexpr T C = Ops::C, CI = (T)1 / Ops::C;
+  T* pt = static_cast<T*>(lb);  // planar
+  const SegTab<T, D>* tb = seg_tab_load<T, D>(tab, P, wa, wb, mono) ? &tab : nullptr;
+  Panel<T, D> V, Q, R;
+  panel_load(V, pf_mat<T, D>(part ? P.cb : P.mc, c), L);
+  panel_scale(V, C);
+  bool conj = sg > 0;  // V <- V + f (U V U^dag - V), U - I in R
+  if (conj) {          // to Y at the segment's start
+    panel_load(R, pf_mat<T, D>(P.bloc, ka - kbase), L);
+    panel_scale(R, C);
+  }
+  // Where Y of slice k waits (this wavefront's panel): xprev's segment totals have been
+  // joined, and bloc holds prefixes at segment starts only, which no k + 1 < wb is.
+  auto yslot = [&](int k) { return part ? pf_mat<T, D>(P.bloc, k + 1 - kbase) : pf_mat<T, D>(P.xprev, k - kbase); };
+  T f = 1;
+  int k = ka, s = 0, j = 0;
+  bool inside = false;  // V is Z of slice k, j of its s doublings done
+#pragma unroll 1
+  for (;;) {
+    if (conj) {
+      __syncthreads();  // la's last readers are done
+      Ops::store(la, R, L);
+      __syncthreads();
+      conjugate_by<T, D, Ops>(V, f, la, lb, L);
+    }
+    if (inside) {
+      if (conj && ++j < s) {
+        Ops::mul(Q, la, R, L);
+        panel_scale(R, (T)2);
+        panel_fma(R, CI, Q);
+        continue;
+      }
+      __syncthreads();
+      panel_to_lds_ct(pt, V, L);  // Z = Z^dag
+      __syncthreads();
+      static_assert(2 * kSegEpi * (D / 16) * 8 <= Ops::BYTES, "sums");
+      seg_epilogue<T, D>(P, k, part, pt, (double)CI, tb, static_cast<double*>(la), mono, L);
+      if (k + 1 >= wb) break;
+      panel_load(V, yslot(k), L);
+      inside = false;
+    } else if (k >= wa) {
+      const int sqk = gp(P.sq)[k];
+      int q, qb;
+      unpack_sq(sqk, s, q, qb);
+      const int m = plan_order(sqk);
+      if (k + 1 < wb) panel_store(yslot(k), V, L);
+      assemble_panel<T, D>(R, lb, P, k, ldexp(P.dt * (double)C, -s), mono, tb, k - wa, L);
+      Ops::store_nct(la, R, L);  // A = -A^dag
+      __syncthreads();
+      Q = V;
+      panel_zero(V);
+      T zk = 1;
+      auto gather = [&](int rb) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          V.re[rb][r] = fma(zk, Q.re[rb][r], V.re[rb][r]);
+          V.im[rb][r] = fma(zk, Q.im[rb][r], V.im[rb][r]);
+        }
+      };
+      for (int n = 1; n <= m; ++n) {
+        Ops::mul(R, la, Q, L, gather);
+        if (n > 1) __syncthreads();  // the previous transpose has been read
+        panel_to_lds_ct(pt, R, L);
+        __syncthreads();
+        panel_from_lds(Q, pt, L);
+        const T ck = CI * (T)(1.0 / n);
+        zk = (T)(1.0 / (n + 1));
+#pragma unroll
+        for (int rb = 0; rb < D / 16; ++rb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            Q.re[rb][r] = (Q.re[rb][r] + R.re[rb][r]) * ck;
+            Q.im[rb][r] = (Q.im[rb][r] + R.im[rb][r]) * ck;
+          }
+      }
+#pragma unroll
+      for (int rb = 0; rb < D / 16; ++rb) gather(rb);
+      inside = true;
+      conj = s > 0;
+      f = (T)0.5;
+      j = 0;
+      if (conj) panel_load(R, pf_mat<T, D>(P.delta, k - kbase), L);  // C (exp(A / 2^s) - I)
+      continue;
+    }
+    // Y to the next slice
+    panel_load(R, pf_mat<T, D>(P.hk, k - kbase), L);
+    conj = true;
+    f = 1;
+    ++k;
   }
 }
 
@@ -2202,8 +2318,27 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
   }
 }
 
-// The problems with squared slices: a grid that leaves at once when there is
-// none, its workgroups spread over the problems and then over their segments.
+// Pieces that a segment of h slices is cut into: one per slice (whose workgroup takes Y
+// through the slices before it: the same steps on the same numbers, two products per
+// slice passed, against about 25 of a slice) if that takes less time in rounds of the
+// grid.  Where several workgroups share a CU the last round's go the faster for being
+// few, and cutting pays only if there is hardly more than one.  One problem of
+// N = 1000 in FP64 (264 segments of four slices): d = 32 (grid 1024) 283 -> 179 us,
+// d = 64 (grid 256) 1.55 -> 1.15 ms; eight problems of d = 32 883 -> 994 us.
+__host__ __device__ inline int sq_pieces(int total, int h, int grid, bool shared) {
+  if (shared && total >= grid + grid / 8) return 1;
+  const int whole = (total + grid - 1) / grid * h * 25, cut = (total * h + grid - 1) / grid * (24 + h);
+  return cut < whole - whole / 10 ? h : 1;
+}
+
+// The segments of the problems with squared slices, in turn over a grid that fills
+// the chip (kSqGrid) and leaves at once when there is none.  The items are those of
+// k_seg_grad (or their pieces), so that one squared problem of a batch spreads over
+// all workgroups; a workgroup passes over the others' at one load each.  (Engine ticks
+// cut in two: the engine's chunks have segments of two slices up to N = 2048.)
+// With 256 workgroups at every d, dealt out by problem, 32 problems of d = 16, N = 1000
+// with s = 2 took 1.38 ms in FP32 (now 0.34; the block form 0.37) and one such
+// problem in a batch of 32 at d = 64 7.6 ms (now 2.8; the block form 6.0).
 template <typename T, int D, typename Ops>
 __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves<T, D>))) void k_seg_grad_sq(Work W) {
   constexpr int LB = StdOps<T, D>::BYTES > Ops::BYTES ? StdOps<T, D>::BYTES : Ops::BYTES;
@@ -2212,22 +2347,21 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
   __shared__ SegTab<T, D> tab;
   Lane L;
   const Items I(W);
-  const int per = max(1, (int)gridDim.x / max(I.nprob, 1));  // workgroups of a problem
-  const int rank = (int)blockIdx.x / max(I.nprob, 1);
-  if (rank >= per) return;
-  for (int p = (int)blockIdx.x % max(I.nprob, 1); p < I.nprob; p += gridDim.x) {
-    const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
-    if (gp(P.squared)[0] == 0) continue;
-    const int sc = seg_count(P.D, P.L), h = seg_len(P.D, P.L);
-    const int c0 = W.rg.c_n > 0 ? W.rg.c_lo : 0, cn = W.rg.c_n > 0 ? W.rg.c_n : P.P;
-    for (int x = rank; x < cn * sc; x += per) {
-      const int c = c0 + x / sc, sg = x % sc;
-      const int ka = c * P.L + sg * h, kb = min(min(P.N, (c + 1) * P.L), ka + h);
-      if (ka >= kb) continue;
-      const bool mono = (gp(P.sq)[ka] & kPlanMono) != 0;
-      seg_grad_body<T, D, Ops, true>(P, c, sg, ka, kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, L);
-      __syncthreads();
-    }
+  if (I.nprob == 0 || gp(W.descs[I.desc(0)].squared)[1] == 0) return;
+  const int cut = kKeepU<D> ? sq_pieces(I.total, W.dyn ? 2 : seg_len(D, W.descs[0].L), kSqGrid<T, D>, kSegWaves<T, D> > 1) : 1;
+  for (int item = blockIdx.x; item < I.total * cut; item += gridDim.x) {
+    const SegItem g = seg_split(item / cut, W.rg, I, W.descs);
+    if (g.ka >= g.kb || gp(W.descs[I.desc(g.p)].squared)[0] == 0) continue;
+    const ProbDesc P = W.descs[I.desc(g.p)];  // a copy: stores cannot alias it
+    const int h = seg_len(P.D, P.L), x = item % cut;
+    const int wa = g.ka + h * x / cut, wb = min(g.kb, g.ka + h * (x + 1) / cut);
+    if (wa >= wb) continue;
+    const bool mono = (gp(P.sq)[g.ka] & kPlanMono) != 0;
+    if constexpr (kKeepU<D>)
+      seg_grad_pieces<T, D, Ops>(P, g.c, g.s, g.ka, wa, wb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, L);
+    else
+      seg_grad_body<T, D, Ops, true>(P, g.c, g.s, g.ka, g.kb, W.rg.kbase, blockIdx.y, mono, la, lb, tab, L);
+    __syncthreads();
   }
 }
 
@@ -3349,7 +3483,10 @@ static void stage_seg(int stage, const Launch& L, const Range& rg, double ur) {
       const dim3 grid(grid_of(L, segs.total, 0), (L.flags & RUN_RAWDG) ? 2 : 1);
       if (L.dyn) hipLaunchKernelGGL((k_seg_grad<T, D, Ops, true>), grid, dim3(NT), 0, st, segs);
       else hipLaunchKernelGGL((k_seg_grad<T, D, Ops, false>), grid, dim3(NT), 0, st, segs);
-      const dim3 sq(L.dyn ? 256 : std::max(1, std::min(segs.total, 256)), grid.y);
+      const int cap = kSqGrid<T, D>;
+      const int items =
+          segs.total * (kKeepU<D> && !L.dyn ? sq_pieces(segs.total, seg_len(D, L.chunk), cap, kSegWaves<T, D> > 1) : 1);
+      const dim3 sq(L.dyn ? cap : std::max(1, std::min(items, cap)), grid.y);
       hipLaunchKernelGGL((k_seg_grad_sq<T, D, Ops>), sq, dim3(NT), 0, st, segs);
       break;
     }

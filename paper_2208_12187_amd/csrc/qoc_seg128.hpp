@@ -811,26 +811,18 @@ __global__ __launch_bounds__(512) void k_seg_grad128(Work W, void* scratch) {
   }
 }
 
-// The problems with squared slices, as k_seg_grad_sq.
+// The segments of the problems with squared slices, as k_seg_grad_sq.
 __global__ __launch_bounds__(512) void k_seg_grad_sq128(Work W, void* scratch) {
   __shared__ __align__(16) unsigned char lds[S128::BYTES];
   Lane L;
   const Items I(W);
-  const int per = max(1, (int)gridDim.x / max(I.nprob, 1));  // workgroups of a problem
-  const int rank = (int)blockIdx.x / max(I.nprob, 1);
-  if (rank >= per) return;
-  for (int p = (int)blockIdx.x % max(I.nprob, 1); p < I.nprob; p += gridDim.x) {
-    const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
-    if (gp(P.squared)[0] == 0) continue;
-    const int sc = seg_count(P.D, P.L), h = seg_len(P.D, P.L);
-    const int c0 = W.rg.c_n > 0 ? W.rg.c_lo : 0, cn = W.rg.c_n > 0 ? W.rg.c_n : P.P;
-    for (int x = rank; x < cn * sc; x += per) {
-      const int c = c0 + x / sc, sg = x % sc;
-      const int ka = c * P.L + sg * h, kb = min(min(P.N, (c + 1) * P.L), ka + h);
-      if (ka >= kb) continue;
-      const bool mono = (gp(P.sq)[ka] & kPlanMono) != 0;
-      px_grad<true>(P, c, sg, ka, kb, W.rg.kbase, blockIdx.y, mono, lds, scratch, L);
-      __syncthreads();
-    }
+  if (I.nprob == 0 || gp(W.descs[I.desc(0)].squared)[1] == 0) return;
+  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+    const SegItem g = seg_split(item, W.rg, I, W.descs);
+    if (g.ka >= g.kb || gp(W.descs[I.desc(g.p)].squared)[0] == 0) continue;
+    const ProbDesc P = W.descs[I.desc(g.p)];  // a copy: stores cannot alias it
+    const bool mono = (gp(P.sq)[g.ka] & kPlanMono) != 0;
+    px_grad<true>(P, g.c, g.s, g.ka, g.kb, W.rg.kbase, blockIdx.y, mono, lds, scratch, L);
+    __syncthreads();
   }
 }
