@@ -219,7 +219,11 @@ void build_tables(qoc_engine* E, Bucket& b) {
       switch (s) {
         case ST_PREP: items = r.m + 2; break;
         case ST_PLAN: items = r.N; break;
-        case ST_EXPM: case ST_ADJ: items = r.D == 128 && E->precision == QOC_FP64 ? r.N : r.lo.P * seg_count(r.D, r.lo.L); break;
+        case ST_EXPM: case ST_ADJ: {
+          const bool f64 = E->precision == QOC_FP64;
+          items = r.D == 128 && f64 ? r.N : r.lo.P * seg_count(r.lo.L, seg_max(r.D, r.lo.L, f64));
+          break;
+        }
         case ST_SCAN: case ST_MC: case ST_BSCAN: items = r.lo.P; break;
         case ST_CARRY: items = r.lo.PG; break;  // carry groups
       }

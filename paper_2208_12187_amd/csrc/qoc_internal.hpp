@@ -20,7 +20,8 @@ struct ProbDesc {
   int d, D, m, N;  // true dimension, padded dimension, controls, slices
   int L, P;        // slices per scan chunk, number of chunks
   int CG, PG;      // chunks per carry group, number of carry groups
-  int flags, pad_;
+  int flags;
+  int SM;  // most slices per segment (seg_max)
   double dt;
   const double* H0z;  // (user) d*d complex128, interleaved
   const double* Hcz;  // (user) m*d*d complex128
@@ -188,13 +189,17 @@ inline int engine_chunk(int N) { return std::max(1, (int)ceil(sqrt(N / 8.0))); }
 // two.  d = 16, one problem of N = 1000 (forward, joins, gradient in us): 14 + 21 +
 // 20 with one, 19 + 12 + 30 with two, 30 + 8 + 47 with four.  d = 128, eight
 // problems of N = 1000: joins 0.49 and gradient 2.50 ms with four, 0.34 and 2.40
-// with eight, which leaves half the chip to one problem.
+// with eight, which leaves half the chip to one problem.  FP64, whose products take
+// more than twice as long, takes shorter ones: one call in us, d = 16, N = 100 75 with
+// two, 62 with one (32 problems 107 and 112); d = 60, N = 60, two problems 532 with two, 390 with
+// one; d = 32, N = 1000 324 with four, 238 with two (32 problems 2301 and 2408).
 constexpr int kSegMax = 8;
-__host__ __device__ inline int seg_max(int D, int L) {
+inline int seg_max(int D, int L, bool f64) {
+  if (f64 && D <= 64) return L <= (D == 16 ? 12 : 8) ? 1 : D == 16 || L <= 24 ? 2 : D == 32 ? 4 : kSegMax;
   return D == 16 || L <= (D == 128 ? 12 : 16) ? 2 : D == 128 || L <= 24 ? 4 : kSegMax;
 }
-__host__ __device__ inline int seg_count(int D, int L) { return (L + seg_max(D, L) - 1) / seg_max(D, L); }
-__host__ __device__ inline int seg_len(int D, int L) { return (L + seg_count(D, L) - 1) / seg_count(D, L); }
+__host__ __device__ inline int seg_count(int L, int most) { return (L + most - 1) / most; }
+__host__ __device__ inline int seg_len(int L, int most) { return (L + seg_count(L, most) - 1) / seg_count(L, most); }
 
 // The carry over the P chunk totals runs in groups of CG =
 // ceil(sqrt(P)) chunks: a serial chain inside every group, one over the PG
@@ -289,6 +294,7 @@ inline void fill_desc(ProbDesc& P, const Layout& Lo, char* pb, int d, int m, int
   P.CG = Lo.CG;
   P.PG = Lo.PG;
   P.flags = flags;
+  P.SM = seg_max(Lo.D, Lo.L, Lo.esize == 8);
   P.dt = dt;
   P.H0z = H0;
   P.Hcz = Hc;

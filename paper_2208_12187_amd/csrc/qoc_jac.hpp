@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void k_jac_out(const T* in, double* J, size_t 
 template <typename T, int D>
 static void jacobian_le64(const Launch& L, int d, int m, int N, void* mats, double* J, size_t ld) {
   const Range rg = {0, N, 0, L.uniformP, 0, 0};
-  const Work segs = {L.descs, 1, L.uniformP * seg_count(D, L.chunk), nullptr, rg, nullptr};
+  const Work segs = {L.descs, 1, L.uniformP * seg_count(L.chunk, seg_max(D, L.chunk, sizeof(T) == 8)), nullptr, rg, nullptr};
   T* out = static_cast<T*>(mats);
   hipLaunchKernelGGL((k_jac<T, D>), dim3(segs.total, (m + kJacGroup - 1) / kJacGroup), dim3(4 * D), 0, L.stream, segs,
                      out);

@@ -1567,7 +1567,7 @@ struct SegItem {
 __device__ __forceinline__ SegItem seg_split(int item, const Range& rg, const Items& I, const ProbDesc* descs) {
   SegItem r;
   if (rg.c_n > 0) {
-    const int sc = seg_count(descs[0].D, descs[0].L);  // uniform launches share L
+    const int sc = seg_count(descs[0].L, descs[0].SM);  // uniform launches share L
     const int per = rg.c_n * sc;
     r.p = item / per;
     const int x = item - r.p * per;
@@ -1576,12 +1576,12 @@ __device__ __forceinline__ SegItem seg_split(int item, const Range& rg, const It
   } else {
     r.p = locate(I.start, I.nprob, item);
     const int x = item - gp(I.start)[r.p];
-    const int sc = seg_count(descs[I.desc(r.p)].D, descs[I.desc(r.p)].L);
+    const int sc = seg_count(descs[I.desc(r.p)].L, descs[I.desc(r.p)].SM);
     r.c = x / sc;
     r.s = x % sc;
   }
   const ProbDesc& P = descs[I.desc(r.p)];
-  const int h = seg_len(P.D, P.L);
+  const int h = seg_len(P.L, P.SM);
   const int k1 = min(P.N, (r.c + 1) * P.L);
   r.ka = r.c * P.L + r.s * h;
   r.kb = min(k1, r.ka + h);
@@ -1905,7 +1905,7 @@ __global__ __launch_bounds__(4 * D) void k_seg_join(Work W) {
     int p, c;
     split_item(item, W.rg.c_lo, W.rg.c_n, I.start, I.nprob, p, c);
     const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
-    const int k1 = min(P.N, (c + 1) * P.L), h = seg_len(P.D, P.L);
+    const int k1 = min(P.N, (c + 1) * P.L), h = seg_len(P.L, P.SM);
     Panel<T, D> S, nxt, acc;
     int k = c * P.L;
     panel_load(S, pf_mat<T, D>(P.xprev, k - W.rg.kbase), L);
@@ -2348,12 +2348,12 @@ __global__ __launch_bounds__(4 * D) __attribute__((amdgpu_waves_per_eu(kSegWaves
   Lane L;
   const Items I(W);
   if (I.nprob == 0 || gp(W.descs[I.desc(0)].squared)[1] == 0) return;
-  const int cut = kKeepU<D> ? sq_pieces(I.total, W.dyn ? 2 : seg_len(D, W.descs[0].L), kSqGrid<T, D>, kSegWaves<T, D> > 1) : 1;
+  const int cut = kKeepU<D> ? sq_pieces(I.total, W.dyn ? 2 : seg_len(W.descs[0].L, W.descs[0].SM), kSqGrid<T, D>, kSegWaves<T, D> > 1) : 1;
   for (int item = blockIdx.x; item < I.total * cut; item += gridDim.x) {
     const SegItem g = seg_split(item / cut, W.rg, I, W.descs);
     if (g.ka >= g.kb || gp(W.descs[I.desc(g.p)].squared)[0] == 0) continue;
     const ProbDesc P = W.descs[I.desc(g.p)];  // a copy: stores cannot alias it
-    const int h = seg_len(P.D, P.L), x = item % cut;
+    const int h = seg_len(P.L, P.SM), x = item % cut;
     const int wa = g.ka + h * x / cut, wb = min(g.kb, g.ka + h * (x + 1) / cut);
     if (wa >= wb) continue;
     const bool mono = (gp(P.sq)[g.ka] & kPlanMono) != 0;
@@ -3446,7 +3446,8 @@ static void stage_seg(int stage, const Launch& L, const Range& rg, double ur) {
   const int grad = (L.flags & RUN_GRAD) ? 1 : 0;
   const Range all = {0, L.uniformN, 0, L.uniformP, rg.kbase};
   const Work dyn = L.dyn ? Work{L.descs, 0, 0, nullptr, Range{0, 0, 0, 0, 0}, L.dyn} : Work{};
-  const Work segs = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * rg.c_n * seg_count(D, L.chunk), nullptr, rg, nullptr};
+  const int most = seg_max(D, L.chunk, sizeof(T) == 8);
+  const Work segs = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * rg.c_n * seg_count(L.chunk, most), nullptr, rg, nullptr};
   switch (stage) {
     case ST_PLAN: {
       Work w = L.dyn ? dyn : slice_work(L, all);
@@ -3485,7 +3486,7 @@ static void stage_seg(int stage, const Launch& L, const Range& rg, double ur) {
       else hipLaunchKernelGGL((k_seg_grad<T, D, Ops, false>), grid, dim3(NT), 0, st, segs);
       const int cap = kSqGrid<T, D>;
       const int items =
-          segs.total * (kKeepU<D> && !L.dyn ? sq_pieces(segs.total, seg_len(D, L.chunk), cap, kSegWaves<T, D> > 1) : 1);
+          segs.total * (kKeepU<D> && !L.dyn ? sq_pieces(segs.total, seg_len(L.chunk, most), cap, kSegWaves<T, D> > 1) : 1);
       const dim3 sq(L.dyn ? cap : std::max(1, std::min(items, cap)), grid.y);
       hipLaunchKernelGGL((k_seg_grad_sq<T, D, Ops>), sq, dim3(NT), 0, st, segs);
       break;
@@ -3573,7 +3574,7 @@ static void stage_seg128(int stage, const Launch& L, const Range& rg, double ur)
   const int parts = (L.flags & RUN_RAWDG) ? 2 : 1;
   const Range all = {0, L.uniformN, 0, L.uniformP, rg.kbase};
   const Work dyn = L.dyn ? Work{L.descs, 0, 0, nullptr, Range{0, 0, 0, 0, 0}, L.dyn} : Work{};
-  const Work segs = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * rg.c_n * seg_count(128, L.chunk), nullptr, rg, nullptr};
+  const Work segs = L.dyn ? dyn : Work{L.descs, L.nprob, L.nprob * rg.c_n * seg_count(L.chunk, seg_max(128, L.chunk, false)), nullptr, rg, nullptr};
   const int cap = kScratchSlots;  // each workgroup owns a region of the scratch
   switch (stage) {
     case ST_PLAN: {

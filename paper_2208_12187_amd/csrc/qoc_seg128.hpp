@@ -503,7 +503,7 @@ __global__ __launch_bounds__(512) void k_seg_join128(Work W, void* scratch) {
     int p, c;
     split_item(item, W.rg.c_lo, W.rg.c_n, I.start, I.nprob, p, c);
     const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
-    const int k1 = min(P.N, (c + 1) * P.L), h = seg_len(P.D, P.L);
+    const int k1 = min(P.N, (c + 1) * P.L), h = seg_len(P.L, P.SM);
     Panel128 S;
     panel_load(S, pf_mat<float, 128>(P.xprev, c * P.L - W.rg.kbase), L);
     for (int k = c * P.L + h; k < k1; k += h) {  // S <- S + (T - I) S, as in k_seg_join
