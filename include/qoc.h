@@ -243,7 +243,7 @@ int qoc_gradient_dev_noalloc(int B, int d, int m, int N, const void* H0, const v
  * (qoc_slice_plan), and the derivative is the plan's truncated Frechet series
  * taken between the costate and the state.  With d <= 64, N >= 64 and a batch
  * that single chains would not fill the chip with (FP32 512, 256 and 64
- * problems at d <= 16, 32 and 64, FP64 512, 96 and 32), the N slices are cut
+ * problems at d <= 16, 32 and 64, FP64 512, 96 and 24), the N slices are cut
  * into chunks whose propagators are formed; results of batches on different
  * sides of that line differ by rounding.  FP64
  * and FP32 only (QOC_BF16X3 returns QOC_ERR_UNSUPPORTED); opt->validate also

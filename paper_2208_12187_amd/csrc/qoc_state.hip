@@ -772,14 +772,15 @@ int sfail(int code, const char* fmt, ...) {
 // Slices per chunk: the chunks' propagators cost matrix products (B N D^3 of
 // them in all) and shorten the chain of N slices to about 2 sqrt(8 N) steps, so
 // the line is the batch at which single chains would fill the chip as well.
-// N = 500, gradient, single chain -> chunked (ms): FP32 d = 16, B = 512 1.60 ->
-// 1.19; d = 32, B = 256 2.33 -> 1.72; d = 64, B = 64 2.36 -> 1.68, B = 16 1.78 ->
-// 0.58.  FP64 d = 16, B = 512 5.1 -> 4.1; d = 32, B = 64 3.8 -> 2.7, B = 256 7.2 ->
-// 9.5; d = 64, B = 16 4.9 -> 3.3, B = 64 9.8 -> 13.1.  Below 64 slices the chunks
-// are too short to gain.
+// Gradient, single chain -> chunked (ms), N = 500: FP32 d = 16, B = 512 1.55 ->
+// 1.11; d = 32, B = 256 2.27 -> 1.60; d = 64, B = 64 2.36 -> 1.69, B = 16 1.75 ->
+// 0.58.  FP64 d = 16, B = 512 5.2 -> 4.1; d = 32, B = 96 4.3 -> 3.5, B = 256 7.2 ->
+// 9.5; d = 64, B = 16 3.5 -> 2.5, B = 24 3.8 -> 3.6, B = 32 4.1 -> 4.6; N = 2000, d = 64:
+// B = 24 14.7 -> 13.6, B = 32 15.9 -> 17.9.  Below 64 slices the chunks are too short to
+// gain.
 int state_chunk(int B, int D, int N, int precision) {
   const bool f64 = precision == QOC_FP64;
-  const int most = D == 16 ? 512 : D == 32 ? (f64 ? 96 : 256) : f64 ? 32 : 64;
+  const int most = D == 16 ? 512 : D == 32 ? (f64 ? 96 : 256) : f64 ? 24 : 64;
   if (D > 64 || B > most || N < 64) return N;
   return qoc::engine_chunk(N);
 }
