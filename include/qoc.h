@@ -254,7 +254,10 @@ int qoc_gradient_dev_noalloc(int B, int d, int m, int N, const void* H0, const v
  * grad [B][m][N], the other inputs as for qoc_gradient_dev; workspace of
  * qoc_state_workspace_size(B, d, m, N, precision) bytes (0 for invalid sizes),
  * 256-byte aligned, contents clobbered; calls sharing it must be ordered on
- * one stream.  Errors as for the other entry points.
+ * one stream.  The size includes the chunks' propagators and so does not grow
+ * steadily with B and N: a call with less than its own size, but room for single
+ * chains (as in a workspace sized for a larger batch or more slices), runs as
+ * single chains.  Errors as for the other entry points.
  */
 size_t qoc_state_workspace_size(int B, int d, int m, int N, int precision);
 

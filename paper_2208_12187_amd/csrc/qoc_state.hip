@@ -791,7 +791,7 @@ struct StateLayout {
   size_t esize, desc_bytes, Hint, norms, mono, sq, psi, lam, tf, small, per_prob, total;
 };
 
-StateLayout make_state_layout(int B, int d, int m, int N, int precision) {
+StateLayout make_state_layout(int B, int d, int m, int N, int precision, bool chunked = true) {
   using qoc::align_up;
   StateLayout Lo;
   Lo.D = qoc::padded_dim(d);
@@ -804,7 +804,7 @@ StateLayout make_state_layout(int B, int d, int m, int N, int precision) {
   Lo.sq = o; o = align_up(o + (size_t)N * 4);
   Lo.psi = o; o = align_up(o + (size_t)(N + 1) * vec);
   Lo.lam = o; o = align_up(o + (size_t)(N + 1) * vec);
-  Lo.L = state_chunk(B, Lo.D, N, precision);
+  Lo.L = chunked ? state_chunk(B, Lo.D, N, precision) : N;
   Lo.P = (N + Lo.L - 1) / Lo.L;
   Lo.tf = o; o = align_up(o + (Lo.P > 1 ? (size_t)Lo.P * mat : 0));
   Lo.small = o; o = align_up(o + 128);
@@ -842,7 +842,10 @@ int run_state_dev(int B, int d, int m, int N, const void* H0, const void* Hc, co
   if (!with_grad && !psiN) return sfail(QOC_ERR_ARG, "psiN must be non-null");
   if (!ws) return sfail(QOC_ERR_ARG, "workspace must be non-null");
   if (((uintptr_t)ws) % qoc::kAlign) return sfail(QOC_ERR_ARG, "workspace must be 256-byte aligned");
-  const StateLayout Lo = make_state_layout(B, d, m, N, opt.precision);
+  StateLayout Lo = make_state_layout(B, d, m, N, opt.precision);
+  // Without room for the chunk totals (a workspace sized for a batch beyond the line of
+  // state_chunk, or for another N), single chains.
+  if (ws_bytes < Lo.total) Lo = make_state_layout(B, d, m, N, opt.precision, false);
   if (ws_bytes < Lo.total) return sfail(QOC_ERR_ARG, "workspace holds %zu bytes, %zu needed", ws_bytes, Lo.total);
 
   char* base = static_cast<char*>(ws);

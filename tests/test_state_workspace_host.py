@@ -23,3 +23,34 @@ def test_batches_that_are_cut_into_chunks(d, prec, last, N):
         assert abs(_totals(B, d, N, prec) - chunks * mat) < 1024
     assert abs(_totals(last + 1, d, N, prec)) < 1024
     assert abs(_totals(1, d, 63, prec)) < 1024
+
+
+def _launches(B, d, N, prec, ws_bytes):
+    """Whether the call passes the check of its workspace.  Without a device it then
+    ends with the device error of the descriptor upload, before any launch."""
+    import ctypes
+
+    import torch
+
+    if torch.cuda.is_available():
+        pytest.skip("host pointers stand in for device memory")
+    L = qoc.lib()
+    o = qoc.options(prec)
+    buf = ctypes.create_string_buffer(4096)
+    p = (ctypes.addressof(buf) + 255) // 256 * 256
+    rc = L.qoc_state_gradient_dev(B, d, 12, N, p, p, p, 0.01, p, p, p, p, p, ws_bytes, ctypes.byref(o))
+    assert rc in (-1, -5), L.qoc_last_error()
+    return rc == -5
+
+
+@pytest.mark.parametrize("d,prec,N,M", [(64, "fp32", 2000, 2000), (64, "fp64", 2000, 2000), (16, "fp32", 500, 500),
+                                        (64, "fp32", 72, 73), (32, "fp64", 128, 129), (64, "fp64", 63, 64)])
+def test_a_workspace_of_a_larger_call_is_accepted(d, prec, N, M):
+    """A workspace sized for B problems of M slices serves every smaller batch of
+    N <= M, whether those are cut into chunks or not."""
+    for B in (1, 24, 25, 32, 64, 65, 200, 513, 600):
+        size = qoc.state_workspace_size(B, d, 12, M, prec)
+        for b in {b for b in (1, 2, B // 2, B - 1, B) if 1 <= b <= B}:
+            assert _launches(b, d, N, prec, size), (B, b)
+    # less than single chains take is refused
+    assert not _launches(4096, d, N, prec, qoc.state_workspace_size(4096, d, 12, N, prec) - 1)
