@@ -78,9 +78,9 @@ typedef struct {
                              the host and ignore it: a non-Hermitian or non-finite
                              input gives unspecified results there, never an error. */
   uint64_t hbm_budget;    /* bytes for the per-slice and per-chunk arrays of a call
-                             (four arrays of one stored matrix per slice, five in
-                             QOC_FP32, three at d <= 16; the segmented Hermitian
-                             path fills few of them); 0 = no limit.
+                             (four arrays of one stored matrix per slice, three at
+                             d <= 16; QOC_FP32 at d > 16 counts a fifth, which it
+                             does not use); 0 = no limit.
                              When those arrays exceed it, slices are
                              processed in checkpoint segments and recomputed
                              for the gradient pass (same results, more work).
