@@ -185,7 +185,7 @@ __device__ __forceinline__ void prep_one(const ProbDesc& P, int mat, double* col
         gp(dst)[row * D + col] = tr[q];
         gp(dst)[D * D + row * D + col] = ti[q];
         nz[q] = __ballot(tr[q] != (T)0 || ti[q] != (T)0) & rowmask;
-        pz[q] = __ballot(pr != 0.0 || pi != 0.0) & rowmask;
+        pz[q] = __ballot((T)pr != (T)0 || (T)pi != (T)0) & rowmask;  // (as its own table has them)
       }
       if (gen) {  // row sums, for the infinity norm
 #pragma unroll
