@@ -667,23 +667,29 @@ struct StdOps {
   }
   // The same product in the three-product form where it pays: D >= 32.  At
   // D = 16 in FP32 its registers cost more occupancy than the saved MFMAs; in FP64
-  // it is faster (one gradient of N = 1000 82 us instead of 87, 32 of them 408
-  // instead of 452), but its errors add up over the slices: X_N 2.0e-15 from 80-bit
-  // arithmetic instead of 1.6e-15.
+  // its errors would add up over the slices of a chain (X_N of N = 1000 2.0e-15
+  // from 80-bit arithmetic instead of 1.6e-15), and only the products whose errors
+  // stay local (mul) take it.
   template <int PAIRS = 1>
   __device__ static __forceinline__ void gemm3(Panel<T, D>& acc, const void* lds, const Panel<T, D>& P,
                                                const Lane& L, bool zero_acc) {
     if constexpr (D >= 32) cgemm3m<T, D, PAIRS>(acc, static_cast<const T*>(lds), P, L, zero_acc);
     else cgemm(acc, static_cast<const T*>(lds), P, L, zero_acc);
   }
+  // Products of exponentials and commutator series (FP64 at D = 16, the series of 32
+  // problems of N = 1000: the gradient 414 us instead of 453).
+  __device__ static __forceinline__ void local(Panel<T, D>& acc, const void* lds, const Panel<T, D>& P, const Lane& L) {
+    if constexpr (D >= 32 || sizeof(T) == 8) cgemm3m<T, D>(acc, static_cast<const T*>(lds), P, L, true);
+    else cgemm(acc, static_cast<const T*>(lds), P, L, true);
+  }
   __device__ static __forceinline__ void mul(Panel<T, D>& acc, const void* lds, const Panel<T, D>& P, const Lane& L) {
-    gemm3(acc, lds, P, L, true);
+    local(acc, lds, P, L);
   }
   // with work on the row blocks that depends on nothing here
   template <typename Side>
   __device__ static __forceinline__ void mul(Panel<T, D>& acc, const void* lds, const Panel<T, D>& P, const Lane& L,
                                              Side side) {
-    gemm3(acc, lds, P, L, true);
+    local(acc, lds, P, L);
 #pragma unroll
     for (int rb = 0; rb < D / 16; ++rb) side(rb);
   }
@@ -691,7 +697,7 @@ struct StdOps {
   __device__ static __forceinline__ void mul_ct(Panel<T, D>& acc, const void* a, const void* b, const Lane& L) {
     Panel<T, D> P;
     load_ct(P, b, L);
-    gemm3(acc, a, P, L, true);
+    local(acc, a, P, L);
   }
 };
 
