@@ -825,9 +825,9 @@ void k_expm(Work W) {
   __shared__ __align__(16) unsigned char lds[Ops::BYTES];
   Lane L;
   const Items I(W);
-  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+  if ((int)blockIdx.x >= I.total) return;  // (one item per workgroup)
   int p, k;
-  split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
+  split_item((int)blockIdx.x, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
   const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
   int s, q, qb;
   const int sqk = gp(P.sq)[k];
@@ -857,9 +857,6 @@ void k_expm(Work W) {
     panel_axpby(R, (T)1, acc, (T)2);
   }
   panel_store(pf_mat<T, D>(P.delta, k - W.rg.kbase), R, L);
-  break;  // one item per workgroup: a single-trip loop
-  __syncthreads();
-  }
 }
 
 // ---------------------------------------------------------------- re-unitarisation
@@ -963,9 +960,9 @@ void k_scan_local(Work W, int dir) {
   const int bwd = dir < 0 ? (int)blockIdx.y : dir;  // dir < 0: both passes, one per blockIdx.y
   Lane L;
   const Items I(W);
-  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+  if ((int)blockIdx.x >= I.total) return;  // (one item per workgroup)
   int p, c;
-  split_item(item, W.rg.c_lo, W.rg.c_n, I.start, I.nprob, p, c);
+  split_item((int)blockIdx.x, W.rg.c_lo, W.rg.c_n, I.start, I.nprob, p, c);
   const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
   const int k0 = c * P.L;
   const int k1 = min(P.N, k0 + P.L);
@@ -989,9 +986,6 @@ void k_scan_local(Work W, int dir) {
     k = kn;
   }
   if (!bwd && !W.rg.recompute) panel_store(pf_mat<T, D>(P.tf, c), S, L);  // (k_reun follows in FP32)
-  break;  // one item per workgroup: a single-trip loop
-  __syncthreads();
-  }
 }
 
 // The re-unitarisation of the forward chunk totals tf[c] (FP32, problems with
@@ -1396,9 +1390,9 @@ void k_adjoint(Work W) {
   __shared__ __align__(16) float eg[GATHER ? 2 * kSampleGather * D : 1];
   Lane L;
   const Items I(W);
-  for (int item = blockIdx.x; item < I.total; item += gridDim.x) {
+  if ((int)blockIdx.x >= I.total) return;  // (one item per workgroup)
   int p, k;
-  split_item(item, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
+  split_item((int)blockIdx.x, W.rg.s_lo, W.rg.s_n, I.start, I.nprob, p, k);
   const ProbDesc P = W.descs[I.desc(p)];  // a copy: stores cannot alias it
   const int sqk = gp(P.sq)[k];
   int s, q, qb;
@@ -1519,9 +1513,6 @@ void k_adjoint(Work W) {
 
   // 5. inner products with the controls (FP64), then the gradient
   gradient_epilogue<T, D>(P, k, A2, L, lds[0], red, mono);
-  }
-  break;  // one item per workgroup: a single-trip loop
-  __syncthreads();
   }
 }
 
