@@ -276,10 +276,8 @@ __device__ __forceinline__ void prep_one(const ProbDesc& P, int mat, double* col
   }
 }
 
-// Convert the caller's complex128 matrices to the compute precision: H0 and
-// Hc[j] to planar D x D (zero padded), V to PF; also the FP64 one-norms
-// (largest column sum of moduli) of H0 and Hc[j].  Items: (problem, matrix
-// index 0..m+1) with index m+1 standing for V; 256 threads per item.
+// Items: (problem, matrix index 0..m+1) with index m+1 standing for V; 256
+// threads per item.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_prep(Work W) {
   __shared__ double colmax[256];
@@ -295,8 +293,7 @@ __global__ __launch_bounds__(256) void k_prep(Work W) {
 
 // Per slice: theta = dt (|H0|_1 + sum_j |u[j][k]| |Hc[j]|_1) in FP64, then the
 // scaling exponent and Taylor degrees of choose_plan().
-// flags: bit 0 gradient, bit 1 the expm evaluates by Paterson-Stockmeyer
-// (FP32 at D = 128), bit 2 the gradient takes the commutator series.
+// flags: PlanFlags.
 __global__ __launch_bounds__(256) void k_plan(Work W, double ur, int flags) {
   const Items I(W);
   for (int item = blockIdx.x * 256 + threadIdx.x; item < I.total; item += gridDim.x * 256) {

@@ -13,16 +13,15 @@
 //    |E| r^qb/qb! * 1/(1 - r/(qb+1)); qb (>= 2) is the least degree for which
 //    the factor of |E| is at most ur.
 //  * commutator series sum_n ad_X^n / n! and sum_n ad_X^n / (n + 1)! (Hermitian
-//    path at d <= 64): |ad_X| <= 2 r, so the exponential's rule at 2 r bounds
-//    both remainders; m is that degree.
+//    path, but FP64 at d > 64): |ad_X| <= 2 r, so the exponential's rule at 2 r
+//    bounds both remainders; m is that degree.
 // Among s in [s0, s0 + 6], s0 = least s >= 0 with r <= 1, the value that
 // minimises the number of complex d x d products of the path is taken:
 //    exp:       (q - 1) + s    (Horner; expm_products(q) + s where the expm
-//                                 runs Paterson-Stockmeyer: FP32 at D = 128)
+//                                 runs Paterson-Stockmeyer: D = 128;
+//                                 taylor_products(q) + s on segments at D <= 64)
 //    gradient:  + frechet_products(qb) + 3 s   (block polynomial, squarings),
 //               or plan_cost's count for the commutator series
-// (where the adjoint reuses the expm's X^2 it saves one product for every s
-// alike, so the choice does not depend on that).
 #pragma once
 
 #include <math.h>
@@ -93,7 +92,8 @@ QOC_HD inline int taylor_products(int q) { return q <= 3 ? q - 1 : (q == 4 ? 2 :
 QOC_HD inline int frechet_products(int qb) { return 5 + 3 * (qb > 3 ? (qb - 3) / 2 : 0); }
 
 // comm: the gradient's m products of the commutator series and, for s > 0,
-// the exponential again, s doublings and the step of Y.
+// the exponential again (at D <= 64 it is kept: its count stands for the traffic,
+// and for the slower kernel of squared slices), s doublings and the step of Y.
 QOC_HD inline int plan_cost(int s, int q, int qb, int m, bool grad, bool ps_expm, bool comm) {
   const int expm = ps_expm ? expm_products(q) : comm ? taylor_products(q) : q - 1;
   int cost = expm + s;
