@@ -54,9 +54,9 @@ def permutation_runs(Hc: np.ndarray, group: int = 4):
 
 
 def slice_flops(plan: np.ndarray, d: int, m: int, prec: str, runs=None) -> dict:
-    """MFMA flops per stage of the block form (general generators, and FP64 at
-    d > 64; the Hermitian path's are series_flops) for slices with plan rows
-    (s, q, qb), and the adjoint's count in the conventional 8 d^3 per
+    """MFMA flops per stage of the block form as it was counted for Hermitian
+    problems (hermitian_flops takes its FP64 adjoint at d > 64) for slices with plan
+    rows (s, q, qb), and the adjoint's count in the conventional 8 d^3 per
     complex product ("adjoint_8d3").
 
     Complex d x d products per slice: expm q - 1 + s (Horner; at d > 64 in
@@ -98,35 +98,61 @@ def slice_flops(plan: np.ndarray, d: int, m: int, prec: str, runs=None) -> dict:
             "adjoint_valu": valu}
 
 
-def series_orders(problems, plan: np.ndarray, prec: str) -> np.ndarray:
+def series_orders(problems, plan: np.ndarray, prec: str, d: int = 64) -> np.ndarray:
     """Orders of the commutator series per slice: the least n with
-    x^(n+1)/(n+1)! <= ur (1 - x/(n+2)), x = 2 theta / 2^s, as the plan picks them
-    at d <= 64."""
+    x^(n+1)/(n+1)! <= ur (1 - x/(n+2)), x = 2 theta / 2^s, as the plan picks them.
+    At d > 64 Horner's rule also needs the n at which the remainder of the sum of
+    x^n/(n+1)! is met, and takes two products at least."""
     ur = 2.0 ** -53 if prec == "fp64" else 2.0 ** -24
     n1 = lambda H: np.abs(H).sum(axis=0).max()
     theta = np.concatenate([p.dt * (n1(p.H0) + np.abs(p.u).T @ np.array([n1(H) for H in p.Hc])) for p in problems])
     x = 2 * theta / 2.0 ** plan[:, 0]
-    n = np.ones(len(x))
-    t = x * x / 2
-    for k in range(1, 30):
-        on = (t > ur * (1 - x / (k + 2))) & (n == k)
-        n[on] = k + 1
-        t = t * x / (k + 2)
-    return n
+
+    def least(t):  # n from 1 while the term that starts at t stays above the bound
+        n = np.ones(len(x))
+        for k in range(1, 30):
+            on = (t > ur * (1 - x / (k + 2))) & (n == k)
+            n[on] = k + 1
+            t = t * x / (k + 2)
+        return n
+
+    n = least(x * x / 2)
+    return n if d <= 64 else np.maximum(np.maximum(n, least(x / 2)), 2)
 
 
 def series_flops(problems, plan: np.ndarray, d: int, prec: str) -> dict:
-    """Matrix-core flops of the Hermitian path at 16 < d <= 64 over all slices (s = 0;
-    the doublings of s > 0 are not counted): the exponential's products, one chain
-    product and the series' one product per order.  FP32 (and split BF16, which
-    runs the same kernels) takes three FP16 products per real one, 24 d^3 flops per
-    complex product, and its chain in FP32 by the three-product form, 6 d^3; FP64
-    takes the latter throughout."""
-    q, m = plan[:, 1], series_orders(problems, plan, prec)
-    n_exp = np.where(q <= 3, q - 1, np.where(q == 4, 2, np.where(q <= 8, 3, 2 + (q - 1) // 3)))
+    """Matrix-core flops of the segmented Hermitian path (d <= 64, and FP32 at d = 128)
+    over all slices: the exponential's products (its form by q at d <= 64,
+    Paterson-Stockmeyer in X^2 and 128), its s squarings, one chain product and the
+    series' one product per order; with s > 0 also the gradient's doublings, two
+    products for Z and one squaring each, and two for Y (at d <= 64 the last squaring is
+    the forward pass's; at d = 128 the exponential is formed again).  FP32 (and split BF16,
+    which runs the same kernels) takes three FP16 products per real one, 24 d^3 flops
+    per complex product, and its chain in FP32 by the three-product form, 6 d^3 (at
+    d = 16 by the four-product form, 8 d^3); FP64 takes three products per complex one,
+    at d = 16 four in its chain."""
+    s, q, m = plan[:, 0], plan[:, 1], series_orders(problems, plan, prec, d)
+    if d > 64:
+        n_exp = np.where(q < 2, 0, np.where(q == 2, 1, 2 + (q - 3) // 2))
+        n_adj = m - (s > 0) + np.where(s > 0, n_exp + 3 * s + 2, 0)
+    else:
+        n_exp = np.where(q <= 3, q - 1, np.where(q == 4, 2, np.where(q <= 8, 3, 2 + (q - 1) // 3)))
+        n_adj = m + np.where(s > 0, 3 * s - (d > 16) + 2, 0)
     g = 6.0 * d ** 3 if prec == "fp64" else 24.0 * d ** 3
-    return {"expm": float(g * n_exp.sum()), "chain": 6.0 * d ** 3 * len(q), "adjoint": float(g * m.sum()),
-            "adjoint_8d3": float(8.0 * d ** 3 * m.sum())}
+    chain = 8.0 if d <= 16 else 6.0
+    return {"expm": float(g * (n_exp + s).sum()), "chain": chain * d ** 3 * len(q), "adjoint": float(g * n_adj.sum()),
+            "adjoint_8d3": float(8.0 * d ** 3 * n_adj.sum())}
+
+
+def hermitian_flops(problems, plan: np.ndarray, d: int, m: int, prec: str) -> dict:
+    """Matrix-core flops of a gradient of Hermitian problems, and the kernel of its
+    adjoint stage: segments, but the block form in FP64 at d > 64, whose exponential
+    runs Paterson-Stockmeyer."""
+    if d <= 64 or prec != "fp64":
+        return dict(series_flops(problems, plan, d, prec), kernel="k_seg_grad" if d <= 64 else "k_seg_grad128")
+    s, q = plan[:, 0], plan[:, 1]
+    n_exp = np.where(q < 2, 0, np.where(q == 2, 1, 2 + (q - 3) // 2)) + s
+    return dict(slice_flops(plan, d, m, prec), expm=float(8.0 * d ** 3 * n_exp.sum()), kernel="k_adjoint128")
 
 
 def worst_rel_grad_err(grad, ref):
@@ -172,12 +198,12 @@ def time_runner(qoc, torch, runner, batch, steps, warmup):
 
 
 def measured_traffic(kernel_avg_ms):
-    """HBM bytes per launch of the adjoint kernel from the committed rocprofv3
+    """HBM bytes per launch of the gradient kernel from the committed rocprofv3
     counter summary (FETCH_SIZE and WRITE_SIZE, each scaled by its reading for a
     plain 1 GiB copy), or None when the kernel sources changed since then."""
     import hashlib
 
-    path = os.path.join(ROOT, "profiles", "k_adjoint_counters.json")
+    path = os.path.join(ROOT, "profiles", "k_seg_grad_counters.json")
     csrc = os.path.join(ROOT, "paper_2208_12187_amd", "csrc")
     try:
         with open(path) as f:
@@ -420,7 +446,7 @@ def main():
     batch = qoc.Batch.from_problems(problems)
     plans = {pr: np.concatenate([qoc.slice_plan(p.H0, p.Hc, p.u, p.dt, pr, True) for p in problems])
              for pr in ("fp32", "fp64", "bf16x3")}
-    flops = {pr: series_flops(problems, plans[pr], d, pr) for pr in plans}
+    flops = {pr: hermitian_flops(problems, plans[pr], d, m, pr) for pr in plans if pr != "bf16x3" or 16 < d <= 64}
     flops_dense = flops[args.precision]
 
     def leg(prec, steps, bsz=B, bat=batch, dense_controls=False):
@@ -445,14 +471,14 @@ def main():
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(achieved / peak, 4), "traffic": None if traffic is None else round(traffic),
                 "traffic_source": None if traffic is None else
-                ("stored rocprofv3 reading (profiles/k_adjoint_counters.json: FETCH_SIZE + WRITE_SIZE per "
+                ("stored rocprofv3 reading (profiles/k_seg_grad_counters.json: FETCH_SIZE + WRITE_SIZE per "
                  "dispatch, each scaled by its reading for a plain 1 GiB copy), used because its kernel-source "
                  "hash matches this build; not measured in this run"),
-                "kernel": "k_seg_grad", "avg_launch_ms": round(adj_ms / max(adj_n, 1), 4),
+                "kernel": flops[args.precision]["kernel"], "avg_launch_ms": round(adj_ms / max(adj_n, 1), 4),
                 "cgemm_8d3_tflops": round(flops[args.precision]["adjoint_8d3"] / adj_avg_s / 1e12, 2)}
 
     def path_flops(pr):
-        return sum(v for k, v in flops[pr].items() if k != "adjoint_8d3")
+        return sum(v for k, v in flops[pr].items() if k not in ("adjoint_8d3", "kernel"))
 
     total_flops = path_flops(args.precision)
     stages = {k: round(v[0] / max(v[1], 1), 4) for k, v in head["stages"].items() if v[1]}
@@ -487,7 +513,8 @@ def main():
         extra["bf16x3"] = {"value": round(v3, 1), "ms_per_step": round(b3["ms_per_step"], 3),
                            "stages_ms": {k: round(v[0] / max(v[1], 1), 4) for k, v in b3["stages"].items() if v[1]},
                            "adjoint_fp32_equiv_tflops": round(flops["bf16x3"]["adjoint_8d3"] / (adj3_ms / max(adj3_n, 1) / 1e3) / 1e12, 2),
-                           "adjoint_bf16_mfma_frac": round(flops["bf16x3"]["adjoint"] / (adj3_ms / max(adj3_n, 1) / 1e3)
+                           # (Hermitian problems run the FP32 precision's split-FP16 kernels)
+                           "adjoint_mfma_frac": round(flops["bf16x3"]["adjoint"] / (adj3_ms / max(adj3_n, 1) / 1e3)
                                                            / 1e12 / PEAK_TFLOPS["bf16x3"], 4),
                            "max_abs_dF_vs_fp32": float(np.max(np.abs(b3["F"] - head["F"]))),
                            "grad_err_vs_fp32": worst_rel_grad_err(b3["grad"], head["grad"])}
