@@ -189,16 +189,17 @@ inline int engine_chunk(int N) { return std::max(1, (int)ceil(sqrt(N / 8.0))); }
 // even as they come.  Longer segments spare the products at their starts and
 // joins, shorter ones fill the chip with a run of few slices (whose chunks are
 // short): d = 60, m = 7, N = 60, two problems, FP32: 324 us with eight, 201 with
-// two.  d = 16, one problem of N = 1000 (forward, joins, gradient in us): 14 + 21 +
-// 20 with one, 19 + 12 + 30 with two, 30 + 8 + 47 with four.  d = 128, eight
+// two.  d = 16, one problem of N = 1000 in FP64 (forward, joins, gradient in us): 11 +
+// 19 + 15 with one, 16 + 11 + 24 with two, 26 + 6 + 40 with four; 32 problems, the whole
+// call, 441 with one and 414 with two.  d = 128, eight
 // problems of N = 1000: joins 0.49 and gradient 2.50 ms with four, 0.34 and 2.40
 // with eight, which leaves half the chip to one problem.  FP64, whose products take
-// more than twice as long, takes shorter ones: one call in us, d = 16, N = 100 75 with
-// two, 62 with one (32 problems 107 and 112); d = 60, N = 60, two problems 532 with two, 390 with
+// more than twice as long, takes shorter ones: one call in us, d = 16, N = 300 73 with
+// two, 66 with one (with s > 0 113 and 90; 32 problems 182 and 182); d = 60, N = 60, two problems 532 with two, 390 with
 // one; d = 32, N = 1000 324 with four, 238 with two (32 problems 2301 and 2408).
 constexpr int kSegMax = 8;
 inline int seg_max(int D, int L, bool f64) {
-  if (f64 && D <= 64) return L <= (D == 16 ? 12 : 8) ? 1 : D == 16 || L <= 24 ? 2 : D == 32 ? 4 : kSegMax;
+  if (f64 && D <= 64) return L <= (D == 16 ? 14 : 8) ? 1 : D == 16 || L <= 24 ? 2 : D == 32 ? 4 : kSegMax;
   return D == 16 || L <= (D == 128 ? 12 : 16) ? 2 : D == 128 || L <= 24 ? 4 : kSegMax;
 }
 __host__ __device__ inline int seg_count(int L, int most) { return (L + most - 1) / most; }

@@ -9,8 +9,8 @@
 
 ``trace`` prints the per-kernel table of a ``--kernel-trace --stats`` run.
 ``mfma`` reads a run with the derived counters MfmaUtil (MFMA-busy cycles
-over GPU-active cycles times the SIMD count, in percent) and MfmaFlopsF32 /
-MfmaFlopsF64 / MfmaFlopsBF16 (512 times the MFMA operation counts) and prints
+over GPU-active cycles times the SIMD count, in percent) and MfmaFlopsF16 /
+MfmaFlopsF32 / MfmaFlopsF64 (512 times the MFMA operation counts) and prints
 their per-dispatch means for every kernel.
 ``sq`` reads a run with wave-state counters (SQ_WAVE_CYCLES, SQ_WAIT_ANY,
 SQ_WAIT_INST_ANY, SQ_ACTIVE_INST_VALU, SQ_ACTIVE_INST_LDS,
@@ -21,7 +21,7 @@ the LDS-active cycles).
 command, calibrates each counter against the plain device-to-device copy of
 ``copy GiB`` that the bench makes before timing (``--copy-gib``; the copy
 reads and writes exactly that many bytes), and prints per-kernel HBM bytes.
-With a json path it also records the FP32 d = 64 adjoint's per-launch
+With a json path it also records the FP32 d = 64 gradient kernel's per-launch
 counters, the calibration factors and a hash of the kernel sources, which
 the bench uses for the ``traffic`` field while the sources are unchanged.
 """
@@ -36,9 +36,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
-# The FP32 d = 64 adjoint stage: its instances (the slices with and without the
-# sampled last step) are summed per launch of the stage.
-ADJOINT = "qoc::k_adjoint<float, 64, qoc::StdOps<float, 64>, false"
+# The FP32 d = 64 gradient kernel of the segmented path.
+GRADIENT = "qoc::k_seg_grad<float, 64, qoc::F16Ops<64>, false"
 
 
 def short(name: str) -> str:
@@ -93,23 +92,23 @@ def bytes_table(fetch_csv: str, write_csv: str, copy_gib: float, json_out: str |
         w = sum(wv[k]) / len(wv[k])
         lines.append(f"| `{k}` | {len(fv[k])} | {f:.1f} | {w:.1f} | {f * fs * 1.024e-3:.1f} | {w * ws * 1.024e-3:.1f} |")
     if json_out:
-        inst = [k for k in fv if k.startswith(ADJOINT)]
+        inst = [k for k in fv if k.startswith(GRADIENT)]
         if not inst:
-            raise SystemExit(f"no {ADJOINT}...> dispatch in {fetch_csv}")
+            raise SystemExit(f"no {GRADIENT}...> dispatch in {fetch_csv}")
         f = sum(sum(fv[k]) / len(fv[k]) for k in inst)
         w = sum(sum(wv[k]) / len(wv[k]) for k in inst)
         with open(json_out, "w") as fh:
-            json.dump({"kernel": "k_adjoint<float, 64>", "fetch_kib": f, "write_kib": w, "fetch_scale": fs,
+            json.dump({"kernel": "k_seg_grad<float, 64>", "fetch_kib": f, "write_kib": w, "fetch_scale": fs,
                        "write_scale": ws, "csrc_sha256": csrc_sha256(),
                        "workload": "fp32 d=64 m=12 N=2000 batch 32"}, fh, indent=1)
     return "\n".join(lines)
 
 
 def mfma_table(path: str) -> str:
-    names = ("MfmaUtil", "MfmaFlopsF32", "MfmaFlopsF64", "MfmaFlopsBF16")
+    names = ("MfmaUtil", "MfmaFlopsF16", "MfmaFlopsF32", "MfmaFlopsF64")
     vals = {n: per_kernel(path, n) for n in names}
     kernels = [k for k in vals["MfmaUtil"] if k.startswith("qoc::")]
-    out = ["| kernel | dispatches | MFMA busy % | MFMA GFLOP per dispatch (F32 / F64 / BF16) |", "|---|---|---|---|"]
+    out = ["| kernel | dispatches | MFMA busy % | MFMA GFLOP per dispatch (F16 / F32 / F64) |", "|---|---|---|---|"]
     for k in kernels:
         u = vals["MfmaUtil"][k]
         fl = [sum(vals[n].get(k, [0.0])) / max(len(vals[n].get(k, [])), 1) / 1e9 for n in names[1:]]
