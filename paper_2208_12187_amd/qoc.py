@@ -419,7 +419,8 @@ class JacobianRunner(Runner):
         self.generators = self.dense_controls = False
         self.B, self.d, self.m, self.N = 1, d, m, N
         self.precision, self.chunk, self.hbm_budget = precision, 0, 0
-        self.ws_bytes = int(lib().qoc_jacobian_workspace_size(d, m, N, PRECISIONS[precision]))
+        p = PRECISIONS[precision] if isinstance(precision, str) else int(precision)
+        self.ws_bytes = int(lib().qoc_jacobian_workspace_size(d, m, N, p))
         self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=device)
         # X_N where the caller gives no buffer for it.  The kernels read it back, on a
         # stream that need not be the current one: like the workspace it is the runner's.

@@ -80,3 +80,11 @@ def test_a_jacobian_elsewhere_is_refused(setup):
     X = torch.zeros((D, D), dtype=torch.complex128)
     r.jacobian(b, J, XN=X, stream=STREAM)
     assert rec.XN == X.data_ptr()
+
+
+@pytest.mark.parametrize("name", ["fp64", "fp32"])
+def test_precision_by_number(name):
+    """As for Runner (and GrapeLSQ, which makes one of each): a name or its number."""
+    a = qoc.JacobianRunner(D, M, N, name, device="cpu")
+    b = qoc.JacobianRunner(D, M, N, qoc.PRECISIONS[name], device="cpu")
+    assert a.ws_bytes == b.ws_bytes > 0
