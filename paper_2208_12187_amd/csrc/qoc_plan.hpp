@@ -122,6 +122,9 @@ enum PlanFlags : int { PLAN_GRAD = 1, PLAN_PS = 2, PLAN_COMM = 4, PLAN_HORNER = 
 
 QOC_HD inline SlicePlan choose_plan(double theta, double ur, int flags) {
   const bool grad = (flags & PLAN_GRAD) != 0, ps_expm = (flags & PLAN_PS) != 0, comm = (flags & PLAN_COMM) != 0;
+  // Infinite or NaN: nothing to compute, and no squarings (the state path takes 2^s steps).
+  // By comparison: theta - theta of a product th * dt is contracted to its rounding error.
+  if (!(theta <= 1.7976931348623157e308)) return SlicePlan{0, 1, 2, 1};
   int s0 = 0;
   while (ldexp(theta, -s0) > 1.0 && s0 < 60) ++s0;
   SlicePlan best = {s0, 1, 2, 1};
